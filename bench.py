@@ -399,9 +399,9 @@ def main():
         top = max(rows, key=lambda r: r[2])
         name, la, kms, kfl, kby = top
         if kfl > 0:
-            # operand precision: the direct-to-LDS GEMM and the fused InfoNCE
-            # kernels always multiply BF16; gemm_kernel names its storage type first
-            bf16_in = (name.startswith("gemm_lds_") or name.startswith("gemm_kernel<bf16")
+            # operand precision: the fused InfoNCE kernels and the GEMM launches
+            # that do not name f32 first multiply BF16
+            bf16_in = ((name.startswith("gemm_lds_") and "<f32," not in name)
                        or name.startswith("infonce"))
             peak = PEAK_BF16_TFLOPS if bf16_in else PEAK_FP32_TFLOPS
             ach = kfl / la / (kms * 1e-3 / la) / 1e12

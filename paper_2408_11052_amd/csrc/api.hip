@@ -93,7 +93,7 @@ struct Slots {
 struct Group {
   int nets[2], count;
   std::vector<int64_t> dwp;              // per layer: dW split-K partials, -1 if unsplit
-  std::vector<int> dwbn;                 // per layer: column tile of the LDS kernel (0: dense partials)
+  std::vector<int> dwbn;                 // per layer: block width of its partials (0: unsplit)
   std::vector<int64_t> dwu;              // per layer: with the Adam epilogue, where an
                                          // unsplit dW goes (-1 if split)
   std::vector<RedJob> few, many;         // reduction jobs (few / many parts); the few
@@ -365,13 +365,13 @@ GemmParams dw_params(const crl_ctx* x, const Group& G, int l) {
   int target = 512;
   if (l > 0) {
     GemmParams P1 = P;
-    plan_split_k(P1, x->bf16, 0, 8);  // unsplit: the tile counts
+    plan_split_k(P1, x->bf16, 0, 8);  // unsplit
     const GemmParams Px = dx_params(x, G, l);
-    if (gemm_pair_ok(P1, Px, x->bf16)) {
+    if (x->bf16 && gemm_pair_ok(P1, Px, true)) {
       int64_t tiles = 0, work = 0;
       for (int e = 0; e < G.count; ++e) {
-        tiles += P1.tiles[e];
-        work += (int64_t)Px.tiles[e] * (Px.d[e].K / 64);
+        tiles += gemm_tiles128(P1.d[e]);
+        work += gemm_tiles128(Px.d[e]) * (Px.d[e].K / 64);
       }
       const int64_t ksteps = x->B / 64;
       work += tiles * ksteps;
@@ -387,9 +387,7 @@ GemmParams dw_params(const crl_ctx* x, const Group& G, int l) {
 }
 
 // Whether layer l's dW runs in one launch with its dX (launch_gemm_dw_dx).
-// The dW split-K partials are then in the 128-wide fragment order, also where
-// dW alone would take 64-wide tiles (N <= 64: the output layer).  Shapes
-// decide it; the workspace and every operand are 16-byte aligned.
+// Shapes decide it; the workspace and every operand are 16-byte aligned.
 bool dw_dx_paired(const crl_ctx* x, const Group& G, int l) {
   if (l == 0) return false;
   GemmParams Pw = dw_params(x, G, l);
@@ -425,9 +423,7 @@ void plan_group(crl_ctx* x, int gi, int64_t& off) {
   for (int l = 0; l <= L; ++l) {
     const GemmParams P = dw_params(x, G, l);
     if (P.splits > 1) {
-      // partial layout of the kernel that will run: fragment order on the
-      // direct-to-LDS kernel, dense otherwise
-      const int bn = dw_dx_paired(x, G, l) ? 128 : gemm_lds_bn(P, x->bf16);
+      const int bn = frag_bn(P);
       int64_t ps = 0;
       for (int e = 0; e < G.count; ++e) ps = std::max(ps, frag_partial_floats(P, e, bn));
       G.dwbn[l] = bn;
@@ -439,7 +435,7 @@ void plan_group(crl_ctx* x, int gi, int64_t& off) {
         j.dst = x->net[G.nets[e]].lay[l].w;
         j.nparts = P.splits;
         j.n = (int32_t)j.stride;
-        j.M = P.d[e].M; j.N = P.d[e].N; j.tiles_n = P.tiles_n[e]; j.bn = bn;
+        j.M = P.d[e].M; j.N = P.d[e].N; j.tiles_n = (j.N + bn - 1) / bn; j.bn = bn;
         G.few.push_back(j);
       }
     } else {
@@ -795,13 +791,13 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
       if (paired != (l > 0 && gemm_pair_ok(Pw, Px, x->bf16)))
         return fail(CRL_EINVAL, "internal: dW + dX launch plan mismatch");
       if (Pw.splits > 1) {
-        const int bn = paired ? 128 : gemm_lds_bn(Pw, x->bf16);
+        const int bn = frag_bn(Pw);
         if (bn != G.dwbn[l]) return fail(CRL_EINVAL, "internal: dW partial layout mismatch");
         int64_t ps = 0;
         for (int e = 0; e < count; ++e) ps = std::max(ps, frag_partial_floats(Pw, e, bn));
         Pw.partial = WF(ws, G.dwp[l]);
         Pw.partial_len = (int64_t)Pw.splits * ps;
-        Pw.frag = 1;
+        Pw.frag = bn;
       }
       // bias column partials of this layer (LayerNorm layers get theirs with dZ;
       // top_bias_ready: the output layer's were written with dout)
@@ -819,7 +815,7 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
     }
     if (paired) {
       // both products read dZ; one launch, the dW work items first
-      CRL_HIP(launch_gemm_dw_dx(Pw, Px, s), "dW + dX GEMM");
+      CRL_HIP(launch_gemm_dw_dx(Pw, Px, x->bf16, s), "dW + dX GEMM");
     } else if (grads) {
       CRL_HIP(launch_gemm(Pw, x->bf16, LAY_MC, LAY_MC, false, s), "dW GEMM");
     }

@@ -1,4 +1,4 @@
-// Instantiations and host dispatch of the MFMA GEMM.
+// Instantiations, launch planning and host dispatch of the MFMA GEMM.
 #include "internal.hpp"
 #include "gemm_lds.hpp"
 
@@ -19,69 +19,48 @@ __global__ void splitk_reduce_kernel(GemmParams P) {
     int64_t row = i / D.N, col = i % D.N;
     int64_t o = row * D.ldc + col;
     if (D.epi == EPI_BIAS) s += D.bias[col];
-    if (D.accumulate) s += C[o];
     C[o] = s;
   }
 }
 
-
 template <typename T, int LA, int LB, typename OutT>
-static const char* kernel_name() {
-  static const char* names[2][2][2][2] = {
-      {{{"gemm_kernel<f32,KC,KC,f32>", "gemm_kernel<f32,KC,KC,bf16>"},
-        {"gemm_kernel<f32,KC,MC,f32>", "gemm_kernel<f32,KC,MC,bf16>"}},
-       {{"gemm_kernel<f32,MC,KC,f32>", "gemm_kernel<f32,MC,KC,bf16>"},
-        {"gemm_kernel<f32,MC,MC,f32>", "gemm_kernel<f32,MC,MC,bf16>"}}},
-      {{{"gemm_kernel<bf16,KC,KC,f32>", "gemm_kernel<bf16,KC,KC,bf16>"},
-        {"gemm_kernel<bf16,KC,MC,f32>", "gemm_kernel<bf16,KC,MC,bf16>"}},
-       {{"gemm_kernel<bf16,MC,KC,f32>", "gemm_kernel<bf16,MC,KC,bf16>"},
-        {"gemm_kernel<bf16,MC,MC,f32>", "gemm_kernel<bf16,MC,MC,bf16>"}}}};
-  return names[sizeof(T) == 2][LA][LB][sizeof(OutT) == 2];
-}
-
-template <int LA, int LB, typename OutT, int BN>
 static const char* lds_kernel_name() {
   static const char* names[2][2][2][2] = {
-      {{{"gemm_lds_kernel<KC,KC,f32,64>", "gemm_lds_kernel<KC,KC,bf16,64>"},
-        {"gemm_lds_kernel<KC,MC,f32,64>", "gemm_lds_kernel<KC,MC,bf16,64>"}},
-       {{"gemm_lds_kernel<MC,KC,f32,64>", "gemm_lds_kernel<MC,KC,bf16,64>"},
-        {"gemm_lds_kernel<MC,MC,f32,64>", "gemm_lds_kernel<MC,MC,bf16,64>"}}},
+      {{{"gemm_lds_kernel<f32,KC,KC,f32>", "gemm_lds_kernel<f32,KC,KC,bf16>"},
+        {"gemm_lds_kernel<f32,KC,MC,f32>", "gemm_lds_kernel<f32,KC,MC,bf16>"}},
+       {{"gemm_lds_kernel<f32,MC,KC,f32>", "gemm_lds_kernel<f32,MC,KC,bf16>"},
+        {"gemm_lds_kernel<f32,MC,MC,f32>", "gemm_lds_kernel<f32,MC,MC,bf16>"}}},
       {{{"gemm_lds_kernel<KC,KC,f32>", "gemm_lds_kernel<KC,KC,bf16>"},
         {"gemm_lds_kernel<KC,MC,f32>", "gemm_lds_kernel<KC,MC,bf16>"}},
        {{"gemm_lds_kernel<MC,KC,f32>", "gemm_lds_kernel<MC,KC,bf16>"},
         {"gemm_lds_kernel<MC,MC,f32>", "gemm_lds_kernel<MC,MC,bf16>"}}}};
-  return names[BN == 128][LA][LB][sizeof(OutT) == 2];
+  return names[sizeof(T) == 2][LA][LB][sizeof(OutT) == 2];
 }
 
-// The direct-to-LDS kernel takes a launch whose K ranges are all whole 64-deep
-// steps, with 16-byte rows (ragged M and N are handled by clamped loads and
-// guarded stores).  N not a multiple of 8 is taken only where the results are
-// stored plainly (no mask epilogue, no fragment-order partials): those column
-// tails are stored element by element.  Its column tile is 128 wide, as the
-// planned grid; or 64 wide when no problem is wider than 64 (one column tile
-// either way).
-static int lds_path_bn(const GemmParams& P) {
-  int nmax = 0;
+// What the kernel assumes of its operands (every caller provides it).
+static bool operands_ok(const GemmParams& P, bool bf16) {
+  const int v = bf16 ? 8 : 4;
   for (int g = 0; g < P.count; ++g) {
     const GemmDesc& d = P.d[g];
-    if (d.K % lds::BK || P.k_chunk % lds::BK) return 0;
-    if (d.N % 8 && (P.defer_reduce || (d.epi != EPI_NONE && d.epi != EPI_BIAS))) return 0;
-    if (d.lda % 8 || d.ldb % 8 || d.ldc % 8) return 0;
-    if (d.epi == EPI_L2 || d.epi == EPI_L2SQ || d.accumulate) return 0;
+    if (d.M < 1 || d.N < 1 || d.K < 1 || d.lda % v || d.ldb % v || d.ldc % 8) return false;
     if ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B) |
          reinterpret_cast<uintptr_t>(d.C)) & 15u)
-      return 0;
-    nmax = d.N > nmax ? d.N : nmax;
+      return false;
+    if (d.N % 8 && (d.epi == EPI_MASK_POS || (P.splits > 1 && P.defer_reduce && P.frag)))
+      return false;
   }
+  return true;
+}
+
+int frag_bn(const GemmParams& P) {
+  int nmax = 0;
+  for (int g = 0; g < P.count; ++g) nmax = P.d[g].N > nmax ? P.d[g].N : nmax;
   return nmax > 64 ? 128 : 64;
 }
 
-int gemm_lds_bn(const GemmParams& P, bool bf16) { return bf16 ? lds_path_bn(P) : 0; }
-
 int64_t frag_partial_floats(const GemmParams& P, int g, int bn) {
   const GemmDesc& d = P.d[g];
-  if (bn == 0) return (int64_t)d.M * d.N;
-  return (int64_t)((d.M + lds::BM - 1) / lds::BM) * ((d.N + bn - 1) / bn) * lds::BM * bn;
+  return (int64_t)((d.M + 127) / 128) * ((d.N + bn - 1) / bn) * 128 * bn;
 }
 
 // algorithmic FLOPs and bytes of one launch (the unpadded K)
@@ -101,34 +80,68 @@ static int max_tiles(const GemmParams& P) {
   return maxt;
 }
 
+static int64_t tiles_of(const GemmDesc& d, int edge) {
+  return (int64_t)((d.M + edge - 1) / edge) * ((d.N + edge - 1) / edge);
+}
+static int64_t tiles_of(const GemmParams& P, int edge) {
+  int64_t n = 0;
+  for (int g = 0; g < P.count; ++g) n += tiles_of(P.d[g], edge);
+  return n;
+}
+int64_t gemm_tiles128(const GemmDesc& d) { return tiles_of(d, 128); }
+
+static void set_tile(GemmParams& P, int edge) {
+  P.tile = edge;
+  for (int g = 0; g < P.count; ++g) {
+    P.tiles_n[g] = (P.d[g].N + edge - 1) / edge;
+    P.tiles[g] = (int)tiles_of(P.d[g], edge);
+  }
+}
+
+// Tile edge of a launch of n32, n64 work items at edges 32 and 64.  A small
+// tile spreads a small launch over more CUs and shortens its longest wave, but
+// reads its operands from LDS more often; the lines lie where the small tile's
+// launch grows past what is resident.  Measured per launch (us, K = N):
+//   BF16, K 1024: 512 work items of edge 32 against 128 of edge 64: 7.2 / 8.5;
+//     1024 / 256: 12.4 / 8.7.  512 of edge 64 against 128 of edge 128: 10.2 /
+//     12.0; 1024 / 256: 18.4 / 13.4.
+//   FP32, K 1024: 512 of edge 32 against 128 of edge 64: 15.9 / 25.6; 1024 /
+//     256: 29.5 / 26.8.  1024 of edge 64 against 256 of edge 128: 70.0 / 73.3;
+//     2048 / 512: 139 / 126 (the MFMAs bind, not the launch).
+static int tile_edge(int64_t n32, int64_t n64, bool bf16) {
+  if (n32 <= 512) return 32;
+  return n64 <= (bf16 ? 512 : 1024) ? 64 : 128;
+}
+
+template <typename T, int LA, int LB, typename OutT, int EDGE, bool ALT>
+static void run_tile(const GemmParams& P, hipStream_t s) {
+  typedef typename lds::TileOf<T, EDGE>::type C;
+  const dim3 grid(max_tiles(P), P.splits, P.count);
+  gemm_lds_kernel<T, LA, LB, OutT, C, ALT><<<grid, C::NT, 0, s>>>(P);
+}
+
 template <typename T, int LA, int LB, typename OutT>
 static hipError_t run(GemmParams& P, hipStream_t s) {
-  const int maxt = max_tiles(P);
-  if (maxt == 0) return hipSuccess;
-  dim3 grid(maxt, P.splits, P.count), block(kGemmThreads);
-  int bn = 0;
-  if constexpr (sizeof(T) == 2) bn = lds_path_bn(P);
-  if (bn == 0)  // the register-staged kernel handles any K: drop zero-padded K
-    for (int g = 0; g < P.count; ++g)
-      if (P.d[g].kb > 0) {
-        P.d[g].K = P.d[g].kb;
-        P.d[g].kb = 0;
-      }
+  if (max_tiles(P) == 0) return hipSuccess;
+  if (!operands_ok(P, sizeof(T) == 2)) return hipErrorInvalidValue;
   double flops = 0.0, bytes = 0.0;
   algo_counts(P, sizeof(T), sizeof(OutT), flops, bytes);
-  if (bn == 128) {
-    KTimer t = timing_begin(lds_kernel_name<LA, LB, OutT, 128>(), flops, bytes, s);
-    gemm_lds_kernel<LA, LB, OutT, 128><<<grid, lds::threads<128>(), 0, s>>>(P);
-    timing_end(t);
-  } else if (bn == 64) {
-    KTimer t = timing_begin(lds_kernel_name<LA, LB, OutT, 64>(), flops, bytes, s);
-    gemm_lds_kernel<LA, LB, OutT, 64><<<grid, lds::threads<64>(), 0, s>>>(P);
-    timing_end(t);
-  } else {
-    KTimer t = timing_begin(kernel_name<T, LA, LB, OutT>(), flops, bytes, s);
-    gemm_kernel<T, LA, LB, OutT><<<grid, block, 0, s>>>(P);
-    timing_end(t);
+  // BF16 launches with a K that is no whole number of stages: the other k
+  // order (see fragment), edge 64
+  bool alt = false;
+  if (sizeof(T) == 2)
+    for (int g = 0; g < P.count; ++g) alt = alt || P.d[g].K % lds::bk<T>() != 0;
+  if (alt) set_tile(P, 64);
+  KTimer t = timing_begin(lds_kernel_name<T, LA, LB, OutT>(), flops, bytes, s);
+  if constexpr (sizeof(T) == 2) {
+    if (alt) run_tile<T, LA, LB, OutT, 64, true>(P, s);
   }
+  if (!alt) {
+    if (P.tile == 128) run_tile<T, LA, LB, OutT, 128, false>(P, s);
+    else if (P.tile == 64) run_tile<T, LA, LB, OutT, 64, false>(P, s);
+    else run_tile<T, LA, LB, OutT, 32, false>(P, s);
+  }
+  timing_end(t);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || P.splits <= 1 || P.defer_reduce) return e;
   int64_t mn = 0;
@@ -144,22 +157,40 @@ static hipError_t run(GemmParams& P, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The layouts in use: KC x MC (forward products, G . psi), KC x KC (input
+// gradients, logits), MC x MC (weight gradients, G^T . phi).
 template <typename T, typename OutT>
 static hipError_t run_layout(GemmParams& P, int la, int lb, hipStream_t s) {
   if (la == LAY_KC && lb == LAY_KC) return run<T, LAY_KC, LAY_KC, OutT>(P, s);
   if (la == LAY_KC && lb == LAY_MC) return run<T, LAY_KC, LAY_MC, OutT>(P, s);
-  if (la == LAY_MC && lb == LAY_KC) return run<T, LAY_MC, LAY_KC, OutT>(P, s);
-  return run<T, LAY_MC, LAY_MC, OutT>(P, s);
+  if constexpr (sizeof(OutT) == 4)
+    if (la == LAY_MC && lb == LAY_MC) return run<T, LAY_MC, LAY_MC, float>(P, s);
+  return hipErrorInvalidValue;
 }
 
 bool gemm_pair_ok(const GemmParams& Pw, const GemmParams& Px, bool bf16) {
-  return bf16 && lds_path_bn(Pw) != 0 && lds_path_bn(Px) == 128 &&
-         (Pw.splits == 1 || Pw.defer_reduce) && Px.splits == 1 && max_tiles(Pw) > 0 &&
+  // a BF16 input gradient keeps its own k order where K is ragged
+  for (int g = 0; g < Px.count; ++g)
+    if (bf16 && Px.d[g].K % lds::bk<bf16_t>()) return false;
+  return (Pw.splits == 1 || Pw.defer_reduce) && Px.splits == 1 && max_tiles(Pw) > 0 &&
          max_tiles(Px) > 0;
 }
 
-hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, hipStream_t s) {
-  if (!gemm_pair_ok(Pw, Px, true)) return hipErrorInvalidValue;
+template <typename T, int EDGE>
+static void run_pair(const GemmParams& Pw, const GemmParams& Px, const PairGrid& G,
+                     hipStream_t s) {
+  typedef typename lds::TileOf<T, EDGE>::type C;
+  gemm_lds_pair_kernel<T, LAY_MC, LAY_MC, float, LAY_KC, LAY_KC, T, C>
+      <<<G.n1 + G.n2, C::NT, 0, s>>>(Pw, Px, G);
+}
+
+hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s) {
+  if (!gemm_pair_ok(Pw, Px, bf16) || !operands_ok(Pw, bf16) || !operands_ok(Px, bf16))
+    return hipErrorInvalidValue;
+  const int edge = tile_edge(tiles_of(Pw, 32) * Pw.splits + tiles_of(Px, 32),
+                             tiles_of(Pw, 64) * Pw.splits + tiles_of(Px, 64), bf16);
+  set_tile(Pw, edge);
+  set_tile(Px, edge);
   PairGrid G;
   G.gx1 = max_tiles(Pw);
   G.gy1 = Pw.splits;
@@ -168,23 +199,37 @@ hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, hipStream_t s) {
   G.gy2 = 1;
   G.n2 = G.gx2 * Px.count;
   double flops = 0.0, bytes = 0.0;
-  algo_counts(Pw, 2.0, 4.0, flops, bytes);
-  algo_counts(Px, 2.0, 2.0, flops, bytes);
-  KTimer t = timing_begin("gemm_lds_pair_kernel<dW,dX>", flops, bytes, s);
-  gemm_lds_pair_kernel<LAY_MC, LAY_MC, float, LAY_KC, LAY_KC, bf16_t>
-      <<<G.n1 + G.n2, lds::threads<128>(), 0, s>>>(Pw, Px, G);
+  const double es = bf16 ? 2.0 : 4.0;
+  algo_counts(Pw, es, 4.0, flops, bytes);
+  algo_counts(Px, es, es, flops, bytes);
+  KTimer t = timing_begin(bf16 ? "gemm_lds_pair_kernel<dW,dX>" : "gemm_lds_pair_kernel<f32,dW,dX>",
+                          flops, bytes, s);
+  if (bf16) {
+    if (edge == 128) run_pair<bf16_t, 128>(Pw, Px, G, s);
+    else if (edge == 64) run_pair<bf16_t, 64>(Pw, Px, G, s);
+    else run_pair<bf16_t, 32>(Pw, Px, G, s);
+  } else {
+    if (edge == 128) run_pair<float, 128>(Pw, Px, G, s);
+    else if (edge == 64) run_pair<float, 64>(Pw, Px, G, s);
+    else run_pair<float, 32>(Pw, Px, G, s);
+  }
   timing_end(t);
   return hipGetLastError();
 }
 
 void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps) {
-  const int BK = bf16 ? GemmCfg<bf16_t>::BK : GemmCfg<float>::BK;
-  int tiles = 0, kmax = 0;
-  for (int g = 0; g < P.count; ++g) {
-    P.tiles_n[g] = (P.d[g].N + kBN - 1) / kBN;
-    P.tiles[g] = ((P.d[g].M + kBM - 1) / kBM) * P.tiles_n[g];
-    tiles += P.tiles[g];
-    kmax = P.d[g].K > kmax ? P.d[g].K : kmax;
+  const int BK = bf16 ? lds::bk<bf16_t>() : lds::bk<float>();
+  int kmax = 0;
+  for (int g = 0; g < P.count; ++g) kmax = P.d[g].K > kmax ? P.d[g].K : kmax;
+  // BF16 splits are counted in tiles of edge 128 whatever tile runs (the
+  // split decides how a sum that is later rounded to BF16 is formed).  An FP32
+  // step of K is half as deep and four times as slow in MFMAs, so its tiles
+  // are chosen first; a reduction launch of its own (4.7 us) pays from 32
+  // steps per split on (an edge-32 work item takes 0.33 us a step).
+  int64_t tiles = tiles_of(P, 128);
+  if (!bf16) {
+    tiles = tiles_of(P, tile_edge(tiles_of(P, 32), tiles_of(P, 64), false));
+    if (min_steps < 8) min_steps = 32;
   }
   int splits = 1;
   if (tiles > 0 && P.partial != nullptr) {
@@ -196,6 +241,7 @@ void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps) {
   if (kc == 0) kc = BK;
   P.splits = splits;
   P.k_chunk = kc;
+  set_tile(P, tile_edge(tiles_of(P, 32) * splits, tiles_of(P, 64) * splits, bf16));
 }
 
 hipError_t launch_gemm(GemmParams& P, bool bf16, int la, int lb, bool out_bf16, hipStream_t s) {
@@ -203,7 +249,7 @@ hipError_t launch_gemm(GemmParams& P, bool bf16, int la, int lb, bool out_bf16, 
     if (out_bf16) return run_layout<bf16_t, bf16_t>(P, la, lb, s);
     return run_layout<bf16_t, float>(P, la, lb, s);
   }
-  if (out_bf16) return run_layout<float, bf16_t>(P, la, lb, s);
+  if (out_bf16) return hipErrorInvalidValue;
   return run_layout<float, float>(P, la, lb, s);
 }
 

@@ -1,243 +1,434 @@
-// BF16 GEMM whose operand tiles go from global memory straight into LDS
-// (global_load_lds_dwordx4: no staging registers, so only an explicit wait
-// orders a tile's arrival before its use), double-buffered.  Tiles that are
-// contiguous along K (KC) are read with ds_read_b128 through an XOR swizzle of
-// their 16-byte chunks; tiles contiguous along M or N (MC) are read with the
-// 16-bit transpose read ds_read_b64_tr_b16, which turns four rows of 4 x 16-bit
-// chunks into the per-lane K runs the MFMA wants.  Tiles are 128 x BN with BN
-// 128 or 64, computed by BN/16 waves of 64 x 32 each (eight or four waves: more
-// resident waves hide more of the load and barrier latency than larger
-// per-wave blocks save in LDS reads).  M and N may be ragged (loads past the edge are clamped into the
-// operand and the results they feed are not stored; an N that is not a multiple of 8 is stored
-// element by element); every K range must be a
-// whole number of 64-deep steps, otherwise gemm_kernel takes the launch.
+// MFMA GEMM whose operand tiles go from global memory straight into LDS
+// (global_load_lds_dwordx4: no staging registers), for BF16 and FP32 storage.
+//
+// A stage is 128 bytes of K of every tile row (64 BF16 or 32 FP32 values);
+// ST stages ring through LDS, so ST - 1 stages (and, software-pipelined, half
+// a stage of fragments in registers) are in flight while one is multiplied.
+// Tiles that are contiguous along K (KC) are read with ds_read_b128 through an
+// XOR swizzle of their 16-byte chunks; tiles contiguous along M or N (MC) are
+// read with the 16-bit transpose read ds_read_b64_tr_b16 (BF16), which turns
+// four rows of 4 x 16-bit chunks into the per-lane K runs the MFMA wants, or
+// as single floats (FP32).
+//   BF16: v_mfma_f32_16x16x32_bf16, FP32 accumulation.
+//   FP32: v_mfma_f32_16x16x4_f32.
+// Every result is the same chain of MFMAs in K order whatever the tile, so all
+// tiles give the same bits.
+//
+// The loads are issued through inline assembly.  Through the builtin the
+// compiler knows that they write LDS and, since it cannot tell the stages
+// apart, waits for all of them (s_waitcnt vmcnt(0)) before the next transpose
+// read: the prefetch then overlapped nothing.  With the explicit counted waits
+// below one 2 x (4096 x 1024 x 1024) BF16 forward launch went from 25.0 to
+// 21.7 us, one 2 x (1024 x 1024 x 4096, two splits) dW launch from 36.7 to
+// 24.7 us (794 and 695 TFLOP/s; a 64-deep step of a resident pair of
+// workgroups takes 0.93 us, 86% of the 1.25-1.35 PFLOP/s that large library
+// products reach on this card; 7 us of a launch are its fixed cost).
 #pragma once
 #include "gemm.hpp"
 
 namespace crl {
 namespace lds {
 
-constexpr int BM = 128, BK = 64;
-// waves and threads of a 128 x BN tile: a 2 x (BN/32) grid of 64 x 32 blocks
-template <int BN> constexpr int waves() { return BN / 16; }
-template <int BN> constexpr int threads() { return 64 * waves<BN>(); }
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
+typedef __attribute__((address_space(3))) char lds_char;
 
-// bytes of a ROWS x 64 BF16 operand tile
-template <int ROWS> constexpr int tile_bytes() { return ROWS * BK * 2; }
+template <typename T> constexpr int bk() { return 128 / (int)sizeof(T); }   // K per stage
+template <typename T> constexpr int vec() { return 16 / (int)sizeof(T); }   // values per chunk
 
-// KC tile: row r holds 64 k values (8 chunks of 16 B); logical chunk c sits
+// BM x BN tile, WM x WN waves, ST stages, OCC waves per SIMD to compile for
+template <int BM_, int BN_, int WM_, int WN_, int ST_, int OCC_> struct Tile {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_, OCC = OCC_;
+  static constexpr int NW = WM * WN, NT = 64 * NW;
+  static constexpr int MI = BM / WM / 16, NJ = BN / WN / 16;  // 16 x 16 blocks per wave
+  static constexpr int STAGE = (BM + BN) * 128;
+  static constexpr int EPI = 4 * BM * (BN + 4);  // FP32 epilogue tile, shares the stages' space
+  static constexpr int SMEM = ST * STAGE > EPI ? ST * STAGE : EPI;
+};
+// The three tile edges of each storage type.  Two 128-tile workgroups fit a CU
+// (64 KB of stages each); a third stage would leave one, which measured slower
+// (26.5 against 20.7 us for the 2 x 4096 x 1024 x 1024 input gradient), as did
+// 256 x 128 tiles with eight waves (22.1 us) and sixteen (20.5; no gain).
+template <typename T, int EDGE> struct TileOf;
+template <> struct TileOf<bf16_t, 128> { typedef Tile<128, 128, 2, 4, 2, 4> type; };
+template <> struct TileOf<bf16_t, 64> { typedef Tile<64, 64, 2, 2, 3, 2> type; };
+template <> struct TileOf<bf16_t, 32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
+template <> struct TileOf<float, 128> { typedef Tile<128, 128, 2, 2, 2, 2> type; };
+template <> struct TileOf<float, 64> { typedef Tile<64, 64, 2, 2, 3, 2> type; };
+template <> struct TileOf<float, 32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
+
+// KC tile: row r holds 128 bytes of K (8 chunks of 16 B); logical chunk c sits
 // in slot c ^ kc_swz(r).  A ds_read_b128 pass of 16 rows then touches 16
 // distinct (bank window, slot) pairs.
 __device__ __forceinline__ int kc_swz(int r) { return (r >> 1) & 7; }
 
-// MC tile of W columns: k-row kr holds W values (W/8 chunks); chunk c sits in
-// slot c ^ mc_swz<W>(kr).  A half-wave of transpose reads covers 8 k-rows x 2
-// adjacent chunks; the swizzle gives those 16 chunks distinct banks.
-template <int W> __device__ __forceinline__ int mc_swz(int kr);
-template <> __device__ __forceinline__ int mc_swz<128>(int kr) {
-  return 2 * ((kr & 3) + 4 * ((kr >> 3) & 1));
-}
-template <> __device__ __forceinline__ int mc_swz<64>(int kr) {
-  return 2 * (((kr >> 1) & 1) + 2 * ((kr >> 3) & 1));
+// MC tile of W columns: k-row kr holds W values; chunk c sits in slot
+// c ^ mc_swz(kr).  BF16: a half-wave of transpose reads covers 8 k-rows x 2
+// adjacent chunks, FP32: a wave reads 16 columns (4 chunks) of 4 k-rows that
+// are 8 apart; the swizzle gives those 16 chunks distinct banks (FP32, W = 32:
+// two rows meet, a row being half the banks).
+template <typename T, int W> __device__ __forceinline__ int mc_swz(int kr) {
+  if (sizeof(T) == 4) return W >= 64 ? 4 * ((kr >> 3) & 3) : 4 * ((kr >> 3) & 1);
+  if (W >= 128) return 2 * ((kr & 3) + 4 * ((kr >> 3) & 1));
+  if (W == 64) return 2 * (((kr >> 1) & 1) + 2 * ((kr >> 3) & 1));
+  return 2 * ((kr >> 3) & 1);
 }
 
-// One wave instruction fills one 1 KB block of the tile; the NW waves take
-// blocks wave, wave+NW, ...  W = extent of the tile along M or N; R = extent of
-// the operand along it; KR = k-rows of an MC operand that exist.  A KC row
-// past R re-reads row R-1, an MC chunk past the row stride re-reads the last
-// chunk (in bounds, and only ever feeding outputs that are not stored); an MC
-// k-row past KR re-reads row KR-1, which meets zero columns of the other
-// operand.
-template <int LAY, int W, int NW>
-__device__ __forceinline__ void issue_tile(const bf16_t* __restrict__ X, int ld, int r0, int R,
-                                           int KR, int k0, char* tile, int wave, int lane) {
-  constexpr int NBLK = tile_bytes<W>() / 1024;
-  static_assert(NBLK % NW == 0, "whole blocks per wave");
-#pragma unroll
-  for (int i = 0; i < NBLK / NW; ++i) {
+// 64 lanes x 16 bytes: lane l's 16 bytes at base + off go to LDS address
+// lds + 16 l.  No register is written and the compiler does not count the
+// load: wait_vm below does.
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               ::"s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+// all but this wave's N latest vector-memory operations done, and its LDS reads
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
+}
+
+// One operand's stages.  One wave instruction fills one 1 KB block of the
+// tile; the NW waves take blocks wave, wave + NW, ...  W = extent of the tile
+// along M or N; R = extent of the operand along it; kv = K values (KC) or
+// k-rows (MC) of the operand that exist.  A KC row past R re-reads row R-1, an
+// MC chunk past the row stride the last chunk, a KC chunk or MC k-row past kv
+// the last one: all in bounds.  Rows and columns past the edge only feed
+// outputs that are not stored; K past the end is zeroed in LDS (zero_tail) or
+// meets zeros of the other operand (GemmDesc::kb).
+template <typename T, int LAY, int W, int NW> struct Operand {
+  static constexpr int NB = W / 8 / NW;
+  static constexpr int LPR = W * (int)sizeof(T) / 16;  // lanes (chunks) per MC k-row
+  static_assert(NB >= 1 && W % (8 * NW) == 0, "whole blocks per wave");
+  const char* base;   // the next stage's first byte
+  int64_t step;       // bytes from one stage to the next
+  uint32_t off[NB];   // this lane's offsets inside a whole stage
+  int ld, r0, R, kv;
+
+  // offset of this lane's chunk of block i in a stage with `lim` K values left
+  __device__ __forceinline__ uint32_t offset(int i, int lim, int wave, int lane) const {
+    constexpr int es = (int)sizeof(T);
     const int blk = wave + NW * i;
-    const bf16_t* src;
     if (LAY == LAY_KC) {  // 8 rows of 128 B per block
       const int r = blk * 8 + (lane >> 3);
-      const int c = (lane & 7) ^ kc_swz(r);
-      src = X + (int64_t)min(r0 + r, R - 1) * ld + k0 + 8 * c;
-    } else {              // 1024 / (2W) k-rows per block
-      constexpr int LPR = W / 8;  // lanes (chunks) per k-row
-      const int kr = blk * (64 / LPR) + lane / LPR;
-      const int c = (lane % LPR) ^ mc_swz<W>(kr);
-      src = X + (int64_t)min(k0 + kr, KR - 1) * ld + min(r0 + 8 * c, ld - 8);
+      const int c = min((lane & 7) ^ kc_swz(r), (lim - 1) / vec<T>());
+      return (uint32_t)((min(r0 + r, R - 1) - r0) * ld * es + 16 * c);
     }
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)(tile + blk * 1024),
-                                     16, 0, 0);
+    const int kr = blk * (64 / LPR) + lane / LPR;
+    const int c = (lane % LPR) ^ mc_swz<T, W>(kr);
+    return (uint32_t)(min(kr, lim - 1) * ld * es + min(r0 + vec<T>() * c, ld - vec<T>()) * es);
+  }
+  __device__ __forceinline__ void init(const void* X, int ld_, int r0_, int R_, int kv_, int kbeg,
+                                       int wave, int lane) {
+    ld = ld_; r0 = r0_; R = R_; kv = kv_;
+    const char* x = reinterpret_cast<const char*>(X);
+    if (LAY == LAY_KC) {
+      base = x + ((int64_t)r0 * ld + kbeg) * (int)sizeof(T);
+      step = 128;
+    } else {
+      base = x + (int64_t)kbeg * ld * (int)sizeof(T);
+      step = (int64_t)bk<T>() * ld * (int)sizeof(T);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) off[i] = offset(i, bk<T>(), wave, lane);
+  }
+  // the stage that starts at k0 (stages come in order), into LDS address dst
+  __device__ __forceinline__ void issue(int k0, uint32_t dst, int wave, int lane) {
+    if (k0 + bk<T>() <= kv) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) load_to_lds(base, off[i], dst + (wave + NW * i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        load_to_lds(base, offset(i, kv - k0, wave, lane), dst + (wave + NW * i) * 1024);
+    }
+    base += step;
+  }
+};
+
+// Zeroes K values valid..bk-1 of a stage's tile (1 <= valid < bk).
+template <typename T, int LAY, int W, int NT>
+__device__ __forceinline__ void zero_tail(char* tile, int valid, int tid) {
+  if (LAY == LAY_KC) {
+    const int n = bk<T>() - valid;
+    for (int idx = tid; idx < W * n; idx += NT) {
+      const int row = idx / n, k = valid + idx % n;
+      reinterpret_cast<T*>(tile + row * 128 + (((k / vec<T>()) ^ kc_swz(row)) << 4))[k % vec<T>()] =
+          T(0);
+    }
+  } else {
+    for (int o = valid * W * (int)sizeof(T) + tid * 16; o < W * 128; o += NT * 16)
+      *reinterpret_cast<u32x4*>(tile + o) = u32x4{0, 0, 0, 0};
   }
 }
 
-// KC fragment: 8 consecutive k (32-k half hh, lane group g) of row `row`
-__device__ __forceinline__ bf16x8 frag_kc(const char* tile, int row, int hh, int g) {
-  const int c = 4 * hh + g;
-  return *reinterpret_cast<const bf16x8*>(tile + row * 128 + ((c ^ kc_swz(row)) << 4));
-}
-// MC fragment: lane (g, j) gets k = 32hh + 8g + 0..7 of column mb + j.  In a
-// 16-lane group, lane j addresses k-row 4t + j/4 at columns 4(j%4)..+3; the
-// transpose read hands lane j the column-j values of those four rows.
-template <int W>
-__device__ __forceinline__ bf16x8 frag_mc(const char* tile, int mb, int hh, int g, int j) {
+// Half a stage's fragments of one 16-row (or 16-column) block at mb; lane
+// (g, j) = (lane / 16, lane % 16).  BF16: 8 consecutive k of row j, starting
+// at 8 c with c = 4 hh + g, or (ALT) 2 g + hh.  ALT is the order of launches
+// whose K is not a whole number of stages; it is kept because BF16 outputs of
+// such launches round differently in another order.
+template <int LAY, int W, bool ALT>
+__device__ __forceinline__ bf16x8 fragment(const char* tile, int mb, int hh, int g, int j,
+                                           bf16_t*) {
+  const int c = ALT ? 2 * g + hh : 4 * hh + g;
+  if (LAY == LAY_KC) {
+    const int row = mb + j;
+    return *reinterpret_cast<const bf16x8*>(tile + row * 128 + ((c ^ kc_swz(row)) << 4));
+  }
+  // In a 16-lane group, lane j addresses k-row 8 c + 4 t + j/4 at columns
+  // 4 (j%4)..+3; the transpose read hands lane j the column-j values of those
+  // four rows.
   v4s h[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const int kr = 32 * hh + 8 * g + 4 * t + (j >> 2);
+    const int kr = 8 * c + 4 * t + (j >> 2);
     const int m = mb + 4 * (j & 3);
-    const int off = kr * (2 * W) + (((m >> 3) ^ mc_swz<W>(kr)) << 4) + (m & 7) * 2;
+    const int off = kr * (2 * W) + (((m >> 3) ^ mc_swz<bf16_t, W>(kr)) << 4) + (m & 7) * 2;
     h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(tile + off));
   }
   v8s r = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
   return __builtin_bit_cast(bf16x8, r);
 }
+// FP32: k = 8 g + 4 hh + 0..3 of row j, one MFMA each.
+template <int LAY, int W, bool ALT>
+__device__ __forceinline__ floatx4 fragment(const char* tile, int mb, int hh, int g, int j,
+                                            float*) {
+  if (LAY == LAY_KC) {
+    const int row = mb + j;
+    return *reinterpret_cast<const floatx4*>(tile + row * 128 +
+                                             (((2 * g + hh) ^ kc_swz(row)) << 4));
+  }
+  floatx4 r;
+  const int m = mb + j;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int kr = 8 * g + 4 * hh + i;
+    r[i] = *reinterpret_cast<const float*>(tile + kr * (4 * W) +
+                                           (((m >> 2) ^ mc_swz<float, W>(kr)) << 4) + (m & 3) * 4);
+  }
+  return r;
+}
+template <typename T> struct Frag { typedef bf16x8 type; };
+template <> struct Frag<float> { typedef floatx4 type; };
 
-// one 64-deep stage: wave (wm, wn) owns rows wm*64 + 0..63, columns
-// wn*32 + 0..31 of the tile
-template <int LA, int LB, int BN>
-__device__ __forceinline__ void compute_tile(floatx4 (&acc)[4][2], const char* At,
-                                             const char* Bt, int wm, int wn, int lane) {
-  constexpr int NJ = 2;
+template <typename T, int LA, int LB, typename C, bool ALT>
+__device__ __forceinline__ void load_half(typename Frag<T>::type (&a)[C::MI],
+                                          typename Frag<T>::type (&b)[C::NJ], const char* st,
+                                          int hh, int wm, int wn, int lane) {
   const int g = lane >> 4, j = lane & 15;
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
-    bf16x8 a[4], b[NJ];
+  for (int i = 0; i < C::NJ; ++i)
+    b[i] = fragment<LB, C::BN, ALT>(st + C::BM * 128, (wn * C::NJ + i) * 16, hh, g, j, (T*)nullptr);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      a[i] = LA == LAY_KC ? frag_kc(At, wm * 64 + i * 16 + j, hh, g)
-                          : frag_mc<BM>(At, wm * 64 + i * 16, hh, g, j);
-#pragma unroll
-    for (int i = 0; i < NJ; ++i)
-      b[i] = LB == LAY_KC ? frag_kc(Bt, wn * 32 + i * 16 + j, hh, g)
-                          : frag_mc<BN>(Bt, wn * 32 + i * 16, hh, g, j);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int jj = 0; jj < NJ; ++jj)
-        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[jj], acc[i][jj], 0, 0, 0);
-  }
+  for (int i = 0; i < C::MI; ++i)
+    a[i] = fragment<LA, C::BM, ALT>(st, (wm * C::MI + i) * 16, hh, g, j, (T*)nullptr);
 }
-
-// s_waitcnt on the vector-memory counter only
-template <int N> __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 16, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(N | 0x70 | 0xF00);
+template <typename C>
+__device__ __forceinline__ void mma_half(floatx4 (&acc)[C::MI][C::NJ], const bf16x8 (&a)[C::MI],
+                                         const bf16x8 (&b)[C::NJ]) {
+#pragma unroll
+  for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < C::NJ; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
 }
-
-// LDS bytes of a 128 x BN tile: two stages, or the FP32 epilogue tile
-template <int BN> constexpr int smem_bytes() {
-  constexpr int stage2 = 2 * (tile_bytes<BM>() + tile_bytes<BN>());
-  constexpr int epi = (int)sizeof(float) * BM * (BN + 4);
-  return stage2 > epi ? stage2 : epi;
+template <typename C>
+__device__ __forceinline__ void mma_half(floatx4 (&acc)[C::MI][C::NJ], const floatx4 (&a)[C::MI],
+                                         const floatx4 (&b)[C::NJ]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < C::NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
 }
 }  // namespace lds
 
-// One workgroup's work item wi of launch P; smem holds smem_bytes<BN>().
-template <int LA, int LB, typename OutT, int BN>
+// One workgroup's work item wi of launch P; smem holds C::SMEM bytes.
+template <typename T, int LA, int LB, typename OutT, typename C, bool ALT>
 __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkItem wi, char* smem) {
   using namespace lds;
-  constexpr int NW = waves<BN>(), NT = threads<BN>();
-  constexpr int TA = tile_bytes<BM>(), TB = tile_bytes<BN>();
-  constexpr int STAGE = TA + TB;
-  constexpr int kLdc = BN + 4;
-  constexpr int NJ = 2;
+  constexpr int BK = bk<T>(), MI = C::MI, NJ = C::NJ;
   const int gi = wi.prob;
   const GemmDesc& D = P.d[gi];
-  const int ntile = P.tiles[gi];
   const int pid = wi.tile;
-  if (pid >= ntile) return;
+  if (pid >= P.tiles[gi]) return;
   const int tm = pid / P.tiles_n[gi], tn = pid % P.tiles_n[gi];
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int kbeg = wi.split * P.k_chunk;
-  const int nk = (min(D.K, kbeg + P.k_chunk) - kbeg) / BK;  // <= 0: empty split
-  const bf16_t* A = reinterpret_cast<const bf16_t*>(D.A);
-  const bf16_t* B = reinterpret_cast<const bf16_t*>(D.B);
-  const int kb = D.kb > 0 ? D.kb : D.K;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
-  floatx4 acc[4][NJ];
+  const int m0 = tm * C::BM, n0 = tn * C::BN;
+  const int K = D.K, kbeg = wi.split * P.k_chunk;
+  const int nk = (min(K, kbeg + P.k_chunk) - kbeg + BK - 1) / BK;  // <= 0: empty split
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+  floatx4 acc[MI][NJ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  auto issue = [&](int t) {
-    char* st = smem + (t & 1) * STAGE;
-    issue_tile<LA, BM, NW>(A, D.lda, m0, D.M, D.K, kbeg + t * BK, st, wave, lane);
-    issue_tile<LB, BN, NW>(B, D.ldb, n0, D.N, kb, kbeg + t * BK, st + TA, wave, lane);
-  };
-  if (nk > 0) issue(0);
-  for (int kt = 0; kt < nk; ++kt) {
-    // this thread's loads of tile kt are the only ones in flight; the barrier
-    // then makes every thread's part of it visible and guarantees that the
-    // other buffer (tile kt-1) is no longer being read
-    wait_vm<0>();
-    __syncthreads();
-    if (kt + 1 < nk) issue(kt + 1);
-    const char* st = smem + (kt & 1) * STAGE;
-    compute_tile<LA, LB, BN>(acc, st, st + TA, wm, wn, lane);
+  if (nk > 0) {
+    typedef Operand<T, LA, C::BM, C::NW> OpA;
+    typedef Operand<T, LB, C::BN, C::NW> OpB;
+    constexpr int LPS = OpA::NB + OpB::NB;  // loads of one wave per stage
+    OpA oa;
+    OpB ob;
+    oa.init(D.A, D.lda, m0, D.M, K, kbeg, wave, lane);
+    ob.init(D.B, D.ldb, n0, D.N, D.kb > 0 ? D.kb : K, kbeg, wave, lane);
+    int head = 0, tail = 0;  // ring slots: the next to fill, the one in use
+    auto issue = [&](int t) {
+      const uint32_t st = lds0 + head * C::STAGE;
+      oa.issue(kbeg + t * BK, st, wave, lane);
+      ob.issue(kbeg + t * BK, st + C::BM * 128, wave, lane);
+      head = head + 1 == C::ST ? 0 : head + 1;
+    };
+    // Stage kt complete for the whole workgroup, with `later` <= ST - 1 of
+    // the following stages issued already: this wave's part has arrived once
+    // at most their loads are outstanding, the barrier covers the others'.
+    // It also means that every wave has its fragments of stage kt - 1 in
+    // registers (its LDS reads are done), so that stage's slot is free.
+    auto arrive = [&](int kt, int later) {
+      if (later >= 3 && C::ST >= 4) wait_vm<(C::ST >= 4 ? 3 : 0) * LPS>();
+      else if (later >= 2 && C::ST >= 3) wait_vm<(C::ST >= 3 ? 2 : 0) * LPS>();
+      else if (later >= 1) wait_vm<LPS>();
+      else wait_vm<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    // the last stage's K values past the end
+    auto finish = [&](int kt, char* st) {
+      const int valid = K - (kbeg + kt * BK);
+      if (valid < BK) {
+        zero_tail<T, LA, C::BM, C::NT>(st, valid, tid);
+        zero_tail<T, LB, C::BN, C::NT>(st + C::BM * 128, valid, tid);
+        __syncthreads();
+      }
+    };
+    // FP32: the running sums are added into `sum` every 128 of K, so that a
+    // long K rounds like the short chains of a split one
+    floatx4 sum[MI][NJ];
+    auto flush = [&]() {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) sum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    typename Frag<T>::type a0[MI], b0[NJ], a1[MI], b1[NJ];
+#pragma unroll
+    for (int s = 0; s < C::ST; ++s)
+      if (s < nk) issue(s);
+    arrive(0, min(nk, (int)C::ST) - 1);
+    finish(0, smem);
+    load_half<T, LA, LB, C, ALT>(a0, b0, smem, 0, wm, wn, lane);
+    for (int kt = 0; kt < nk; ++kt) {
+      // one half's fragments are read while the other half multiplies
+      load_half<T, LA, LB, C, ALT>(a1, b1, smem + tail * C::STAGE, 1, wm, wn, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_half<C>(acc, a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + 1 < nk) {
+        tail = tail + 1 == C::ST ? 0 : tail + 1;
+        // issued by now: stages up to kt + ST - 1
+        arrive(kt + 1, min(nk - 2 - kt, C::ST - 2));
+        if (kt + C::ST < nk) issue(kt + C::ST);
+        char* st = smem + tail * C::STAGE;
+        finish(kt + 1, st);
+        load_half<T, LA, LB, C, ALT>(a0, b0, st, 0, wm, wn, lane);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma_half<C>(acc, a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (sizeof(T) == 4)
+        if ((kt & 3) == 3) flush();
+    }
+    if constexpr (sizeof(T) == 4) {
+      flush();
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = sum[i][j];
+    }
   }
   const bool split = P.splits > 1;
   if (split && P.defer_reduce && P.frag) {
-    // deferred split-K partial in fragment order: wave w's accumulators
-    // acc[i][j] go to floats ((tile * NW + w) * 8 + i * 2 + j) * 256 + 4 lane
-    // of this split's block, one 1 KB store per wave and fragment
-    float* out = P.partial + (int64_t)gi * P.partial_len +
-                 (int64_t)wi.split * ntile * BM * BN + ((int64_t)pid * NW + wave) * (4 * NJ * 256);
+    // deferred split-K partial in fragment order of 128 x frag blocks: the
+    // 16 x 16 block (rb, cb) is fragment (rb % 4, cb % 2) of the 64 x 32 wave
+    // block it lies in, 256 floats, one 1 KB store per wave
+    const int bn = P.frag, nwc = bn / 32, cpb = bn / 16;
+    const int tn_l = (D.N + bn - 1) / bn, nblk = (D.M + 127) / 128 * tn_l;
+    float* out = P.partial + (int64_t)gi * P.partial_len + (int64_t)wi.split * nblk * 128 * bn;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        *reinterpret_cast<floatx4*>(out + (i * NJ + j) * 256 + lane * 4) = acc[i][j];
+      for (int j = 0; j < NJ; ++j) {
+        const int rb = m0 / 16 + wm * MI + i, cb = n0 / 16 + wn * NJ + j;
+        const int blk = (rb >> 3) * tn_l + cb / cpb;
+        const int w = ((rb & 7) >> 2) * nwc + (cb % cpb >> 1);
+        if (rb * 16 < D.M && cb * 16 < D.N)
+          *reinterpret_cast<floatx4*>(
+              out + (((int64_t)blk * 2 * nwc + w) * 8 + (rb & 3) * 2 + (cb & 1)) * 256 + lane * 4) =
+              acc[i][j];
+      }
     return;
   }
   __syncthreads();
 
-  // epilogue: stage the FP32 tile in LDS, then 16-byte row stores
+  // Epilogue: row/column-only operations in registers, then the FP32 tile is
+  // staged in LDS so that global memory sees 16-byte row stores.
   const int r16 = lane & 15, gq = lane >> 4;
+  constexpr int kLdc = C::BN + 4;
   float* Cs = reinterpret_cast<float*>(smem);
-  const bool has_bias = !split && (D.epi == EPI_BIAS || D.epi == EPI_BIAS_RELU);
-  float bcol[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)  // clamped column: past-the-edge values are not stored
-    bcol[j] = has_bias ? D.bias[min(n0 + wn * 32 + j * 16 + r16, D.N - 1)] : 0.f;
+  const int epi = split ? EPI_NONE : D.epi;
+  const bool has_bias = epi == EPI_BIAS || epi == EPI_BIAS_RELU;
+  const bool dist = epi == EPI_L2 || epi == EPI_L2SQ;
   const float alpha = split ? 1.f : D.alpha;
-  const bool relu = !split && D.epi == EPI_BIAS_RELU;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < NJ; ++j) {
+    const int cl = (wn * NJ + j) * 16 + r16;
+    const int col = min(n0 + cl, D.N - 1);  // past-the-edge values are not stored
+    const float bcol = has_bias ? D.bias[col] : 0.f;
+    const float ccol = dist ? D.colv[col] : 0.f;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int cl = wn * 32 + j * 16 + r16;
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int rl = wm * 64 + i * 16 + gq * 4 + r;
-        float v = acc[i][j][r] * alpha + bcol[j];
-        if (relu) v = fmaxf(v, 0.f);
+        const int rl = (wm * MI + i) * 16 + gq * 4 + r;
+        float v = acc[i][j][r] * alpha + bcol;
+        if (epi == EPI_BIAS_RELU) v = fmaxf(v, 0.f);
+        if (sizeof(T) == 4 && dist) {
+          const float rv = D.rowv[min(m0 + rl, D.M - 1)];
+          v = epi == EPI_L2 ? -l2_dist(rv, ccol, v) : -l2sq_dist(rv, ccol, v);
+        }
         Cs[rl * kLdc + cl] = v;
       }
-    }
+  }
   __syncthreads();
-  // BN/8 threads per row, 8 values each; N is a multiple of 8, so a chunk is
+  // BN/8 threads per row, 8 values each; with N a multiple of 8 a chunk is
   // either wholly inside or wholly past the edge
-  constexpr int TPR = BN / 8, RSTEP = NT / TPR;
+  constexpr int TPR = C::BN / 8, RSTEP = C::NT / TPR;
   const int ch = tid % TPR;
   const int col0 = n0 + ch * 8;
-  const int rows = min(BM, D.M - m0);
+  const int rows = min(C::BM, D.M - m0);
   if (col0 >= D.N) return;
-  // N not a multiple of 8 (a few output columns, no mask epilogue): element stores
   const int nc = min(8, D.N - col0);
-  const bool ragged = (D.N & 7) != 0;
+  const bool ragged = (D.N & 7) != 0;  // unrolled element stores: no private-memory array
   if (split) {
     float* out = P.partial + (int64_t)gi * P.partial_len + (int64_t)wi.split * D.M * D.N;
     for (int rl = tid / TPR; rl < rows; rl += RSTEP) {
       const float* src = Cs + rl * kLdc + ch * 8;
       float* dst = out + (int64_t)(m0 + rl) * D.N + col0;
-      if (ragged) {  // unrolled with constant indices: no private-memory array
+      if (ragged) {
 #pragma unroll
         for (int k = 0; k < 8; ++k)
           if (k < nc) dst[k] = src[k];
@@ -248,7 +439,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     }
     return;
   }
-  OutT* __restrict__ C = reinterpret_cast<OutT*>(D.C);
+  OutT* __restrict__ Cg = reinterpret_cast<OutT*>(D.C);
   const OutT* __restrict__ aux = reinterpret_cast<const OutT*>(D.aux);
   for (int rl = tid / TPR; rl < rows; rl += RSTEP) {
     const float* src = Cs + rl * kLdc + ch * 8;
@@ -256,7 +447,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     float v[8];
     *reinterpret_cast<float4*>(v) = *reinterpret_cast<const float4*>(src);
     *reinterpret_cast<float4*>(v + 4) = *reinterpret_cast<const float4*>(src + 4);
-    if (D.epi == EPI_MASK_POS) {
+    if (epi == EPI_MASK_POS) {  // only with N a multiple of 8 (hidden widths)
       float a8[8];
       load8_any(aux + o, a8);
 #pragma unroll
@@ -265,37 +456,35 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     if (ragged) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if (k < nc) C[o + k] = Store<OutT>::from_f(v[k]);
+        if (k < nc) Cg[o + k] = Store<OutT>::from_f(v[k]);
       continue;
     }
-    store8_any(C + o, v);
+    store8_any(Cg + o, v);
   }
 }
 
-// two workgroups per CU: 2 * waves<BN>() waves over the 4 SIMDs
-template <int LA, int LB, typename OutT, int BN>
-__global__ __launch_bounds__(lds::threads<BN>())
-__attribute__((amdgpu_waves_per_eu(lds::waves<BN>() / 2, lds::waves<BN>() / 2)))
+template <typename T, int LA, int LB, typename OutT, typename C, bool ALT>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
 void gemm_lds_kernel(GemmParams P) {
-  __shared__ __attribute__((aligned(1024))) char smem[lds::smem_bytes<BN>()];
-  gemm_lds_tile<LA, LB, OutT, BN>(P, gemm_work_item(), smem);
+  __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
+  gemm_lds_tile<T, LA, LB, OutT, C, ALT>(P, gemm_work_item(), smem);
 }
 
-// Two independent launches of 128 x 128 tiles in one grid: ids [0, n1) take
-// launch P1 (grid g1 = tiles x splits x problems), the rest launch P2.  One
-// launch instead of two saves a launch's fixed cost (first stage, epilogue,
-// ramp) and lets the second launch's tiles fill the first one's tail.
+// Two independent launches in one grid: ids [0, n1) take launch P1 (grid g1 =
+// tiles x splits x problems), the rest launch P2.  One launch instead of two
+// saves a launch's fixed cost (first stage, epilogue, ramp) and lets the
+// second launch's tiles fill the first one's tail.
 struct PairGrid { int n1, gx1, gy1, gx2, gy2, n2; };
-template <int LA1, int LB1, typename Out1, int LA2, int LB2, typename Out2>
-__global__ __launch_bounds__(lds::threads<128>())
-__attribute__((amdgpu_waves_per_eu(lds::waves<128>() / 2, lds::waves<128>() / 2)))
+template <typename T, int LA1, int LB1, typename Out1, int LA2, int LB2, typename Out2, typename C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
 void gemm_lds_pair_kernel(GemmParams P1, GemmParams P2, PairGrid G) {
-  __shared__ __attribute__((aligned(1024))) char smem[lds::smem_bytes<128>()];
+  __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   const int id = blockIdx.x;
   if (id < G.n1)
-    gemm_lds_tile<LA1, LB1, Out1, 128>(P1, work_item_of(id, G.gx1, G.gy1, G.n1), smem);
+    gemm_lds_tile<T, LA1, LB1, Out1, C, false>(P1, work_item_of(id, G.gx1, G.gy1, G.n1), smem);
   else
-    gemm_lds_tile<LA2, LB2, Out2, 128>(P2, work_item_of(id - G.n1, G.gx2, G.gy2, G.n2), smem);
+    gemm_lds_tile<T, LA2, LB2, Out2, C, false>(P2, work_item_of(id - G.n1, G.gx2, G.gy2, G.n2),
+                                               smem);
 }
 
 }  // namespace crl

@@ -28,22 +28,20 @@ void timing_end(KTimer& t);
 hipError_t launch_gemm(GemmParams& P, bool bf16, int la, int lb, bool out_bf16,
                        hipStream_t s);
 // One layer's weight gradient (Pw: MC x MC, FP32 out or deferred split-K
-// partials) and input gradient (Px: KC x KC, BF16 out, unsplit) in one launch
-// of the direct-to-LDS kernel with 128-wide tiles (also for a dW with N <= 64);
-// gemm_pair_ok tells whether both launches qualify (BF16 storage, both on the
-// direct-to-LDS kernel, dX 128 wide, no split-K reduction left to run).
+// partials) and input gradient (Px: KC x KC, storage-type out, unsplit) in one
+// launch; gemm_pair_ok tells whether the two can share one (no split-K
+// reduction left to run; a BF16 dX whose K is whole stages).
 bool gemm_pair_ok(const GemmParams& Pw, const GemmParams& Px, bool bf16);
-hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, hipStream_t s);
-// Split factor and chunk for a batch of problems (fills P.splits, P.k_chunk):
-// the largest power of two that keeps the launch within target_wgs workgroups
-// and every split at least min_steps K steps deep.
+hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s);
+// Split factor, chunk and tile for a batch of problems (fills P.splits,
+// P.k_chunk, P.tile, P.tiles): the largest power of two that keeps the launch
+// within target_wgs workgroups and every split at least min_steps K steps deep.
 void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps = 4);
-// Column-tile width of the direct-to-LDS kernel for this launch (128 or 64),
-// or 0 when the register-staged kernel takes it.  Depends on shapes, leading
-// dimensions and pointer alignment only.
-int gemm_lds_bn(const GemmParams& P, bool bf16);
-// Floats of one split's deferred partial of problem g: the whole 128 x bn
-// tiles in fragment order (bn > 0), or the dense M x N block (bn == 0).
+int64_t gemm_tiles128(const GemmDesc& d);  // 128 x 128 tiles of one problem
+// Block width (128, or 64 when no problem is wider) of the fragment order that
+// a launch's deferred split-K partials take.
+int frag_bn(const GemmParams& P);
+// Floats of one split's deferred partial of problem g: whole 128 x bn blocks.
 int64_t frag_partial_floats(const GemmParams& P, int g, int bn);
 
 // kernels.hip
@@ -110,8 +108,8 @@ int colsum_chunks(int B);
 // (many-part jobs) in the launch's index space.
 // Sum of nparts partial blocks (src + k * stride floats, k = 0..nparts-1, in
 // that order) into g + dst.  bn == 0: n contiguous floats.  bn > 0: split-K
-// partials of an M x N GEMM in the direct-to-LDS kernel's fragment order
-// (128 x bn tiles, tiles_n per row of tiles), scattered into the row-major
+// partials of an M x N GEMM in fragment order (128 x bn blocks, tiles_n per
+// row of blocks), scattered into the row-major
 // M x N block at dst.
 struct RedJob {
   int64_t src;
