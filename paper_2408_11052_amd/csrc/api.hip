@@ -137,7 +137,7 @@ struct crl_ctx {
   // workspace plan (byte offsets)
   int64_t ws_bytes;
   int64_t splitk, splitk_floats;
-  int64_t r, c, diag, nphi, npsi, logits, cpm, cps, rowsumH, colsumH, cpartB;
+  int64_t r, c, diag, nphi, npsi, logits, cpm, cps, rowsumH, colsumH;
   int64_t rowterm, rowaux, uphi, upsi;  // pairwise objectives; cosine unit rows
   int64_t phi_b, psi_b, row_m, row_s, col_m, col_s, dx_part, rs_part;
   int64_t xsa2, noise, logpi, fpol, dact;  // actor step
@@ -249,6 +249,27 @@ int64_t plan_params(crl_ctx* x, int first, int last, std::vector<int64_t>& gaps)
   return end;
 }
 
+// dphi = G psi (KC x MC) or dpsi = G^T phi (MC x MC) of the materialised
+// critic matrix: shapes and split plan (the partials are summed by
+// obj_finish_kernel, so a split of eight steps pays)
+GemmParams obj_params(const crl_ctx* x) {
+  GemmParams P{};
+  P.count = 1;
+  GemmDesc& d = P.d[0];
+  d.M = x->B; d.N = x->D; d.K = x->B;
+  d.lda = x->ldF; d.ldb = d.ldc = x->D;
+  d.alpha = 1.f;
+  d.epi = EPI_NONE;
+  P.partial = reinterpret_cast<float*>(1);
+  plan_split_k(P, false, 256, 8);
+  P.partial = nullptr;
+  P.defer_reduce = 1;
+  return P;
+}
+int obj_splits(const crl_ctx* x) {
+  return x->energy == CRL_ENERGY_L1 ? l1_backward_splits(x->B, x->D) : obj_params(x).splits;
+}
+
 // Floats of split-K partials that the largest split GEMM launch needs.
 int64_t splitk_need(crl_ctx* x) {
   int64_t need = 0;
@@ -275,10 +296,8 @@ int64_t splitk_need(crl_ctx* x) {
     const int d[2][3] = {{x->B, x->D, x->H}, {x->B, x->D, x->H}};
     consider(2, d, x->bf16);
   }
-  if (!x->fused) {  // dphi = G psi and dpsi = G^T phi, single FP32 problems
-    const int d[1][3] = {{x->B, x->D, x->B}};
-    consider(1, d, false);
-  }
+  if (!x->fused)  // partials of dphi and dpsi
+    need = std::max(need, (int64_t)2 * obj_splits(x) * x->B * x->D);
   if (x->actor) {
     for (int l = 0; l <= n[2].L; ++l) {
       const int d[1][3] = {{n[2].lay[l].fan_in, n[2].lay[l].fan_out, x->B}};
@@ -395,6 +414,11 @@ bool dw_dx_paired(const crl_ctx* x, const Group& G, int l) {
   return gemm_pair_ok(Pw, dx_params(x, G, l), x->bf16);
 }
 
+// Whether a layer's bias gradient is summed inside its dW launch: the launch
+// then reads the same values that a column sum would (not the BF16 copy of an
+// FP32 output gradient).
+bool bias_from_dw(const crl_ctx* x, bool top) { return top ? !x->bf16 : true; }
+
 // Partial buffers of a group's backward and the jobs that reduce them into
 // the gradient vector: dW split-K partials, bias column partials (output
 // layer, and ReLU hidden layers), LayerNorm column partials (dg, db_ln, db).
@@ -462,9 +486,12 @@ void plan_group(crl_ctx* x, int gi, int64_t& off) {
       const LayerOff& lo = N.lay[l];
       if (top || !x->ln) {
         // the critic's output-layer partials come from the fused InfoNCE
-        // backward reduction (blocks of 256 / D rows), the others from the
-        // column sums
-        const int np = (top && gi == 0 && x->fused) ? fused_bias_chunks(x->B, lo.fan_out) : nrb;
+        // backward reduction (blocks of 256 / D rows), those of a layer whose
+        // dW reads the gradient itself from that launch (one per split), the
+        // others (FP32 gradients with a BF16 copy) from the column sums
+        const int np = (top && gi == 0 && x->fused) ? fused_bias_chunks(x->B, lo.fan_out)
+                       : bias_from_dw(x, top)       ? P.splits
+                                                    : nrb;
         S.bp[l] = take_bytes(x, off, (int64_t)np * lo.fan_out * 4);
         add(G.many, S.bp[l], lo.fan_out, lo.b, np, lo.fan_out);
       }
@@ -510,6 +537,7 @@ void plan_workspace(crl_ctx* x) {
   int64_t off = 0;
   auto take = [&](int64_t bytes) { return take_bytes(x, off, bytes); };
   const int64_t B = x->B, D = x->D;
+  x->ldF = x->fused ? 0 : (int)align_up(B, 8);
   x->ln_rows_per_wave = 16;
   x->ln_nparts = ln_bwd_partials(x->B, x->ln_rows_per_wave);
   for (int e = 0; e < (x->actor ? 3 : 2); ++e) plan_slots(x, e, take_bytes, off);
@@ -526,17 +554,15 @@ void plan_workspace(crl_ctx* x) {
   x->rowterm = take(B * 4);
   x->rowaux = take(B * 4);
   x->uphi = x->upsi = -1;
-  x->logits = x->cpm = x->cps = x->rowsumH = x->colsumH = x->cpartB = -1;
+  x->logits = x->cpm = x->cps = x->rowsumH = x->colsumH = -1;
   x->phi_b = x->psi_b = x->row_m = x->row_s = x->col_m = x->col_s = x->dx_part = x->rs_part = -1;
   if (!x->fused) {
     x->rchunks = 64;
-    x->ldF = (int)align_up(B, 8);
     x->logits = take(B * x->ldF * 4);
     x->cpm = take((int64_t)x->rchunks * B * 4);
     x->cps = take((int64_t)x->rchunks * B * 4);
     x->rowsumH = take(B * 4);
-    x->colsumH = take(B * 4);
-    x->cpartB = take(((B + 127) / 128) * x->ldF * 4);
+    x->colsumH = take((int64_t)obj_splits(x) * B * 4);
     if (x->energy == CRL_ENERGY_COS) {
       x->uphi = take(B * D * 4);
       x->upsi = take(B * D * 4);
@@ -799,17 +825,20 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
         Pw.partial_len = (int64_t)Pw.splits * ps;
         Pw.frag = bn;
       }
-      // bias column partials of this layer (LayerNorm layers get theirs with dZ;
+      // bias partials of this layer (LayerNorm layers get theirs with dZ;
       // top_bias_ready: the output layer's were written with dout)
-      if ((top && !top_bias_ready) || (!top && !x->ln)) {
+      const bool own_bias = (top && !top_bias_ready) || (!top && !x->ln);
+      if (own_bias && bias_from_dw(x, top))
+        for (int e = 0; e < count; ++e)
+          Pw.d[e].bsum = WF(ws, x->sl[nc[e].net].bp[l]);
+      if (own_bias && !bias_from_dw(x, top)) {
         ColSumArgs ca{};
         for (int e = 0; e < count; ++e) {
           const Slots& S = x->sl[nc[e].net];
-          ca.X[e] = top ? (const void*)WF(ws, S.dout) : dZ[e];
+          ca.X[e] = WF(ws, S.dout);
           ca.part[e] = WF(ws, S.bp[l]);
         }
-        const int Nc = top ? N0.out_dim : H;
-        CRL_HIP(launch_colsum_partials(ca, count, B, Nc, Nc, top ? false : x->bf16, s),
+        CRL_HIP(launch_colsum_partials(ca, count, B, N0.out_dim, N0.out_dim, s),
                 "bias gradient");
       }
     }
@@ -907,25 +936,28 @@ int contrastive_fwd(crl_ctx* x, const float* phi, const float* psi, void* ws, co
       d.alpha = 1.f;
       d.epi = EPI_NONE;
       if (x->energy == CRL_ENERGY_COS) {
-        CRL_HIP(launch_unit_rows(phi, WF(ws, o.uphi), WF(ws, o.nphi), B, D, s), "unit rows");
-        CRL_HIP(launch_unit_rows(psi, WF(ws, o.upsi), WF(ws, o.npsi), B, D, s), "unit rows");
+        CRL_HIP(launch_unit_rows(phi, psi, WF(ws, o.uphi), WF(ws, o.upsi), WF(ws, o.nphi),
+                                 WF(ws, o.npsi), B, D, s), "unit rows");
         d.A = WF(ws, o.uphi);
         d.B = WF(ws, o.upsi);
       } else if (x->energy == CRL_ENERGY_L2 || x->energy == CRL_ENERGY_L2SQ) {
-        CRL_HIP(launch_sqnorm(phi, WF(ws, o.nphi), B, D, s), "norms");
-        CRL_HIP(launch_sqnorm(psi, WF(ws, o.npsi), B, D, s), "norms");
         d.epi = x->energy == CRL_ENERGY_L2 ? EPI_L2 : EPI_L2SQ;
-        d.rowv = WF(ws, o.nphi);
-        d.colv = WF(ws, o.npsi);
       }
       plan_split_k(P, false, 512);
       CRL_HIP(launch_gemm(P, false, LAY_KC, LAY_KC, false, s), "logits GEMM");
     }
-    CRL_HIP(launch_row_obj(F, B, x->ldF, x->loss, r, dg, term, WF(ws, o.rowaux), s),
-            "row log-sum-exp and objective terms");
-    const int rc_ = std::min(x->rchunks, B);
-    CRL_HIP(launch_col_lse_partial(F, B, x->ldF, rc_, WF(ws, o.cpm), WF(ws, o.cps), s), "column LSE");
-    CRL_HIP(launch_lse_merge(WF(ws, o.cpm), WF(ws, o.cps), rc_, B, c, s), "column LSE merge");
+    float* cm = WF(ws, o.cpm);
+    float* cs = WF(ws, o.cps);
+    CRL_HIP(launch_row_col(F, B, x->ldF, x->loss, r, dg, term, WF(ws, o.rowaux), cm, cs, s),
+            "row and column log-sum-exps and objective terms");
+    if (col_merge_in_loss(B)) {
+      CRL_HIP(launch_loss(r, c, dg, term, B, x->loss, x->cfg.logsumexp_penalty, loss_out, advance,
+                          s, cm, cs, col_chunks(B)), "loss");
+      return CRL_OK;
+    }
+    LseMergeArgs m{};
+    m.pm[0] = cm; m.ps[0] = cs; m.nparts[0] = col_chunks(B); m.out[0] = c;
+    CRL_HIP(launch_lse_merge(m, 1, B, s), "column LSE merge");
   } else {
     FusedArgs a{};
     a.phi = phi; a.psi = psi;
@@ -960,46 +992,48 @@ int contrastive_bwd(crl_ctx* x, const float* phi, const float* psi, void* ws, fl
     const bool cosine = x->energy == CRL_ENERGY_COS;
     CRL_HIP(launch_grad_obj(F, B, x->ldF, r, c, WF(ws, x->diag), WF(ws, x->rowaux), x->loss,
                             x->energy, beta, rsH, s), "objective gradient");
-    if (x->energy == CRL_ENERGY_L1) {
-      CRL_HIP(launch_l1_backward(phi, psi, F, x->ldF, 0, dphi, B, D, s), "L1 backward");
-      CRL_HIP(launch_l1_backward(psi, phi, F, x->ldF, 1, dpsi, B, D, s), "L1 backward");
+    // both sides' products in one launch, then their split sums, the energy's
+    // own term and the BF16 copies in another
+    const int splits = obj_splits(x);
+    const int64_t n = (int64_t)B * D;
+    float* part = WF(ws, x->splitk);
+    const bool l1 = x->energy == CRL_ENERGY_L1;
+    ObjFinish f{};
+    f.out[0] = dphi; f.out[1] = dpsi;
+    f.part[0] = splits > 1 || l1 ? part : dphi;
+    f.part[1] = splits > 1 || l1 ? part + splits * n : dpsi;
+    f.X[0] = cosine ? WF(ws, x->uphi) : phi;  // the unit rows stand in with the cosine energy
+    f.X[1] = cosine ? WF(ws, x->upsi) : psi;
+    if (l1) {
+      CRL_HIP(launch_l1_backward(phi, psi, F, x->ldF, part, splits, B, D, s), "L1 backward");
     } else {
-      float* splitk = WF(ws, x->splitk);
-      for (int side = 0; side < 2; ++side) {
-        // side 0: dphi = G psi (G as KC); side 1: dpsi = G^T phi (G as MC);
-        // the unit rows stand in for phi and psi with the cosine energy
-        const float* Y = side == 0 ? (cosine ? WF(ws, x->upsi) : psi)
-                                   : (cosine ? WF(ws, x->uphi) : phi);
-        GemmParams P{};
-        P.count = 1;
-        GemmDesc& d = P.d[0];
-        d.A = F; d.lda = x->ldF;
-        d.B = Y; d.ldb = D;
-        d.C = side == 0 ? dphi : dpsi; d.ldc = D;
-        d.M = B; d.N = D; d.K = B;
-        d.alpha = 1.f;
-        d.epi = EPI_NONE;
-        P.partial = splitk;
-        plan_split_k(P, false, 512);
-        P.partial_len = (int64_t)P.splits * B * D;
-        CRL_HIP(launch_gemm(P, false, side == 0 ? LAY_KC : LAY_MC, LAY_MC, false, s), "dphi/dpsi GEMM");
-      }
-      if (dist) {
-        CRL_HIP(launch_l2_fix(dphi, phi, rsH, B, D, s), "distance row term");
-        ColSumArgs ca{};
-        ca.X[0] = F; ca.out[0] = WF(ws, x->colsumH); ca.part[0] = WF(ws, x->cpartB);
-        CRL_HIP(launch_colsum(ca, 1, B, B, x->ldF, false, s), "distance column sums");
-        CRL_HIP(launch_l2_fix(dpsi, psi, WF(ws, x->colsumH), B, D, s), "distance column term");
-      }
-      if (cosine) {
-        CRL_HIP(launch_cos_fix(dphi, WF(ws, x->uphi), WF(ws, x->nphi), B, D, s), "cosine backward");
-        CRL_HIP(launch_cos_fix(dpsi, WF(ws, x->upsi), WF(ws, x->npsi), B, D, s), "cosine backward");
-      }
+      GemmParams Pr = obj_params(x), Pc = obj_params(x);
+      Pr.d[0].A = Pc.d[0].A = F;
+      Pr.d[0].B = f.X[1];
+      Pc.d[0].B = f.X[0];
+      Pr.d[0].C = dphi;
+      Pc.d[0].C = dpsi;
+      Pr.partial = part;
+      Pc.partial = part + splits * n;
+      Pr.partial_len = Pc.partial_len = splits * n;
+      if (dist) Pc.d[0].asum = WF(ws, x->colsumH);  // column sums of H, per split
+      CRL_HIP(launch_gemm_obj(Pc, Pr, s), "dphi and dpsi GEMMs");
+    }
+    if (dist) {
+      f.rs[0] = rsH; f.nrs[0] = 1;
+      f.rs[1] = WF(ws, x->colsumH); f.nrs[1] = splits;
+    }
+    if (cosine) {
+      f.nrm[0] = WF(ws, x->nphi);
+      f.nrm[1] = WF(ws, x->npsi);
     }
     if (x->bf16) {
-      CRL_HIP(launch_cast_bf16(dphi, reinterpret_cast<bf16_t*>(dphi_t), (int64_t)B * D, s), "cast");
-      CRL_HIP(launch_cast_bf16(dpsi, reinterpret_cast<bf16_t*>(dpsi_t), (int64_t)B * D, s), "cast");
+      f.outb[0] = reinterpret_cast<bf16_t*>(dphi_t);
+      f.outb[1] = reinterpret_cast<bf16_t*>(dpsi_t);
     }
+    if (splits > 1 || l1 || dist || cosine || x->bf16)
+      CRL_HIP(launch_obj_finish(f, splits, dist ? kFixDist : cosine ? kFixCos : kFixNone, B, D, s),
+              "dphi and dpsi");
   } else {
     FusedArgs a{};
     a.phi = phi; a.psi = psi;

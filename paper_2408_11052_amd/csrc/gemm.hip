@@ -80,42 +80,61 @@ static int max_tiles(const GemmParams& P) {
   return maxt;
 }
 
-static int64_t tiles_of(const GemmDesc& d, int edge) {
-  return (int64_t)((d.M + edge - 1) / edge) * ((d.N + edge - 1) / edge);
+static int64_t tiles_of(const GemmDesc& d, int tile) {
+  static const int rows[4] = {32, 64, 64, 128}, cols[4] = {32, 32, 64, 128};
+  return (int64_t)((d.M + rows[tile] - 1) / rows[tile]) *
+         ((d.N + cols[tile] - 1) / cols[tile]);
 }
-static int64_t tiles_of(const GemmParams& P, int edge) {
+static int64_t tiles_of(const GemmParams& P, int tile) {
   int64_t n = 0;
-  for (int g = 0; g < P.count; ++g) n += tiles_of(P.d[g], edge);
+  for (int g = 0; g < P.count; ++g) n += tiles_of(P.d[g], tile);
   return n;
 }
-int64_t gemm_tiles128(const GemmDesc& d) { return tiles_of(d, 128); }
+int64_t gemm_tiles128(const GemmDesc& d) { return tiles_of(d, kTile128); }
 
-static void set_tile(GemmParams& P, int edge) {
-  P.tile = edge;
+static void set_tile(GemmParams& P, int tile) {
+  static const int cols[4] = {32, 32, 64, 128};
+  P.tile = tile;
   for (int g = 0; g < P.count; ++g) {
-    P.tiles_n[g] = (P.d[g].N + edge - 1) / edge;
-    P.tiles[g] = (int)tiles_of(P.d[g], edge);
+    P.tiles_n[g] = (P.d[g].N + cols[tile] - 1) / cols[tile];
+    P.tiles[g] = (int)tiles_of(P.d[g], tile);
   }
 }
 
-// Tile edge of a launch of n32, n64 work items at edges 32 and 64.  A small
-// tile spreads a small launch over more CUs and shortens its longest wave, but
-// reads its operands from LDS more often; the lines lie where the small tile's
-// launch grows past what is resident.  Measured per launch (us, K = N):
-//   BF16, K 1024: 512 work items of edge 32 against 128 of edge 64: 7.2 / 8.5;
-//     1024 / 256: 12.4 / 8.7.  512 of edge 64 against 128 of edge 128: 10.2 /
-//     12.0; 1024 / 256: 18.4 / 13.4.
-//   FP32, K 1024: 512 of edge 32 against 128 of edge 64: 15.9 / 25.6; 1024 /
-//     256: 29.5 / 26.8.  1024 of edge 64 against 256 of edge 128: 70.0 / 73.3;
-//     2048 / 512: 139 / 126 (the MFMAs bind, not the launch).
-static int tile_edge(int64_t n32, int64_t n64, bool bf16) {
-  if (n32 <= 512) return 32;
-  return n64 <= (bf16 ? 512 : 1024) ? 64 : 128;
+// Tile of a launch with n[tile] work items in each: the one with the least
+// time, taken as (work items of the busiest of 256 CUs) x (a work item's
+// time).  A small tile spreads a small launch and shortens its longest chain;
+// a large one reads its operands from LDS less often.  The times are measured
+// per K of 1024, launch overhead off, in us; the first number is that of a CU
+// with one work item, whose latencies nothing hides, the second that of each
+// of several.  (FP32, 2 x 600 x 1024 x 1024: 33.4 us in 32, 28.8 in 64 x 32,
+// 35.6 in 64 tiles; 2 x 256: 15.4, 17.9, 25.4; 2 x 4096: 161, 140, 133, and
+// 126 in 128 tiles.  BF16, 2 x 512: 12.5 us in 32, 8.5 in 64, 11.6 in 128
+// tiles; 2 x 2048: 43, 18.5, 13.4.)
+static int pick_tile(const int64_t (&n)[4], bool bf16) {
+  static const double one[2][4] = {{5.7, 13.9, 21.3, 66.0}, {2.1, 1e9, 4.4, 8.0}};
+  static const double more[2][4] = {{5.6, 8.2, 16.0, 61.0}, {2.1, 1e9, 3.4, 8.7}};
+  int best = kTile128;
+  double least = 1e300;
+  for (int t = kTile128; t >= kTile32; --t) {
+    const int64_t rounds = (n[t] + 255) / 256;
+    const double us = rounds <= 1 ? one[bf16][t] : more[bf16][t] * (double)rounds;
+    if (us < least) {
+      least = us;
+      best = t;
+    }
+  }
+  return best;
+}
+static int pick_tile(const GemmParams& P, int splits, bool bf16) {
+  int64_t n[4];
+  for (int t = 0; t < 4; ++t) n[t] = tiles_of(P, t) * splits;
+  return pick_tile(n, bf16);
 }
 
-template <typename T, int LA, int LB, typename OutT, int EDGE, bool ALT>
+template <typename T, int LA, int LB, typename OutT, int TILE, bool ALT>
 static void run_tile(const GemmParams& P, hipStream_t s) {
-  typedef typename lds::TileOf<T, EDGE>::type C;
+  typedef typename lds::TileOf<T, TILE>::type C;
   const dim3 grid(max_tiles(P), P.splits, P.count);
   gemm_lds_kernel<T, LA, LB, OutT, C, ALT><<<grid, C::NT, 0, s>>>(P);
 }
@@ -127,19 +146,20 @@ static hipError_t run(GemmParams& P, hipStream_t s) {
   double flops = 0.0, bytes = 0.0;
   algo_counts(P, sizeof(T), sizeof(OutT), flops, bytes);
   // BF16 launches with a K that is no whole number of stages: the other k
-  // order (see fragment), edge 64
+  // order (see fragment), 64 tiles
   bool alt = false;
   if (sizeof(T) == 2)
     for (int g = 0; g < P.count; ++g) alt = alt || P.d[g].K % lds::bk<T>() != 0;
-  if (alt) set_tile(P, 64);
+  if (alt) set_tile(P, kTile64);
   KTimer t = timing_begin(lds_kernel_name<T, LA, LB, OutT>(), flops, bytes, s);
   if constexpr (sizeof(T) == 2) {
-    if (alt) run_tile<T, LA, LB, OutT, 64, true>(P, s);
+    if (alt) run_tile<T, LA, LB, OutT, kTile64, true>(P, s);
   }
   if (!alt) {
-    if (P.tile == 128) run_tile<T, LA, LB, OutT, 128, false>(P, s);
-    else if (P.tile == 64) run_tile<T, LA, LB, OutT, 64, false>(P, s);
-    else run_tile<T, LA, LB, OutT, 32, false>(P, s);
+    if (P.tile == kTile128) run_tile<T, LA, LB, OutT, kTile128, false>(P, s);
+    else if (P.tile == kTile64) run_tile<T, LA, LB, OutT, kTile64, false>(P, s);
+    else if (P.tile == kTile32) run_tile<T, LA, LB, OutT, kTile32, false>(P, s);
+    else if constexpr (sizeof(T) == 4) run_tile<T, LA, LB, OutT, kTile64x32, false>(P, s);
   }
   timing_end(t);
   hipError_t e = hipGetLastError();
@@ -176,43 +196,63 @@ bool gemm_pair_ok(const GemmParams& Pw, const GemmParams& Px, bool bf16) {
          max_tiles(Px) > 0;
 }
 
-template <typename T, int EDGE>
-static void run_pair(const GemmParams& Pw, const GemmParams& Px, const PairGrid& G,
-                     hipStream_t s) {
-  typedef typename lds::TileOf<T, EDGE>::type C;
-  gemm_lds_pair_kernel<T, LAY_MC, LAY_MC, float, LAY_KC, LAY_KC, T, C>
-      <<<G.n1 + G.n2, C::NT, 0, s>>>(Pw, Px, G);
+// Tile of a pair of launches, and the grid that holds both.
+static PairGrid plan_pair(GemmParams& P1, GemmParams& P2, bool bf16) {
+  int64_t n[4];
+  for (int t = 0; t < 4; ++t) n[t] = tiles_of(P1, t) * P1.splits + tiles_of(P2, t) * P2.splits;
+  const int tile = pick_tile(n, bf16);
+  set_tile(P1, tile);
+  set_tile(P2, tile);
+  PairGrid G;
+  G.gx1 = max_tiles(P1);
+  G.gy1 = P1.splits;
+  G.n1 = G.gx1 * G.gy1 * P1.count;
+  G.gx2 = max_tiles(P2);
+  G.gy2 = P2.splits;
+  G.n2 = G.gx2 * G.gy2 * P2.count;
+  return G;
+}
+
+template <typename T, int TILE, int LA2, int LB2>
+static void run_pair_tile(const GemmParams& P1, const GemmParams& P2, const PairGrid& G,
+                          hipStream_t s) {
+  typedef typename lds::TileOf<T, TILE>::type C;
+  gemm_lds_pair_kernel<T, LAY_MC, LAY_MC, float, LA2, LB2, T, C>
+      <<<G.n1 + G.n2, C::NT, 0, s>>>(P1, P2, G);
+}
+template <typename T, int LA2, int LB2>
+static void run_pair(GemmParams& P1, GemmParams& P2, hipStream_t s) {
+  const PairGrid G = plan_pair(P1, P2, sizeof(T) == 2);
+  if (P1.tile == kTile128) run_pair_tile<T, kTile128, LA2, LB2>(P1, P2, G, s);
+  else if (P1.tile == kTile64) run_pair_tile<T, kTile64, LA2, LB2>(P1, P2, G, s);
+  else if (P1.tile == kTile32) run_pair_tile<T, kTile32, LA2, LB2>(P1, P2, G, s);
+  else if constexpr (sizeof(T) == 4) run_pair_tile<T, kTile64x32, LA2, LB2>(P1, P2, G, s);
 }
 
 hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s) {
   if (!gemm_pair_ok(Pw, Px, bf16) || !operands_ok(Pw, bf16) || !operands_ok(Px, bf16))
     return hipErrorInvalidValue;
-  const int edge = tile_edge(tiles_of(Pw, 32) * Pw.splits + tiles_of(Px, 32),
-                             tiles_of(Pw, 64) * Pw.splits + tiles_of(Px, 64), bf16);
-  set_tile(Pw, edge);
-  set_tile(Px, edge);
-  PairGrid G;
-  G.gx1 = max_tiles(Pw);
-  G.gy1 = Pw.splits;
-  G.n1 = G.gx1 * G.gy1 * Pw.count;
-  G.gx2 = max_tiles(Px);
-  G.gy2 = 1;
-  G.n2 = G.gx2 * Px.count;
   double flops = 0.0, bytes = 0.0;
   const double es = bf16 ? 2.0 : 4.0;
   algo_counts(Pw, es, 4.0, flops, bytes);
   algo_counts(Px, es, es, flops, bytes);
   KTimer t = timing_begin(bf16 ? "gemm_lds_pair_kernel<dW,dX>" : "gemm_lds_pair_kernel<f32,dW,dX>",
                           flops, bytes, s);
-  if (bf16) {
-    if (edge == 128) run_pair<bf16_t, 128>(Pw, Px, G, s);
-    else if (edge == 64) run_pair<bf16_t, 64>(Pw, Px, G, s);
-    else run_pair<bf16_t, 32>(Pw, Px, G, s);
-  } else {
-    if (edge == 128) run_pair<float, 128>(Pw, Px, G, s);
-    else if (edge == 64) run_pair<float, 64>(Pw, Px, G, s);
-    else run_pair<float, 32>(Pw, Px, G, s);
-  }
+  if (bf16) run_pair<bf16_t, LAY_KC, LAY_KC>(Pw, Px, s);
+  else run_pair<float, LAY_KC, LAY_KC>(Pw, Px, s);
+  timing_end(t);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_obj(GemmParams& Pc, GemmParams& Pr, hipStream_t s) {
+  if (!operands_ok(Pc, false) || !operands_ok(Pr, false)) return hipErrorInvalidValue;
+  if ((Pc.splits > 1 && !Pc.defer_reduce) || (Pr.splits > 1 && !Pr.defer_reduce))
+    return hipErrorInvalidValue;
+  double flops = 0.0, bytes = 0.0;
+  algo_counts(Pc, 4.0, 4.0, flops, bytes);
+  algo_counts(Pr, 4.0, 4.0, flops, bytes);
+  KTimer t = timing_begin("gemm_lds_pair_kernel<f32,dpsi,dphi>", flops, bytes, s);
+  run_pair<float, LAY_KC, LAY_MC>(Pc, Pr, s);
   timing_end(t);
   return hipGetLastError();
 }
@@ -221,14 +261,14 @@ void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps) {
   const int BK = bf16 ? lds::bk<bf16_t>() : lds::bk<float>();
   int kmax = 0;
   for (int g = 0; g < P.count; ++g) kmax = P.d[g].K > kmax ? P.d[g].K : kmax;
-  // BF16 splits are counted in tiles of edge 128 whatever tile runs (the
-  // split decides how a sum that is later rounded to BF16 is formed).  An FP32
-  // step of K is half as deep and four times as slow in MFMAs, so its tiles
-  // are chosen first; a reduction launch of its own (4.7 us) pays from 32
-  // steps per split on (an edge-32 work item takes 0.33 us a step).
-  int64_t tiles = tiles_of(P, 128);
+  // BF16 splits are counted in 128 tiles whatever tile runs (the split decides
+  // how a sum that is later rounded to BF16 is formed).  An FP32 step of K is
+  // half as deep and four times as slow in MFMAs, so its tiles are chosen
+  // first; a reduction launch of its own (4.7 us) pays from 32 steps per split
+  // on (a 32-tile work item takes 0.33 us a step).
+  int64_t tiles = tiles_of(P, kTile128);
   if (!bf16) {
-    tiles = tiles_of(P, tile_edge(tiles_of(P, 32), tiles_of(P, 64), false));
+    tiles = tiles_of(P, pick_tile(P, 1, false));
     if (min_steps < 8) min_steps = 32;
   }
   int splits = 1;
@@ -241,7 +281,7 @@ void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps) {
   if (kc == 0) kc = BK;
   P.splits = splits;
   P.k_chunk = kc;
-  set_tile(P, tile_edge(tiles_of(P, 32) * splits, tiles_of(P, 64) * splits, bf16));
+  set_tile(P, pick_tile(P, splits, bf16));
 }
 
 hipError_t launch_gemm(GemmParams& P, bool bf16, int la, int lb, bool out_bf16, hipStream_t s) {

@@ -20,8 +20,8 @@ enum : int {
   EPI_BIAS = 1,      // v + bias[n]
   EPI_BIAS_RELU = 2, // max(v + bias[n], 0)
   EPI_MASK_POS = 3,  // aux(m,n) > 0 ? v : 0      (ReLU backward)
-  EPI_L2 = 4,        // -l2_dist(rowv[m], colv[n], v)
-  EPI_L2SQ = 5       // -l2sq_dist(rowv[m], colv[n], v)
+  EPI_L2 = 4,        // -l2_dist(|A(m,.)|^2, |B(.,n)|^2, v)   (FP32 KC x KC,
+  EPI_L2SQ = 5       // -l2sq_dist(|A(m,.)|^2, |B(.,n)|^2, v)  unsplit)
 };
 
 struct GemmDesc {
@@ -30,8 +30,6 @@ struct GemmDesc {
   void* C;
   const float* bias;
   const void* aux;    // same storage type and leading dim as C
-  const float* rowv;
-  const float* colv;
   int M, N, K;
   int lda, ldb, ldc;
   int epi;
@@ -39,14 +37,17 @@ struct GemmDesc {
   int kb;             // rows k < kb of an MC-layout B exist (0: all K).  Rows
                       // k >= kb are re-reads of row kb-1; the caller
                       // guarantees A is zero in those columns
+  float* asum;        // FP32 MC x MC launches: sum_k A(m,k) to asum[split * M + m], or NULL
+  float* bsum;        // MC x MC launches: sum_k B(k,n) to bsum[split * N + n], or NULL
 };
 
 constexpr int kGemmMaxGroup = 2;
+enum : int { kTile32 = 0, kTile64x32 = 1, kTile64 = 2, kTile128 = 3 };  // rows x columns
 
 struct GemmParams {
   GemmDesc d[kGemmMaxGroup];
   int count;
-  int tile;            // tile edge of the launch: 128, 64 or 32 (plan_split_k)
+  int tile;            // kTile*, chosen by plan_split_k
   int tiles_n[kGemmMaxGroup];
   int tiles[kGemmMaxGroup];
   int splits;          // split-K factor (>= 1)

@@ -2,8 +2,8 @@
 // (global_load_lds_dwordx4: no staging registers), for BF16 and FP32 storage.
 //
 // A stage is 128 bytes of K of every tile row (64 BF16 or 32 FP32 values);
-// ST stages ring through LDS, so ST - 1 stages (and, software-pipelined, half
-// a stage of fragments in registers) are in flight while one is multiplied.
+// ST stages ring through LDS, so ST - 1 of them are in flight while one is
+// multiplied (BF16: software-pipelined by half a stage of fragments as well).
 // Tiles that are contiguous along K (KC) are read with ds_read_b128 through an
 // XOR swizzle of their 16-byte chunks; tiles contiguous along M or N (MC) are
 // read with the 16-bit transpose read ds_read_b64_tr_b16 (BF16), which turns
@@ -46,17 +46,18 @@ template <int BM_, int BN_, int WM_, int WN_, int ST_, int OCC_> struct Tile {
   static constexpr int EPI = 4 * BM * (BN + 4);  // FP32 epilogue tile, shares the stages' space
   static constexpr int SMEM = ST * STAGE > EPI ? ST * STAGE : EPI;
 };
-// The three tile edges of each storage type.  Two 128-tile workgroups fit a CU
-// (64 KB of stages each); a third stage would leave one, which measured slower
-// (26.5 against 20.7 us for the 2 x 4096 x 1024 x 1024 input gradient), as did
+// The tiles of each storage type.  Two 128-tile workgroups fit a CU (64 KB of
+// stages each); a third stage would leave one, which measured slower (26.5
+// against 20.7 us for the 2 x 4096 x 1024 x 1024 input gradient), as did
 // 256 x 128 tiles with eight waves (22.1 us) and sixteen (20.5; no gain).
-template <typename T, int EDGE> struct TileOf;
-template <> struct TileOf<bf16_t, 128> { typedef Tile<128, 128, 2, 4, 2, 4> type; };
-template <> struct TileOf<bf16_t, 64> { typedef Tile<64, 64, 2, 2, 3, 2> type; };
-template <> struct TileOf<bf16_t, 32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
-template <> struct TileOf<float, 128> { typedef Tile<128, 128, 2, 2, 2, 2> type; };
-template <> struct TileOf<float, 64> { typedef Tile<64, 64, 2, 2, 3, 2> type; };
-template <> struct TileOf<float, 32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
+template <typename T, int TILE> struct TileOf;
+template <> struct TileOf<bf16_t, kTile128> { typedef Tile<128, 128, 2, 4, 2, 4> type; };
+template <> struct TileOf<bf16_t, kTile64> { typedef Tile<64, 64, 2, 2, 3, 2> type; };
+template <> struct TileOf<bf16_t, kTile32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
+template <> struct TileOf<float, kTile128> { typedef Tile<128, 128, 2, 2, 2, 2> type; };
+template <> struct TileOf<float, kTile64> { typedef Tile<64, 64, 2, 2, 2, 2> type; };
+template <> struct TileOf<float, kTile64x32> { typedef Tile<64, 32, 2, 2, 3, 2> type; };
+template <> struct TileOf<float, kTile32> { typedef Tile<32, 32, 2, 2, 4, 2> type; };
 
 // KC tile: row r holds 128 bytes of K (8 chunks of 16 B); logical chunk c sits
 // in slot c ^ kc_swz(r).  A ds_read_b128 pass of 16 rows then touches 16
@@ -244,6 +245,27 @@ __device__ __forceinline__ void mma_half(floatx4 (&acc)[C::MI][C::NJ], const flo
       for (int j = 0; j < C::NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
 }
+// acc + (sum over K of one fragment's rows), through a product with ones; rhs:
+// the fragment is the column operand
+__device__ __forceinline__ floatx4 mma_ones(bf16x8 x, floatx4 acc, bool rhs) {
+  const __bf16 o = (__bf16)1.f;
+  const bf16x8 one = {o, o, o, o, o, o, o, o};
+  return rhs ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x, acc, 0, 0, 0)
+             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, one, acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mma_ones(floatx4 x, floatx4 acc, bool rhs) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    acc = rhs ? __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, x[q], acc, 0, 0, 0)
+              : __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], 1.f, acc, 0, 0, 0);
+  return acc;
+}
+__device__ __forceinline__ float square_sum(floatx4 x, float s) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s = __builtin_fmaf(x[q], x[q], s);
+  return s;
+}
+__device__ __forceinline__ float square_sum(bf16x8, float s) { return s; }  // not used
 }  // namespace lds
 
 // One workgroup's work item wi of launch P; smem holds C::SMEM bytes.
@@ -268,6 +290,23 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // MC x MC launches may ask for an operand's sums over K (wave-uniform)
+  constexpr bool SUMS = LA == LAY_MC && LB == LAY_MC;
+  constexpr int NS = sizeof(T) == 2 || NJ > MI ? NJ : MI;  // A's sums: FP32 only
+  const bool want_a = SUMS && sizeof(T) == 4 && D.asum != nullptr && tn == 0 && wn == 0;
+  const bool want_b = SUMS && D.bsum != nullptr && tm == 0 && wm == 0;
+  floatx4 ks[NS], kss[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) ks[i] = kss[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // distance energies (FP32 KC x KC): the rows' squared norms
+  constexpr bool DIST = LA == LAY_KC && LB == LAY_KC && sizeof(T) == 4;
+  const bool dist = DIST && (D.epi == EPI_L2 || D.epi == EPI_L2SQ);
+  float na[MI], nb[NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) na[i] = 0.f;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) nb[j] = 0.f;
 
   if (nk > 0) {
     typedef Operand<T, LA, C::BM, C::NW> OpA;
@@ -309,6 +348,30 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     // FP32: the running sums are added into `sum` every 128 of K, so that a
     // long K rounds like the short chains of a split one
     floatx4 sum[MI][NJ];
+    // the operands' own sums over K: one more MFMA per fragment with ones, in
+    // the first tile row (B) or column (A) of the launch
+    auto sum_k = [&](const typename Frag<T>::type (&a)[MI], const typename Frag<T>::type (&b)[NJ]) {
+      if constexpr (SUMS) {
+        if constexpr (sizeof(T) == 4)
+          if (want_a)
+#pragma unroll
+            for (int i = 0; i < MI; ++i) ks[i] = mma_ones(a[i], ks[i], false);
+        if (want_b)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) ks[j] = mma_ones(b[j], ks[j], true);
+      }
+    };
+    // squared norms of the operands' rows, from the fragments as they pass
+    auto norms = [&](const typename Frag<T>::type (&a)[MI], const typename Frag<T>::type (&b)[NJ]) {
+      if constexpr (DIST) {
+        if (dist) {
+#pragma unroll
+          for (int i = 0; i < MI; ++i) na[i] = square_sum(a[i], na[i]);
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) nb[j] = square_sum(b[j], nb[j]);
+        }
+      }
+    };
     auto flush = [&]() {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
@@ -317,6 +380,12 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
           sum[i][j] += acc[i][j];
           acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
+      if constexpr (SUMS)
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+          kss[i] += ks[i];
+          ks[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
     };
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
@@ -324,33 +393,57 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
 #pragma unroll
         for (int j = 0; j < NJ; ++j) sum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
+    auto multiply = [&](const typename Frag<T>::type (&a)[MI],
+                        const typename Frag<T>::type (&b)[NJ]) {
+      mma_half<C>(acc, a, b);
+      sum_k(a, b);
+      norms(a, b);
+    };
     typename Frag<T>::type a0[MI], b0[NJ], a1[MI], b1[NJ];
+    if constexpr (sizeof(T) == 4) {
+      // FP32: the MFMAs of a half (32 cycles each) outlast its LDS reads, and
+      // holding the next half's fragments measured 7 to 15% slower
 #pragma unroll
-    for (int s = 0; s < C::ST; ++s)
-      if (s < nk) issue(s);
-    arrive(0, min(nk, (int)C::ST) - 1);
-    finish(0, smem);
-    load_half<T, LA, LB, C, ALT>(a0, b0, smem, 0, wm, wn, lane);
-    for (int kt = 0; kt < nk; ++kt) {
-      // one half's fragments are read while the other half multiplies
-      load_half<T, LA, LB, C, ALT>(a1, b1, smem + tail * C::STAGE, 1, wm, wn, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      mma_half<C>(acc, a0, b0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (kt + 1 < nk) {
-        tail = tail + 1 == C::ST ? 0 : tail + 1;
-        // issued by now: stages up to kt + ST - 1
-        arrive(kt + 1, min(nk - 2 - kt, C::ST - 2));
-        if (kt + C::ST < nk) issue(kt + C::ST);
+      for (int s = 0; s < C::ST - 1; ++s)
+        if (s < nk) issue(s);
+      for (int kt = 0; kt < nk; ++kt) {
+        arrive(kt, min(nk - 1 - kt, C::ST - 2));
+        if (kt + C::ST - 1 < nk) issue(kt + C::ST - 1);
         char* st = smem + tail * C::STAGE;
-        finish(kt + 1, st);
+        tail = tail + 1 == C::ST ? 0 : tail + 1;
+        finish(kt, st);
         load_half<T, LA, LB, C, ALT>(a0, b0, st, 0, wm, wn, lane);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      mma_half<C>(acc, a1, b1);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (sizeof(T) == 4)
+        multiply(a0, b0);
+        load_half<T, LA, LB, C, ALT>(a1, b1, st, 1, wm, wn, lane);
+        multiply(a1, b1);
         if ((kt & 3) == 3) flush();
+      }
+    } else {
+      // BF16: one half's fragments are read while the other half multiplies
+#pragma unroll
+      for (int s = 0; s < C::ST; ++s)
+        if (s < nk) issue(s);
+      arrive(0, min(nk, (int)C::ST) - 1);
+      finish(0, smem);
+      load_half<T, LA, LB, C, ALT>(a0, b0, smem, 0, wm, wn, lane);
+      for (int kt = 0; kt < nk; ++kt) {
+        load_half<T, LA, LB, C, ALT>(a1, b1, smem + tail * C::STAGE, 1, wm, wn, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a0, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + 1 < nk) {
+          tail = tail + 1 == C::ST ? 0 : tail + 1;
+          // issued by now: stages up to kt + ST - 1
+          arrive(kt + 1, min(nk - 2 - kt, C::ST - 2));
+          if (kt + C::ST < nk) issue(kt + C::ST);
+          char* st = smem + tail * C::STAGE;
+          finish(kt + 1, st);
+          load_half<T, LA, LB, C, ALT>(a0, b0, st, 0, wm, wn, lane);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a1, b1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     if constexpr (sizeof(T) == 4) {
       flush();
@@ -358,6 +451,28 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = sum[i][j];
+#pragma unroll
+      for (int i = 0; i < NS; ++i) ks[i] = kss[i];
+    }
+  }
+  if constexpr (SUMS) {
+    // every column (A) or row (B) of a ones product holds the sum
+    if constexpr (sizeof(T) == 4)
+      if (want_a && (lane & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = m0 + (wm * MI + i) * 16 + (lane >> 4) * 4 + r;
+            if (row < D.M) D.asum[(int64_t)wi.split * D.M + row] = ks[i][r];
+          }
+      }
+    if (want_b && lane < 16) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int col = n0 + (wn * NJ + j) * 16 + lane;
+        if (col < D.N) D.bsum[(int64_t)wi.split * D.N + col] = ks[j][0];
+      }
     }
   }
   const bool split = P.splits > 1;
@@ -391,14 +506,26 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
   float* Cs = reinterpret_cast<float*>(smem);
   const int epi = split ? EPI_NONE : D.epi;
   const bool has_bias = epi == EPI_BIAS || epi == EPI_BIAS_RELU;
-  const bool dist = epi == EPI_L2 || epi == EPI_L2SQ;
+  if constexpr (DIST) {
+    if (dist) {  // each lane's quarter of K; then lane (g, j) has row / column j's norm
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        na[i] += __shfl_xor(na[i], 16, 64);
+        na[i] += __shfl_xor(na[i], 32, 64);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        nb[j] += __shfl_xor(nb[j], 16, 64);
+        nb[j] += __shfl_xor(nb[j], 32, 64);
+      }
+    }
+  }
   const float alpha = split ? 1.f : D.alpha;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int cl = (wn * NJ + j) * 16 + r16;
     const int col = min(n0 + cl, D.N - 1);  // past-the-edge values are not stored
     const float bcol = has_bias ? D.bias[col] : 0.f;
-    const float ccol = dist ? D.colv[col] : 0.f;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -406,9 +533,11 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
         const int rl = (wm * MI + i) * 16 + gq * 4 + r;
         float v = acc[i][j][r] * alpha + bcol;
         if (epi == EPI_BIAS_RELU) v = fmaxf(v, 0.f);
-        if (sizeof(T) == 4 && dist) {
-          const float rv = D.rowv[min(m0 + rl, D.M - 1)];
-          v = epi == EPI_L2 ? -l2_dist(rv, ccol, v) : -l2sq_dist(rv, ccol, v);
+        if constexpr (DIST) {
+          if (dist) {
+            const float rv = __shfl(na[i], gq * 4 + r, 64);
+            v = epi == EPI_L2 ? -l2_dist(rv, nb[j], v) : -l2sq_dist(rv, nb[j], v);
+          }
         }
         Cs[rl * kLdc + cl] = v;
       }
@@ -464,7 +593,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
 }
 
 template <typename T, int LA, int LB, typename OutT, typename C, bool ALT>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC)))
 void gemm_lds_kernel(GemmParams P) {
   __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   gemm_lds_tile<T, LA, LB, OutT, C, ALT>(P, gemm_work_item(), smem);
@@ -476,7 +605,7 @@ void gemm_lds_kernel(GemmParams P) {
 // second launch's tiles fill the first one's tail.
 struct PairGrid { int n1, gx1, gy1, gx2, gy2, n2; };
 template <typename T, int LA1, int LB1, typename Out1, int LA2, int LB2, typename Out2, typename C>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC)))
 void gemm_lds_pair_kernel(GemmParams P1, GemmParams P2, PairGrid G) {
   __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   const int id = blockIdx.x;

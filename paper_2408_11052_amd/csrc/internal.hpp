@@ -33,6 +33,9 @@ hipError_t launch_gemm(GemmParams& P, bool bf16, int la, int lb, bool out_bf16,
 // reduction left to run; a BF16 dX whose K is whole stages).
 bool gemm_pair_ok(const GemmParams& Pw, const GemmParams& Px, bool bf16);
 hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s);
+// dpsi = G^T phi (Pc: MC x MC) and dphi = G psi (Pr: KC x MC) of the
+// materialised critic matrix in one launch, FP32; splits stay unreduced.
+hipError_t launch_gemm_obj(GemmParams& Pc, GemmParams& Pr, hipStream_t s);
 // Split factor, chunk and tile for a batch of problems (fills P.splits,
 // P.k_chunk, P.tile, P.tiles): the largest power of two that keeps the launch
 // within target_wgs workgroups and every split at least min_steps K steps deep.
@@ -80,25 +83,13 @@ hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf
                                int rows_per_wave, hipStream_t s);
 int ln_bwd_partials(int B, int rows_per_wave);
 
-// out[k][n] = sum_w part[w][k][n] for k < nk; the three sums go to out0/1/2.
-struct ColReduceArgs {
-  const float* part[2];
-  float* out[2][3];
-};
-hipError_t launch_partial_reduce(const ColReduceArgs& a, int count, int nparts, int nk,
-                                 int N, hipStream_t s);
-
-// column sums of X [B][N] (FP32 or BF16), written to out[N] (FP32).
+// column sums of X [B][N] (FP32) over chunks of 128 rows: part[e][ceil(B/128)][N]
 struct ColSumArgs {
-  const void* X[2];
-  float* out[2];
-  float* part[2];   // [ceil(B/128)][N]
+  const float* X[2];
+  float* part[2];
 };
-hipError_t launch_colsum(const ColSumArgs& a, int count, int B, int N, int ld,
-                         bool bf16, hipStream_t s);
-// only the per-chunk partials part[e][ceil(B/128)][N] of launch_colsum
 hipError_t launch_colsum_partials(const ColSumArgs& a, int count, int B, int N, int ld,
-                                  bool bf16, hipStream_t s);
+                                  hipStream_t s);
 int colsum_chunks(int B);
 
 // Deferred gradient reductions: g[dst + i] = sum_k part_k[i], part_k at byte
@@ -133,7 +124,6 @@ hipError_t launch_grad_reduce(const char* ws, float* g, const RedJob* few, int n
                               int64_t total4, const RedJob* many, int nmany, int64_t nblocks,
                               double bytes, hipStream_t s, const AdamArgs* A = nullptr);
 
-hipError_t launch_sqnorm(const float* X, float* out, int B, int D, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
 // Adam coefficients: 1 - b and log b are formed in double on the host.
 struct AdamCoef {
@@ -152,9 +142,6 @@ struct AdamArgs {
 };
 hipError_t launch_counter_add(int64_t* c, int64_t inc, hipStream_t s);
 
-// materialised critic matrix (FP32 B x B in the workspace, row stride ld)
-hipError_t launch_col_lse_partial(const float* F, int B, int ld, int rchunks, float* pm,
-                                  float* ps, hipStream_t s);
 // log-sum-exp of (max, sum) partials [nparts][B] per column j, for `count`
 // problems in one launch
 struct LseMergeArgs {
@@ -164,31 +151,49 @@ struct LseMergeArgs {
   float* out[2];
 };
 hipError_t launch_lse_merge(const LseMergeArgs& a, int count, int B, hipStream_t s);
-hipError_t launch_lse_merge(const float* pm, const float* ps, int nparts, int B,
-                            float* out, hipStream_t s);
 // loss_out[8] from r, c, diag and (pairwise objectives) the per-row terms;
-// then *advance += 1 if advance is not NULL (one workgroup, so no fence)
-hipError_t launch_loss(const float* r, const float* c, const float* diag, const float* term,
+// then *advance += 1 if advance is not NULL (one workgroup, so no fence).
+// nparts > 0: c is first formed (and written) from the column partials.
+hipError_t launch_loss(const float* r, float* c, const float* diag, const float* term,
                        int B, int loss, float beta, float* loss_out, int64_t* advance,
-                       hipStream_t s);
-hipError_t launch_l2_fix(float* dX, const float* X, const float* rs, int B, int D,
-                         hipStream_t s);
+                       hipStream_t s, const float* col_m = nullptr, const float* col_s = nullptr,
+                       int nparts = 0);
 
 // objectives.hip: energies and objectives on the materialised matrix
-hipError_t launch_unit_rows(const float* X, float* U, float* nrm, int B, int D, hipStream_t s);
+// unit rows U and norms of phi and psi
+hipError_t launch_unit_rows(const float* phi, const float* psi, float* Uphi, float* Upsi,
+                            float* nphi, float* npsi, int B, int D, hipStream_t s);
 hipError_t launch_l1_energy(const float* phi, const float* psi, float* F, int B, int D, int ld,
                             hipStream_t s);
-hipError_t launch_l1_backward(const float* X, const float* Y, const float* G, int ldg, int trans,
-                              float* dX, int B, int D, hipStream_t s);
+// partials part[side][split][B][D] of dphi (side 0) and dpsi (1)
+int l1_backward_splits(int B, int D);
+hipError_t launch_l1_backward(const float* phi, const float* psi, const float* G, int ldg,
+                              float* part, int splits, int B, int D, hipStream_t s);
 // r, diag, and for the pairwise objectives the row terms and the sums that
-// form dL/dF_ii
-hipError_t launch_row_obj(const float* F, int B, int ld, int loss, float* r, float* diag,
-                          float* term, float* aux, hipStream_t s);
+// form dL/dF_ii; and the columns' (max, sum) over col_chunks(B) chunks of rows
+int col_chunks(int B);
+bool col_merge_in_loss(int B);  // few enough columns for the loss kernel to merge the chunks
+hipError_t launch_row_col(const float* F, int B, int ld, int loss, float* r, float* diag,
+                          float* term, float* aux, float* col_m, float* col_s, hipStream_t s);
 // in place F -> dL/dF (or H for the distance energies, with its row sums)
 hipError_t launch_grad_obj(float* F, int B, int ld, const float* r, const float* c,
                            const float* diag, const float* aux, int loss, int energy, float beta,
                            float* rowsum, hipStream_t s);
-hipError_t launch_cos_fix(float* dX, const float* U, const float* nrm, int B, int D, hipStream_t s);
+// dphi (side 0) and dpsi (1) from `splits` partials [splits][B][D] (which may
+// be the output itself, splits = 1), then the energy's own term:
+//   kFixDist: -= (sum of nrs row sums rs[k][row]) X;  kFixCos: X the unit rows,
+//   (v - (v . X) X) / nrm.  outb: BF16 copies, or NULL.
+enum : int { kFixNone = 0, kFixDist = 1, kFixCos = 2 };
+struct ObjFinish {
+  const float* part[2];
+  float* out[2];
+  bf16_t* outb[2];
+  const float* X[2];
+  const float* rs[2];
+  int nrs[2];
+  const float* nrm[2];
+};
+hipError_t launch_obj_finish(const ObjFinish& a, int splits, int fix, int B, int D, hipStream_t s);
 
 // fused InfoNCE (BF16 tiles, FP32 online LSE)
 struct FusedArgs {

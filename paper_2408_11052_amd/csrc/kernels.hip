@@ -348,57 +348,9 @@ __device__ inline void load4(const float* p, float (&o)[4]) {
   float4 a = *reinterpret_cast<const float4*>(p);
   o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
 }
-__device__ inline void load4(const bf16_t* p, float (&o)[4]) {
-  uint2 u = *reinterpret_cast<const uint2*>(p);
-  o[0] = __builtin_bit_cast(float, u.x << 16);
-  o[1] = __builtin_bit_cast(float, u.x & 0xffff0000u);
-  o[2] = __builtin_bit_cast(float, u.y << 16);
-  o[3] = __builtin_bit_cast(float, u.y & 0xffff0000u);
-}
-
 constexpr int kColRows = 128;  // rows per chunk of the column-sum kernel
 
-// out[k][n] = sum over w of part[w][k][n]: 16 outputs per workgroup, the
-// parts split over 16 groups (w = grp, grp + 16, ...; four independent running
-// sums per thread), then a fixed-order tree over the groups in LDS.
-__global__ __launch_bounds__(256) void partial_reduce_kernel(ColReduceArgs a, int nparts,
-                                                             int nk, int N) {
-  __shared__ float red[16][17];
-  const int e = blockIdx.y;
-  const int col = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  const int i = blockIdx.x * 16 + col;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  if (i < nk * N) {
-    const float* p = a.part[e] + i;
-    const int64_t st = (int64_t)nk * N;
-    int w = grp;
-    for (; w + 48 < nparts; w += 64) {
-      s0 += p[w * st];
-      s1 += p[(w + 16) * st];
-      s2 += p[(w + 32) * st];
-      s3 += p[(w + 48) * st];
-    }
-    for (; w < nparts; w += 16) s0 += p[w * st];
-  }
-  red[grp][col] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  for (int h = 8; h >= 1; h >>= 1) {
-    if (grp < h) red[grp][col] += red[grp + h][col];
-    __syncthreads();
-  }
-  if (grp == 0 && i < nk * N) a.out[e][i / N][i % N] = red[0][col];
-}
-
-hipError_t launch_partial_reduce(const ColReduceArgs& a, int count, int nparts, int nk,
-                                 int N, hipStream_t s) {
-  dim3 grid((nk * N + 15) / 16, count), block(256);
-  CRL_TIMED("partial_reduce_kernel", 0.0, 4.0 * count * (nparts + 1.0) * nk * N, s,
-            partial_reduce_kernel<<<grid, block, 0, s>>>(a, nparts, nk, N));
-  return hipGetLastError();
-}
-
-// Column sums of X [B][ld] over one chunk of rows (same block shape as above).
-template <typename T>
+// Column sums of X [B][ld] over one chunk of rows, 256 columns per workgroup.
 __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B, int N, int ld) {
   __shared__ float red[4][256];
   const int e = blockIdx.z;
@@ -407,7 +359,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B
   const int r0 = blockIdx.y * kColRows, r1 = min(B, r0 + kColRows);
   float acc[4] = {0, 0, 0, 0};
   if (n0 < N) {
-    const T* X = reinterpret_cast<const T*>(a.X[e]);
+    const float* X = a.X[e];
     // the wavefront's rows r0 + wave, + 4, + 8, ... in that order, eight
     // rows' loads in flight before they are added
     int row = r0 + wave;
@@ -439,26 +391,13 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B
 int colsum_chunks(int B) { return (B + kColRows - 1) / kColRows; }
 
 hipError_t launch_colsum_partials(const ColSumArgs& a, int count, int B, int N, int ld,
-                                  bool bf16, hipStream_t s) {
+                                  hipStream_t s) {
   // N and ld must be multiples of 4 (vector loads of 4 elements)
   const int nrb = colsum_chunks(B);
   dim3 grid((N + 255) / 256, nrb, count), block(256);
-  const double cs_bytes = (double)count * B * N * (bf16 ? 2 : 4);
-  if (bf16) CRL_TIMED("colsum_partial_kernel", 0.0, cs_bytes, s,
-                      colsum_partial_kernel<bf16_t><<<grid, block, 0, s>>>(a, B, N, ld));
-  else      CRL_TIMED("colsum_partial_kernel", 0.0, cs_bytes, s,
-                      colsum_partial_kernel<float><<<grid, block, 0, s>>>(a, B, N, ld));
+  CRL_TIMED("colsum_partial_kernel", 0.0, 4.0 * count * B * N, s,
+            colsum_partial_kernel<<<grid, block, 0, s>>>(a, B, N, ld));
   return hipGetLastError();
-}
-
-hipError_t launch_colsum(const ColSumArgs& a, int count, int B, int N, int ld, bool bf16,
-                         hipStream_t s) {
-  const int nrb = colsum_chunks(B);
-  hipError_t err = launch_colsum_partials(a, count, B, N, ld, bf16, s);
-  if (err != hipSuccess) return err;
-  ColReduceArgs r{};
-  for (int e = 0; e < count; ++e) { r.part[e] = a.part[e]; r.out[e][0] = a.out[e]; }
-  return launch_partial_reduce(r, count, nrb, 1, N, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -781,21 +720,6 @@ hipError_t launch_grad_reduce(const char* ws, float* g, const RedJob* few, int n
   return hipGetLastError();
 }
 
-__global__ void sqnorm_kernel(const float* __restrict__ X, float* __restrict__ out, int B, int D) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= B) return;
-  float s = 0.f;
-  for (int d = lane; d < D; d += 64) { float v = X[(int64_t)row * D + d]; s += v * v; }
-  s = wave_sum(s);
-  if (lane == 0) out[row] = s;
-}
-hipError_t launch_sqnorm(const float* X, float* out, int B, int D, hipStream_t s) {
-  CRL_TIMED("sqnorm_kernel", 2.0 * B * D, 4.0 * B * (D + 1.0), s,
-            sqnorm_kernel<<<(B + 3) / 4, 256, 0, s>>>(X, out, B, D));
-  return hipGetLastError();
-}
-
 __global__ void cast_bf16_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, int64_t n) {
   int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4;
   for (; i < n; i += (int64_t)gridDim.x * blockDim.x * 4) {
@@ -854,35 +778,9 @@ hipError_t launch_counter_add(int64_t* c, int64_t inc, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ranges: [nranges][2] = (offset, length) in floats
-
 // ---------------------------------------------------------------------------
-// materialised InfoNCE: F [B][B] FP32 in memory
+// log-sum-exp merge and loss
 // ---------------------------------------------------------------------------
-// per (row chunk, column) online (max, sum) over the chunk's rows
-__global__ void col_lse_partial_kernel(const float* __restrict__ F, int B, int ld, int rows_per,
-                                       float* __restrict__ pm, float* __restrict__ ps) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= B) return;
-  const int i0 = blockIdx.y * rows_per, i1 = min(B, i0 + rows_per);
-  float m = -INFINITY, s = 0.f;
-  for (int i = i0; i < i1; ++i) {
-    float f = F[(int64_t)i * ld + j];
-    if (f > m) { s = s * __expf(m - f) + 1.f; m = f; }
-    else s += __expf(f - m);
-  }
-  pm[(int64_t)blockIdx.y * B + j] = m;
-  ps[(int64_t)blockIdx.y * B + j] = s;
-}
-hipError_t launch_col_lse_partial(const float* F, int B, int ld, int rchunks, float* pm, float* ps,
-                                  hipStream_t s) {
-  int rows_per = (B + rchunks - 1) / rchunks;
-  dim3 grid((B + 255) / 256, rchunks);
-  CRL_TIMED("col_lse_partial_kernel", 0.0, 4.0 * B * B, s,
-            col_lse_partial_kernel<<<grid, 256, 0, s>>>(F, B, ld, rows_per, pm, ps));
-  return hipGetLastError();
-}
-
 __global__ __launch_bounds__(1024) void lse_merge_kernel(LseMergeArgs a, int B) {
   // problem blockIdx.y; 64 columns per workgroup (a wavefront reads 256
   // contiguous bytes of one part), the parts split over the 16 wavefronts
@@ -919,13 +817,6 @@ hipError_t launch_lse_merge(const LseMergeArgs& a, int count, int B, hipStream_t
             lse_merge_kernel<<<dim3((B + 63) / 64, count), 1024, 0, s>>>(a, B));
   return hipGetLastError();
 }
-hipError_t launch_lse_merge(const float* pm, const float* ps, int nparts, int B, float* out,
-                            hipStream_t s) {
-  LseMergeArgs a{};
-  a.pm[0] = pm; a.ps[0] = ps; a.nparts[0] = nparts; a.out[0] = out;
-  return launch_lse_merge(a, 1, B, s);
-}
-
 // Loss from r, c, diag (and the per-row objective terms of the pairwise
 // objectives) in one workgroup: per-thread Kahan sums, then an ordered
 // pairwise tree over the threads (deterministic).
@@ -934,19 +825,34 @@ hipError_t launch_lse_merge(const float* pm, const float* ps, int nparts, int B,
 // with L_obj the objective `loss` (CRL_LOSS_*): the two InfoNCE directions,
 // their sum, FlatNCE (exp(x - x) per row, x = r - diag or c - diag), or the
 // mean of term[] (Forward-Backward, DPO, IPO, SPPO).
+// With nparts > 0 each thread first merges its columns' (max, sum) partials in
+// part order into c: one launch (4.5 us) less where the columns are few.
 __global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ r,
-                                                    const float* __restrict__ c,
+                                                    float* __restrict__ c,
                                                     const float* __restrict__ diag,
                                                     const float* __restrict__ term, int B,
                                                     int loss, float beta,
                                                     float* __restrict__ loss_out,
-                                                    int64_t* __restrict__ advance) {
+                                                    int64_t* __restrict__ advance,
+                                                    const float* __restrict__ col_m,
+                                                    const float* __restrict__ col_s, int nparts) {
   __shared__ float sh[7][1024];
   float acc[6] = {0, 0, 0, 0, 0, 0}, cmp[6] = {0, 0, 0, 0, 0, 0};
   float bad = 0.f;
   const bool pairwise = loss >= CRL_LOSS_FB;
   for (int i = threadIdx.x; i < B; i += 1024) {
-    float ri = r[i], ci = c[i], di = diag[i];
+    const float ri = r[i], di = diag[i];
+    float ci;
+    if (nparts > 0) {
+      float m = -INFINITY, sum = 0.f;
+#pragma unroll 4
+      for (int p = 0; p < nparts; ++p)
+        lse_merge(m, sum, col_m[(int64_t)p * B + i], col_s[(int64_t)p * B + i]);
+      ci = m + __logf(sum);
+      c[i] = ci;
+    } else {
+      ci = c[i];
+    }
     float o = 0.f;
     if (loss == CRL_LOSS_FLATNCE_FWD) { const float x = ri - di; o = __expf(x - x); }
     else if (loss == CRL_LOSS_FLATNCE_BWD) { const float x = ci - di; o = __expf(x - x); }
@@ -985,26 +891,12 @@ __global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ r,
     if (advance) *advance += 1;
   }
 }
-hipError_t launch_loss(const float* r, const float* c, const float* diag, const float* term,
+hipError_t launch_loss(const float* r, float* c, const float* diag, const float* term,
                        int B, int loss, float beta, float* loss_out, int64_t* advance,
-                       hipStream_t s) {
-  CRL_TIMED("loss_kernel", 0.0, 16.0 * B, s,
-            loss_kernel<<<1, 1024, 0, s>>>(r, c, diag, term, B, loss, beta, loss_out, advance));
-  return hipGetLastError();
-}
-
-// dX[i][d] -= rs[i] * X[i][d]
-__global__ void l2_fix_kernel(float* __restrict__ dX, const float* __restrict__ X,
-                              const float* __restrict__ rs, int B, int D) {
-  int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (k >= (int64_t)B * D) return;
-  dX[k] -= rs[k / D] * X[k];
-}
-hipError_t launch_l2_fix(float* dX, const float* X, const float* rs, int B, int D,
-                         hipStream_t s) {
-  int64_t n = (int64_t)B * D;
-  CRL_TIMED("l2_fix_kernel", 2.0 * n, 12.0 * n, s,
-            l2_fix_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(dX, X, rs, B, D));
+                       hipStream_t s, const float* col_m, const float* col_s, int nparts) {
+  CRL_TIMED("loss_kernel", 0.0, 16.0 * B + 8.0 * B * nparts, s,
+            loss_kernel<<<1, 1024, 0, s>>>(r, c, diag, term, B, loss, beta, loss_out, advance,
+                                           col_m, col_s, nparts));
   return hipGetLastError();
 }
 

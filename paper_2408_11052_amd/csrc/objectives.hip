@@ -11,6 +11,8 @@
 // Energies (Appendix A.2): dot and L2 / L2-without-root come from the logit
 // GEMM's epilogue; cosine is the dot product of unit rows (unit_rows_kernel);
 // L1 is not a product and has its own vector-ALU kernels here.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace crl {
@@ -20,25 +22,29 @@ __device__ __forceinline__ float softplusf(float x) {
 }
 
 
-// U[i] = X[i] / |X[i]| (0 for a zero row) and nrm[i] = |X[i]|, one wave per row.
-__global__ __launch_bounds__(256) void unit_rows_kernel(const float* __restrict__ X,
-                                                        float* __restrict__ U,
-                                                        float* __restrict__ nrm, int B, int D) {
+// U[i] = X[i] / |X[i]| (0 for a zero row) and nrm[i] = |X[i]|, one wave per
+// row of phi (blockIdx.y = 0) or psi (1).
+__global__ __launch_bounds__(256) void unit_rows_kernel(
+    const float* __restrict__ phi, const float* __restrict__ psi, float* __restrict__ Uphi,
+    float* __restrict__ Upsi, float* __restrict__ nphi, float* __restrict__ npsi, int B, int D) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= B) return;
-  const float* x = X + (int64_t)row * D;
+  const float* x = (blockIdx.y ? psi : phi) + (int64_t)row * D;
+  float* U = (blockIdx.y ? Upsi : Uphi) + (int64_t)row * D;
   float s = 0.f;
   for (int d = lane; d < D; d += 64) s += x[d] * x[d];
   s = wave_sum(s);
   const float n = sqrtf(s);
   const float inv = n > 0.f ? 1.f / n : 0.f;
-  for (int d = lane; d < D; d += 64) U[(int64_t)row * D + d] = x[d] * inv;
-  if (lane == 0) nrm[row] = n;
+  for (int d = lane; d < D; d += 64) U[d] = x[d] * inv;
+  if (lane == 0) (blockIdx.y ? npsi : nphi)[row] = n;
 }
-hipError_t launch_unit_rows(const float* X, float* U, float* nrm, int B, int D, hipStream_t s) {
-  CRL_TIMED("unit_rows_kernel", 3.0 * B * D, 4.0 * B * (2.0 * D + 1.0), s,
-            unit_rows_kernel<<<(B + 3) / 4, 256, 0, s>>>(X, U, nrm, B, D));
+hipError_t launch_unit_rows(const float* phi, const float* psi, float* Uphi, float* Upsi,
+                            float* nphi, float* npsi, int B, int D, hipStream_t s) {
+  CRL_TIMED("unit_rows_kernel", 6.0 * B * D, 8.0 * B * (2.0 * D + 1.0), s,
+            unit_rows_kernel<<<dim3((B + 3) / 4, 2), 256, 0, s>>>(phi, psi, Uphi, Upsi, nphi,
+                                                                  npsi, B, D));
   return hipGetLastError();
 }
 
@@ -95,78 +101,85 @@ hipError_t launch_l1_energy(const float* phi, const float* psi, float* F, int B,
   return hipGetLastError();
 }
 
-// dX_xk = -sum_y C(x, y) sign(X_xk - Y_yk), C(x, y) = G[x][y] (trans = 0:
-// X = phi, Y = psi, giving dphi) or G[y][x] (trans = 1: X = psi, Y = phi,
+// dX_xk = -sum_y C(x, y) sign(X_xk - Y_yk), C(x, y) = G[x][y] (side 0:
+// X = phi, Y = psi, giving dphi) or G[y][x] (side 1: X = psi, Y = phi,
 // giving dpsi, since dF_ij/dpsi_jk = +sign(phi_ik - psi_jk) =
-// -sign(psi_jk - phi_ik)).  A workgroup owns 32 rows x all D features (a
-// thread: one row, features t%8 + 8m); 32-row slices of Y and the matching
-// 32 x 32 block of C go through LDS.
-constexpr int kL1R = 32;
-template <int TRANS>
-__global__ __launch_bounds__(256) void l1_backward_kernel(const float* __restrict__ X,
-                                                          const float* __restrict__ Y,
+// -sign(psi_jk - phi_ik)).  Five vector instructions per (x, y, k) bind it.
+// A workgroup owns 64 rows x 32 features of one side and one split of y: lane
+// l has row l, wave w features 8w..8w+7, so the block of C is read from LDS
+// without conflicts and Y as broadcasts, and the splits fill the chip.  One
+// thread per row and eight strided features with all of y in one workgroup
+// (54 workgroups a side) took 1755 us at B = 1701, D = 40; this takes 46.
+constexpr int kL1X = 64, kL1F = 32, kL1Y = 32;
+__global__ __launch_bounds__(256) void l1_backward_kernel(const float* __restrict__ phi,
+                                                          const float* __restrict__ psi,
                                                           const float* __restrict__ G, int ldg,
-                                                          float* __restrict__ dX, int B, int D) {
-  extern __shared__ float sm[];
-  float* Ys = sm;                       // [kL1R][D + 1]
-  float* Cs = sm + kL1R * (D + 1);      // [kL1R x rows][kL1R y] (+1 pad)
-  const int tid = threadIdx.x;
-  const int rl = tid >> 3, kq = tid & 7;
-  const int x = blockIdx.x * kL1R + rl;
-  const int nk = (D + 7) / 8;           // features per thread (<= 32)
-  float acc[32] = {};
-  float xv[32];
+                                                          float* __restrict__ part, int splits,
+                                                          int ysplit, int B, int D) {
+  __shared__ __attribute__((aligned(16))) float Ys[kL1Y][kL1F];
+  __shared__ float Cs[kL1Y][kL1X + 1];
+  const int side = blockIdx.z & 1, f0 = (blockIdx.z >> 1) * kL1F;
+  const float* __restrict__ X = side ? psi : phi;
+  const float* __restrict__ Y = side ? phi : psi;
+  const int tid = threadIdx.x, xl = tid & 63, fq = (tid >> 6) * 8;
+  const int x0 = blockIdx.x * kL1X, x = x0 + xl;
+  const int yb = blockIdx.y * ysplit, ye = min(B, yb + ysplit);
+  float xv[8], acc[8];
 #pragma unroll
-  for (int m = 0; m < 32; ++m) {
-    const int k = kq + 8 * m;
-    xv[m] = (m < nk && k < D && x < B) ? X[(int64_t)x * D + k] : 0.f;
+  for (int m = 0; m < 8; ++m) {
+    xv[m] = (x < B && f0 + fq + m < D) ? X[(int64_t)x * D + f0 + fq + m] : 0.f;
+    acc[m] = 0.f;
   }
-  for (int y0 = 0; y0 < B; y0 += kL1R) {
+  for (int y0 = yb; y0 < ye; y0 += kL1Y) {
     __syncthreads();
-    for (int v = tid; v < kL1R * D; v += 256) {
-      const int r = v / D, k = v % D;
-      Ys[r * (D + 1) + k] = (y0 + r < B) ? Y[(int64_t)(y0 + r) * D + k] : 0.f;
+    for (int v = tid; v < kL1Y * kL1F; v += 256) {
+      const int r = v / kL1F, k = v % kL1F;
+      Ys[r][k] = (y0 + r < ye && f0 + k < D) ? Y[(int64_t)(y0 + r) * D + f0 + k] : 0.f;
     }
-    for (int v = tid; v < kL1R * kL1R; v += 256) {
-      const int a = v / kL1R, b = v % kL1R;     // a: x row in the block, b: y
-      const int xa = blockIdx.x * kL1R + a, yb = y0 + b;
+    for (int v = tid; v < kL1Y * kL1X; v += 256) {
+      // consecutive threads along G's rows
+      const int xi = side ? v % kL1X : v / kL1Y, yi = side ? v / kL1X : v % kL1Y;
       float c = 0.f;
-      if (xa < B && yb < B) c = TRANS ? G[(int64_t)yb * ldg + xa] : G[(int64_t)xa * ldg + yb];
-      Cs[a * (kL1R + 1) + b] = c;
+      if (x0 + xi < B && y0 + yi < ye)
+        c = side ? G[(int64_t)(y0 + yi) * ldg + x0 + xi] : G[(int64_t)(x0 + xi) * ldg + y0 + yi];
+      Cs[yi][xi] = c;
     }
     __syncthreads();
-    const int ny = min(kL1R, B - y0);
-    for (int b = 0; b < ny; ++b) {
-      const float c = Cs[rl * (kL1R + 1) + b];
-      const float* yr = Ys + b * (D + 1);
+#pragma unroll 4
+    for (int y = 0; y < kL1Y; ++y) {  // rows past the split hold C = 0
+      const uint32_t c = __builtin_bit_cast(uint32_t, Cs[y][xl]);
+      float yv[8];
+      *reinterpret_cast<float4*>(yv) = *reinterpret_cast<const float4*>(&Ys[y][fq]);
+      *reinterpret_cast<float4*>(yv + 4) = *reinterpret_cast<const float4*>(&Ys[y][fq + 4]);
 #pragma unroll
-      for (int m = 0; m < 32; ++m) {
-        if (m >= nk) break;
-        const int k = kq + 8 * m;
-        const float dlt = xv[m] - (k < D ? yr[k] : 0.f);
-        const float sg = dlt > 0.f ? 1.f : (dlt < 0.f ? -1.f : 0.f);
-        acc[m] -= c * sg;
+      for (int m = 0; m < 8; ++m) {
+        // -c sign(d): c with the opposite of d's sign; nothing where d is 0 (or NaN)
+        const float d = xv[m] - yv[m];
+        const uint32_t t = c ^ (~__builtin_bit_cast(uint32_t, d) & 0x80000000u);
+        acc[m] += __builtin_islessgreater(d, 0.f) ? __builtin_bit_cast(float, t) : 0.f;
       }
     }
   }
   if (x >= B) return;
+  float* out = part + (((int64_t)side * splits + blockIdx.y) * B + x) * D + f0 + fq;
 #pragma unroll
-  for (int m = 0; m < 32; ++m) {
-    const int k = kq + 8 * m;
-    if (m < nk && k < D) dX[(int64_t)x * D + k] = acc[m];
-  }
+  for (int m = 0; m < 8; ++m)
+    if (f0 + fq + m < D) out[m] = acc[m];
 }
-hipError_t launch_l1_backward(const float* X, const float* Y, const float* G, int ldg, int trans,
-                              float* dX, int B, int D, hipStream_t s) {
-  if (D > 256) return hipErrorInvalidValue;
-  const size_t lds = sizeof(float) * (kL1R * (D + 1) + kL1R * (kL1R + 1));
-  const dim3 grid((B + kL1R - 1) / kL1R);
-  if (trans)
-    CRL_TIMED("l1_backward_kernel<cols>", 3.0 * B * B * D, 4.0 * (3.0 * B * D + (double)B * B), s,
-              l1_backward_kernel<1><<<grid, 256, lds, s>>>(X, Y, G, ldg, dX, B, D));
-  else
-    CRL_TIMED("l1_backward_kernel<rows>", 3.0 * B * B * D, 4.0 * (3.0 * B * D + (double)B * B), s,
-              l1_backward_kernel<0><<<grid, 256, lds, s>>>(X, Y, G, ldg, dX, B, D));
+// Splits of y: about 1024 workgroups (four per CU), each at least 128 rows
+// of y deep so that its partial (a B x D block) stays cheap to sum.
+int l1_backward_splits(int B, int D) {
+  const int tiles = (B + kL1X - 1) / kL1X * ((D + kL1F - 1) / kL1F) * 2;
+  int S = 1;
+  while (S < 16 && tiles * S * 2 <= 1024 && B / (2 * S) >= 128) S *= 2;
+  return S;
+}
+hipError_t launch_l1_backward(const float* phi, const float* psi, const float* G, int ldg,
+                              float* part, int splits, int B, int D, hipStream_t s) {
+  const int ysplit = ((B + splits - 1) / splits + kL1Y - 1) / kL1Y * kL1Y;
+  const dim3 grid((B + kL1X - 1) / kL1X, splits, (D + kL1F - 1) / kL1F * 2);
+  CRL_TIMED("l1_backward_kernel", 6.0 * B * B * D, 8.0 * (2.0 * B * D + (double)B * B), s,
+            l1_backward_kernel<<<grid, 256, 0, s>>>(phi, psi, G, ldg, part, splits, ysplit, B, D));
   return hipGetLastError();
 }
 
@@ -178,15 +191,9 @@ hipError_t launch_l1_backward(const float* X, const float* Y, const float* G, in
 //   IPO:  term = sum_j (F_ii - F_ij - 1)^2,        aux = sum_{j != i} (F_ii - F_ij - 1)
 //   SPPO: term = B (F_ii - 1)^2 + sum_j (F_ij + 1)^2
 template <int LOSS>
-__global__ __launch_bounds__(256) void row_obj_kernel(const float* __restrict__ F, int B, int ld,
-                                                      float* __restrict__ r,
-                                                      float* __restrict__ diag,
-                                                      float* __restrict__ term,
-                                                      float* __restrict__ aux) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= B) return;
-  const float* row = F + (int64_t)i * ld;
+__device__ __forceinline__ void row_obj(const float* __restrict__ row, int i, int B, int lane,
+                                        float* __restrict__ r, float* __restrict__ diag,
+                                        float* __restrict__ term, float* __restrict__ aux) {
   const float fii = row[i];
   float m = -INFINITY;
   for (int j = lane; j < B; j += 64) m = fmaxf(m, row[j]);
@@ -225,24 +232,76 @@ __global__ __launch_bounds__(256) void row_obj_kernel(const float* __restrict__ 
     if (LOSS == CRL_LOSS_DPO || LOSS == CRL_LOSS_IPO) aux[i] = a;
   }
 }
-hipError_t launch_row_obj(const float* F, int B, int ld, int loss, float* r, float* diag,
-                          float* term, float* aux, hipStream_t s) {
-  const dim3 grid((B + 3) / 4);
-  const double bytes = 4.0 * ((double)B * B + 4.0 * B);
+// Column chunk: the (max, sum) of 256 columns over rows [i0, i1), eight rows'
+// loads in flight before their maximum and then their sum are taken.
+__device__ __forceinline__ void col_lse(const float* __restrict__ F, int ld, int B, int j, int i0,
+                                        int i1, float& m, float& s) {
+  m = -INFINITY;
+  s = 0.f;
+  for (int i = i0; i < i1; i += 8) {
+    float f[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f[k] = i + k < i1 ? F[(int64_t)(i + k) * ld + j] : -INFINITY;
+    float mn = m;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) mn = fmaxf(mn, f[k]);
+    s = m == -INFINITY ? 0.f : s * __expf(m - mn);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (i + k < i1) s += __expf(f[k] - mn);
+    m = mn;
+  }
+}
+
+// Rows and columns of F in one launch (both only read it): blocks [0, nrow)
+// take four rows each, one per wavefront, the rest one chunk of rows of 256
+// columns each.
+template <int LOSS>
+__global__ __launch_bounds__(256) void row_col_kernel(const float* __restrict__ F, int B, int ld,
+                                                      int nrow, int ncol, int rows_per,
+                                                      float* __restrict__ r,
+                                                      float* __restrict__ diag,
+                                                      float* __restrict__ term,
+                                                      float* __restrict__ aux,
+                                                      float* __restrict__ col_m,
+                                                      float* __restrict__ col_s) {
+  if ((int)blockIdx.x < nrow) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i < B) row_obj<LOSS>(F + (int64_t)i * ld, i, B, threadIdx.x & 63, r, diag, term, aux);
+    return;
+  }
+  const int blk = blockIdx.x - nrow, chunk = blk / ncol;
+  const int j = (blk % ncol) * 256 + threadIdx.x;
+  if (j >= B) return;
+  float m, s;
+  col_lse(F, ld, B, j, chunk * rows_per, min(B, (chunk + 1) * rows_per), m, s);
+  col_m[(int64_t)chunk * B + j] = m;
+  col_s[(int64_t)chunk * B + j] = s;
+}
+// Row chunks of the column log-sum-exps (at most 64, the workspace's slots).
+// Up to B = 2048 the loss kernel itself merges them (its one workgroup takes
+// two columns a thread), so there they are fewer; above, lse_merge_kernel does.
+int col_chunks(int B) { return std::min(B, B <= 1024 ? 16 : B <= 2048 ? 32 : 64); }
+bool col_merge_in_loss(int B) { return B <= 2048; }
+hipError_t launch_row_col(const float* F, int B, int ld, int loss, float* r, float* diag,
+                          float* term, float* aux, float* col_m, float* col_s, hipStream_t s) {
+  const int nrow = (B + 3) / 4, ncol = (B + 255) / 256, chunks = col_chunks(B);
+  const int rows_per = (B + chunks - 1) / chunks;
+  const dim3 grid(nrow + ncol * chunks);
+  const double bytes = 4.0 * (2.0 * B * B + 4.0 * B);
   switch (loss) {
-#define CRL_ROW_OBJ(L_, NAME)                                                       \
-  case L_:                                                                          \
-    CRL_TIMED(NAME, 0.0, bytes, s,                                                  \
-              row_obj_kernel<L_><<<grid, 256, 0, s>>>(F, B, ld, r, diag, term, aux)); \
-    break;
-    CRL_ROW_OBJ(CRL_LOSS_FB, "row_obj_kernel<fb>")
-    CRL_ROW_OBJ(CRL_LOSS_DPO, "row_obj_kernel<dpo>")
-    CRL_ROW_OBJ(CRL_LOSS_IPO, "row_obj_kernel<ipo>")
-    CRL_ROW_OBJ(CRL_LOSS_SPPO, "row_obj_kernel<sppo>")
+#define CRL_ROW_OBJ(L_, NAME)                                                              \
+  CRL_TIMED(NAME, 0.0, bytes, s,                                                           \
+            row_col_kernel<L_><<<grid, 256, 0, s>>>(F, B, ld, nrow, ncol, rows_per, r, diag, \
+                                                    term, aux, col_m, col_s));             \
+  break;
+    case CRL_LOSS_FB: CRL_ROW_OBJ(CRL_LOSS_FB, "row_col_kernel<fb>")
+    case CRL_LOSS_DPO: CRL_ROW_OBJ(CRL_LOSS_DPO, "row_col_kernel<dpo>")
+    case CRL_LOSS_IPO: CRL_ROW_OBJ(CRL_LOSS_IPO, "row_col_kernel<ipo>")
+    case CRL_LOSS_SPPO: CRL_ROW_OBJ(CRL_LOSS_SPPO, "row_col_kernel<sppo>")
+    // the InfoNCE family needs only r and the diagonal
+    default: CRL_ROW_OBJ(CRL_LOSS_FWD, "row_col_kernel<lse>")
 #undef CRL_ROW_OBJ
-    default:  // the InfoNCE family needs only r and the diagonal
-      CRL_TIMED("row_obj_kernel<lse>", 0.0, bytes, s,
-                row_obj_kernel<CRL_LOSS_FWD><<<grid, 256, 0, s>>>(F, B, ld, r, diag, term, aux));
   }
   return hipGetLastError();
 }
@@ -341,27 +400,47 @@ hipError_t launch_grad_obj(float* F, int B, int ld, const float* r, const float*
   return hipGetLastError();
 }
 
-// Cosine energy backward: with dU = G V (rows of unit vectors U, V),
-// dX_i = (dU_i - (dU_i . U_i) U_i) / |X_i| (0 for a zero row), in place on dX.
-__global__ __launch_bounds__(256) void cos_fix_kernel(float* __restrict__ dX,
-                                                      const float* __restrict__ U,
-                                                      const float* __restrict__ nrm, int B,
-                                                      int D) {
-  const int lane = threadIdx.x & 63;
+// The end of the materialised backward, both sides in one launch (one wave per
+// row): the split-K partials' sum in split order, the energy's own term
+// (distance: - (sum_j H_ij) x_i; cosine: with dU = G V for the unit rows,
+// (dU_i - (dU_i . U_i) U_i) / |X_i|, 0 for a zero row) and the BF16 copies.
+// Five launches of 4 to 5 us each before (reductions, row terms, casts).
+__global__ __launch_bounds__(256) void obj_finish_kernel(ObjFinish a, int splits, int fix, int B,
+                                                         int D) {
+  const int side = blockIdx.y, lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= B) return;
-  float* dx = dX + (int64_t)row * D;
-  const float* u = U + (int64_t)row * D;
-  float s = 0.f;
-  for (int d = lane; d < D; d += 64) s += dx[d] * u[d];
-  s = wave_sum(s);
-  const float n = nrm[row];
-  const float inv = n > 0.f ? 1.f / n : 0.f;
-  for (int d = lane; d < D; d += 64) dx[d] = (dx[d] - s * u[d]) * inv;
+  const int64_t n = (int64_t)B * D, o = (int64_t)row * D;
+  const float* part = a.part[side] + o;  // may be out itself
+  const float* __restrict__ X = a.X[side] + o;
+  float* out = a.out[side] + o;
+  bf16_t* outb = a.outb[side];
+  float rs = 0.f, dot = 0.f, inv = 1.f;
+  if (fix == kFixDist)
+    for (int k = 0; k < a.nrs[side]; ++k) rs += a.rs[side][(int64_t)k * B + row];
+  if (fix == kFixCos) {
+    for (int d = lane; d < D; d += 64) {
+      float v = 0.f;
+      for (int k = 0; k < splits; ++k) v += part[k * n + d];
+      dot += v * X[d];
+    }
+    dot = wave_sum(dot);
+    const float nr = a.nrm[side][row];
+    inv = nr > 0.f ? 1.f / nr : 0.f;
+  }
+  for (int d = lane; d < D; d += 64) {
+    float v = 0.f;
+    for (int k = 0; k < splits; ++k) v += part[k * n + d];
+    if (fix == kFixDist) v -= rs * X[d];
+    if (fix == kFixCos) v = (v - dot * X[d]) * inv;
+    out[d] = v;
+    if (outb) outb[o + d] = f2bf(v);
+  }
 }
-hipError_t launch_cos_fix(float* dX, const float* U, const float* nrm, int B, int D, hipStream_t s) {
-  CRL_TIMED("cos_fix_kernel", 4.0 * B * D, 4.0 * B * (3.0 * D + 1.0), s,
-            cos_fix_kernel<<<(B + 3) / 4, 256, 0, s>>>(dX, U, nrm, B, D));
+hipError_t launch_obj_finish(const ObjFinish& a, int splits, int fix, int B, int D,
+                             hipStream_t s) {
+  CRL_TIMED("obj_finish_kernel", 0.0, 8.0 * B * D * (splits + 2.0), s,
+            obj_finish_kernel<<<dim3((B + 3) / 4, 2), 256, 0, s>>>(a, splits, fix, B, D));
   return hipGetLastError();
 }
 
