@@ -37,6 +37,33 @@ __device__ inline float box_muller(uint64_t seed, uint64_t b, uint64_t n, int k)
   return r * ((k & 1) ? sn : cs);
 }
 
+// Element i of a GEMM result: stored, or its split-K partials in split order
+// plus the bias, as the split-K reduction writes them.  (Three reduction
+// launches of 4.7 us a policy step before.)
+struct Summed {
+  const float* part;  // NULL: final
+  int64_t stride;
+  int splits;
+  const float* bias;
+};
+__device__ __forceinline__ float summed(const Summed& p, const float* final_, int64_t i, int col) {
+  if (!p.part) return *final_;
+  float s = 0.f;
+  for (int k = 0; k < p.splits; ++k) s += p.part[k * p.stride + i];
+  return p.bias ? s + p.bias[col] : s;
+}
+Summed summed_of(const GemmParams& P, int g) {
+  Summed p{};
+  if (P.splits > 1) {
+    const GemmDesc& d = P.d[g];
+    p.part = P.partial + (int64_t)g * P.partial_len;
+    p.stride = (int64_t)d.M * d.N;
+    p.splits = P.splits;
+    p.bias = d.epi == EPI_BIAS ? d.bias : nullptr;
+  }
+  return p;
+}
+
 }  // namespace
 
 // One wavefront per sample.  From the policy output o = [mu | rho | pad]:
@@ -45,19 +72,24 @@ __device__ inline float box_muller(uint64_t seed, uint64_t b, uint64_t n, int k)
 // Writes the critic input [s, a] (state columns copied from x_sa), eps and log pi.
 template <typename T>
 __global__ __launch_bounds__(256) void actor_head_fwd_kernel(
-    const float* __restrict__ out, int ldo, int A, uint64_t seed,
+    float* out, Summed top, int ldo, int A, uint64_t seed,
     const int64_t* __restrict__ step, const T* __restrict__ x_sa, T* __restrict__ x_sa2,
     int ld, int d_s, float* __restrict__ eps, float* __restrict__ logpi, int B) {
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
   const uint64_t n = (uint64_t)(*step);
-  const float* o = out + (int64_t)b * ldo;
+  float* o = out + (int64_t)b * ldo;
   T* row2 = x_sa2 + (int64_t)b * ld;
   float lp = 0.f;
   for (int k = lane; k < A; k += 64) {
     const float z = box_muller(seed, (uint64_t)b, n, k);
-    const float mu = o[k], rho = o[A + k];
+    const float mu = summed(top, o + k, (int64_t)b * ldo + k, k);
+    const float rho = summed(top, o + A + k, (int64_t)b * ldo + A + k, A + k);
+    if (top.part) {
+      o[k] = mu;
+      o[A + k] = rho;
+    }
     const float sigma = softplusf_(rho) + kSigmaMin;
     const float u = fmaf(sigma, z, mu);
     const float a = tanhf(u);
@@ -66,6 +98,8 @@ __global__ __launch_bounds__(256) void actor_head_fwd_kernel(
     eps[(int64_t)b * A + k] = z;
     row2[d_s + k] = Store<T>::from_f(a);
   }
+  if (top.part)
+    for (int k = 2 * A + lane; k < ldo; k += 64) o[k] = summed(top, o + k, (int64_t)b * ldo + k, k);
   const T* row = x_sa + (int64_t)b * ld;
   for (int c = lane; c < ld; c += 64) {
     if (c < d_s) row2[c] = row[c];
@@ -84,18 +118,23 @@ __global__ __launch_bounds__(256) void actor_head_fwd_kernel(
 //   L1    f = -sum |p - q|              -> sign(p - q) / B
 template <typename T>
 __global__ __launch_bounds__(256) void actor_energy_kernel(
-    const float* __restrict__ phi, const float* __restrict__ psi, int D, int energy,
-    float* __restrict__ f, T* __restrict__ dphi, int B) {
+    float* phi, float* psi, Summed tp, Summed tq, int D, int energy, float* __restrict__ f,
+    T* __restrict__ dphi, int B) {
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
-  const float* p = phi + (int64_t)b * D;
-  const float* q = psi + (int64_t)b * D;
+  float* p = phi + (int64_t)b * D;
+  float* q = psi + (int64_t)b * D;
   T* d = dphi + (int64_t)b * D;
   const float invB = 1.f / (float)B;
   float pq = 0.f, pp = 0.f, qq = 0.f, dd = 0.f, l1 = 0.f;
   for (int k = lane; k < D; k += 64) {
-    const float x = p[k], y = q[k];
+    const float x = summed(tp, p + k, (int64_t)b * D + k, k);
+    const float y = summed(tq, q + k, (int64_t)b * D + k, k);
+    if (tp.part) {  // read back below by the lane that writes them
+      p[k] = x;
+      q[k] = y;
+    }
     pq += x * y;
     pp += x * x;
     qq += y * y;
@@ -142,8 +181,8 @@ __global__ __launch_bounds__(256) void actor_energy_kernel(
 template <typename T>
 __global__ __launch_bounds__(256) void actor_head_bwd_kernel(
     const float* __restrict__ out, int ldo, int A, const float* __restrict__ eps,
-    const float* __restrict__ da, int ldd, const float* __restrict__ log_alpha,
-    float* dout, T* dout_t, int B) {  // dout_t may alias dout (FP32)
+    float* da, Summed dx, int ldd, const float* __restrict__ log_alpha, float* dout, T* dout_t,
+    int B) {  // dout_t may alias dout (FP32)
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
@@ -156,7 +195,10 @@ __global__ __launch_bounds__(256) void actor_head_bwd_kernel(
     const float mu = o[k], rho = o[A + k];
     const float sigma = softplusf_(rho) + kSigmaMin;
     const float t = tanhf(fmaf(sigma, z, mu));
-    const float gu = 2.f * c * t + da[(int64_t)b * ldd + k] * (1.f - t * t);
+    float* dak = da + (int64_t)b * ldd + k;
+    const float dv = summed(dx, dak, (int64_t)b * A + k, k);
+    if (dx.part) *dak = dv;
+    const float gu = 2.f * c * t + dv * (1.f - t * t);
     const float gr = (gu * z - c / sigma) / (1.f + expf(-rho));
     g[k] = gu;
     g[A + k] = gr;
@@ -169,41 +211,7 @@ __global__ __launch_bounds__(256) void actor_head_bwd_kernel(
   }
 }
 
-// loss_out = {L_pi, mean log pi, L_alpha, mean f}; *alpha_grad = dL_alpha/dlog alpha.
-//   L_pi = alpha mean(log pi) - mean(f),  L_alpha = -log alpha (mean(log pi) + H)
-// Per-thread Kahan sums, then an ordered tree over the workgroup.
-__global__ __launch_bounds__(1024) void actor_loss_kernel(
-    const float* __restrict__ logpi, const float* __restrict__ f, int B,
-    const float* __restrict__ log_alpha, float target_entropy, float* __restrict__ loss_out,
-    float* __restrict__ alpha_grad) {
-  __shared__ float sh[2][1024];
-  float s0 = 0.f, c0 = 0.f, s1 = 0.f, c1 = 0.f;
-  for (int i = threadIdx.x; i < B; i += 1024) {
-    kahan_add(s0, c0, logpi[i]);
-    kahan_add(s1, c1, f[i]);
-  }
-  sh[0][threadIdx.x] = s0 - c0;
-  sh[1][threadIdx.x] = s1 - c1;
-  __syncthreads();
-  for (int w = 512; w >= 1; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-      sh[1][threadIdx.x] += sh[1][threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const float la = *log_alpha;
-    const float mlp = sh[0][0] / (float)B, mf = sh[1][0] / (float)B;
-    loss_out[0] = expf(la) * mlp - mf;
-    loss_out[1] = mlp;
-    loss_out[2] = -la * (mlp + target_entropy);
-    loss_out[3] = mf;
-    *alpha_grad = -(mlp + target_entropy);
-  }
-}
-
-hipError_t launch_actor_head_fwd(const float* out, int ldo, int A, uint64_t seed,
+hipError_t launch_actor_head_fwd(float* out, const GemmParams& top, int ldo, int A, uint64_t seed,
                                  const int64_t* step, const void* x_sa, void* x_sa2, int ld,
                                  int d_s, float* eps, float* logpi, int B, bool bf16,
                                  hipStream_t s) {
@@ -212,40 +220,42 @@ hipError_t launch_actor_head_fwd(const float* out, int ldo, int A, uint64_t seed
   const double bytes = (double)B * (8.0 * A + es * (d_s + ld) + 4.0 * A + 4.0);
   if (bf16)
     CRL_TIMED("actor_head_fwd_kernel", 0.0, bytes, s,
-      actor_head_fwd_kernel<bf16_t><<<grid, block, 0, s>>>(out, ldo, A, seed, step,
+      actor_head_fwd_kernel<bf16_t><<<grid, block, 0, s>>>(out, summed_of(top, 0), ldo, A, seed, step,
         (const bf16_t*)x_sa, (bf16_t*)x_sa2, ld, d_s, eps, logpi, B));
   else
     CRL_TIMED("actor_head_fwd_kernel", 0.0, bytes, s,
-      actor_head_fwd_kernel<float><<<grid, block, 0, s>>>(out, ldo, A, seed, step,
+      actor_head_fwd_kernel<float><<<grid, block, 0, s>>>(out, summed_of(top, 0), ldo, A, seed, step,
         (const float*)x_sa, (float*)x_sa2, ld, d_s, eps, logpi, B));
   return hipGetLastError();
 }
 
-hipError_t launch_actor_energy(const float* phi, const float* psi, int D, int energy, float* f,
-                               void* dphi, int B, bool bf16, hipStream_t s) {
+hipError_t launch_actor_energy(float* phi, float* psi, const GemmParams& top, int D, int energy,
+                               float* f, void* dphi, int B, bool bf16, hipStream_t s) {
+  const Summed tp = summed_of(top, 0), tq = summed_of(top, 1);
   dim3 grid((B + 3) / 4), block(256);
   const double bytes = (double)B * (8.0 * D + (bf16 ? 2.0 : 4.0) * D + 4.0);
   if (bf16)
     CRL_TIMED("actor_energy_kernel", 2.0 * B * D, bytes, s,
-      actor_energy_kernel<bf16_t><<<grid, block, 0, s>>>(phi, psi, D, energy, f, (bf16_t*)dphi, B));
+      actor_energy_kernel<bf16_t><<<grid, block, 0, s>>>(phi, psi, tp, tq, D, energy, f, (bf16_t*)dphi, B));
   else
     CRL_TIMED("actor_energy_kernel", 2.0 * B * D, bytes, s,
-      actor_energy_kernel<float><<<grid, block, 0, s>>>(phi, psi, D, energy, f, (float*)dphi, B));
+      actor_energy_kernel<float><<<grid, block, 0, s>>>(phi, psi, tp, tq, D, energy, f, (float*)dphi, B));
   return hipGetLastError();
 }
 
 hipError_t launch_actor_head_bwd(const float* out, int ldo, int A, const float* eps,
-                                 const float* da, int ldd, const float* log_alpha, float* dout,
-                                 void* dout_t, int B, bool bf16, hipStream_t s) {
+                                 float* da, int ldd, const GemmParams& dx, const float* log_alpha,
+                                 float* dout, void* dout_t, int B, bool bf16, hipStream_t s) {
+  const Summed sx = summed_of(dx, 0);
   dim3 grid((B + 3) / 4), block(256);
   const double bytes = (double)B * (8.0 * A + 8.0 * A + (4.0 + (bf16 ? 2.0 : 4.0)) * ldo);
   if (bf16)
     CRL_TIMED("actor_head_bwd_kernel", 0.0, bytes, s,
-      actor_head_bwd_kernel<bf16_t><<<grid, block, 0, s>>>(out, ldo, A, eps, da, ldd, log_alpha,
+      actor_head_bwd_kernel<bf16_t><<<grid, block, 0, s>>>(out, ldo, A, eps, da, sx, ldd, log_alpha,
                                                            dout, (bf16_t*)dout_t, B));
   else
     CRL_TIMED("actor_head_bwd_kernel", 0.0, bytes, s,
-      actor_head_bwd_kernel<float><<<grid, block, 0, s>>>(out, ldo, A, eps, da, ldd, log_alpha,
+      actor_head_bwd_kernel<float><<<grid, block, 0, s>>>(out, ldo, A, eps, da, sx, ldd, log_alpha,
                                                           dout, (float*)dout_t, B));
   return hipGetLastError();
 }
@@ -294,15 +304,6 @@ hipError_t launch_goal_mix(const void* x_g, int ld_g, const void* x_sg, int ld_s
       goal_mix_kernel<float><<<grid, block, 0, s>>>((const float*)x_g, ld_g,
         (const float*)x_sg, ld_sg, d_s, d_g, seed, step, thr53, B, (float*)xg_out,
         (float*)xsg_out));
-  return hipGetLastError();
-}
-
-hipError_t launch_actor_loss(const float* logpi, const float* f, int B, const float* log_alpha,
-                             float target_entropy, float* loss_out, float* alpha_grad,
-                             hipStream_t s) {
-  CRL_TIMED("actor_loss_kernel", 0.0, 8.0 * B, s,
-            actor_loss_kernel<<<1, 1024, 0, s>>>(logpi, f, B, log_alpha, target_entropy,
-                                                 loss_out, alpha_grad));
   return hipGetLastError();
 }
 

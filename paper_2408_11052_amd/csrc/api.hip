@@ -144,7 +144,7 @@ struct crl_ctx {
   int64_t xg_mix, xsg_mix;                 // random-goal inputs of the actor step, or -1
   uint64_t mix_thr;                        // floor(random_goal_ratio * 2^53)
   int ldd;                                 // row stride of dact
-  int ln_rows_per_wave, ln_nparts, rchunks;
+  int ln_nparts, rchunks;
   int ldF;                     // row stride of the materialised logits
   LossWs na;                   // the loss forward packed from offset 0 (no-alloc entry point)
   int64_t na_bytes;            // bytes that layout needs
@@ -538,8 +538,7 @@ void plan_workspace(crl_ctx* x) {
   auto take = [&](int64_t bytes) { return take_bytes(x, off, bytes); };
   const int64_t B = x->B, D = x->D;
   x->ldF = x->fused ? 0 : (int)align_up(B, 8);
-  x->ln_rows_per_wave = 16;
-  x->ln_nparts = ln_bwd_partials(x->B, x->ln_rows_per_wave);
+  x->ln_nparts = ln_bwd_partials(x->B);
   for (int e = 0; e < (x->actor ? 3 : 2); ++e) plan_slots(x, e, take_bytes, off);
   x->grp[0].nets[0] = 0; x->grp[0].nets[1] = 1; x->grp[0].count = 2;
   x->grp[1].nets[0] = 2; x->grp[1].nets[1] = 2; x->grp[1].count = 1;
@@ -747,9 +746,12 @@ int mlp_forward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t 
 // Backward of `count` MLPs from the output gradients in their dout / dout_t
 // slots, last layer first.  With a gradient vector: dW, bias and LayerNorm
 // parameter gradients of every layer.  A net with dx set (count must be 1)
-// also gets the gradient of the chosen input columns.
+// also gets the gradient of the chosen input columns (dx_deferred: its split-K
+// partials are left unreduced and the launch's parameters returned).  loss:
+// the policy's loss, reduced in the gradient reduction's launch.
 int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t s,
-                 bool top_bias_ready = false, const AdamArgs* adam = nullptr) {
+                 bool top_bias_ready = false, const AdamArgs* adam = nullptr,
+                 const ActorLossArgs* loss = nullptr, GemmParams* dx_deferred = nullptr) {
   const Net& N0 = x->net[nc[0].net];
   const int B = x->B, H = N0.H, L = N0.L;
   // adam: the parameter gradients go into the Adam step of the vector as
@@ -864,6 +866,10 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
         P.partial = splitk;
         plan_split_k(P, x->bf16, 512);
         P.partial_len = (int64_t)P.splits * d.M * d.N;
+        if (dx_deferred) {
+          P.defer_reduce = P.splits > 1;
+          *dx_deferred = P;
+        }
         CRL_HIP(launch_gemm(P, x->bf16, LAY_KC, LAY_KC, false, s), "input gradient GEMM");
       }
       break;
@@ -881,9 +887,9 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
         a.b[e] = nc[e].p + lp.be;
         a.dH[e] = W(ws, S.dH);
         a.dZ[e] = W(ws, S.dZ[nxt]);
-        a.part[e] = WF(ws, S.lnp[l - 1]);
+        a.part[e] = grads ? WF(ws, S.lnp[l - 1]) : nullptr;
       }
-      CRL_HIP(launch_ln_swish_bwd(a, count, B, H, x->bf16, x->ln_rows_per_wave, s), "LayerNorm backward");
+      CRL_HIP(launch_ln_swish_bwd(a, count, B, H, x->bf16, s), "LayerNorm backward");
     }
     cur = nxt;
   }
@@ -897,11 +903,12 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
       const int64_t n = nc[0].net == 2 ? x->nparam_actor : x->nparam;
       bytes += (24.0 + (adam->pb ? 2.0 : 0.0)) * n - (nc[0].g ? 0.0 : 4.0 * n);
       CRL_HIP(launch_grad_reduce(wsc, nc[0].g, G.d_few, (int)G.few.size(), G.chunks, G.d_many,
-                                 (int)G.many.size(), G.nblocks, bytes, s, adam),
+                                 (int)G.many.size(), G.nblocks, bytes, s, adam, loss),
               "gradient reductions with the Adam step");
     } else {
       CRL_HIP(launch_grad_reduce(wsc, nc[0].g, G.d_few, G.nfew_plain, G.total4_plain, G.d_many,
-                                 (int)G.many.size(), G.nblocks, G.few_bytes + G.many_bytes, s),
+                                 (int)G.many.size(), G.nblocks, G.few_bytes + G.many_bytes, s, nullptr,
+                                 loss),
               "gradient reductions");
     }
   }
@@ -1450,7 +1457,7 @@ static int actor_step(crl_ctx* x, const float* params, const uint16_t* params_bf
   float* logpi = WF(ws, x->logpi);
   float* fpol = WF(ws, x->fpol);
   float* dact = WF(ws, x->dact);
-  const float* pout = WF(ws, x->sl[2].out);
+  float* pout = WF(ws, x->sl[2].out);
 
   // random goals: the policy and psi see the mixed goals
   if (x->mix_thr > 0) {
@@ -1462,25 +1469,26 @@ static int actor_step(crl_ctx* x, const float* params, const uint16_t* params_bf
   }
   // policy MLP on [s, g], then the sampled action and log pi
   NetCall pol = {2, x_sg, x->ld_sg, actor_params, apb, actor_grads, nullptr, 0, 0, 0};
-  CRL_TRY(mlp_forward(x, &pol, 1, ws, s));
-  CRL_HIP(launch_actor_head_fwd(pout, x->P, x->A, seed, step, x_sa, xsa2, x->net[0].ld_in,
+  GemmParams top{};
+  CRL_TRY(mlp_forward(x, &pol, 1, ws, s, &top));
+  CRL_HIP(launch_actor_head_fwd(pout, top, x->P, x->A, seed, step, x_sa, xsa2, x->net[0].ld_in,
                                 x->cfg.obs_dim, eps, logpi, B, x->bf16, s), "policy head");
   // frozen critic on (s, a') and g
   NetCall crit[2] = {{0, xsa2, x->net[0].ld_in, params, pb, nullptr, nullptr, 0, 0, 0},
                      {1, x_g, x->net[1].ld_in, params, pb, nullptr, nullptr, 0, 0, 0}};
-  CRL_TRY(mlp_forward(x, crit, 2, ws, s));
-  CRL_HIP(launch_actor_energy(WF(ws, x->sl[0].out), WF(ws, x->sl[1].out), x->D, x->energy, fpol,
-                              W(ws, x->sl[0].dout_t), B, x->bf16, s), "policy energy");
+  CRL_TRY(mlp_forward(x, crit, 2, ws, s, &top));
+  CRL_HIP(launch_actor_energy(WF(ws, x->sl[0].out), WF(ws, x->sl[1].out), top, x->D, x->energy,
+                              fpol, W(ws, x->sl[0].dout_t), B, x->bf16, s), "policy energy");
   // d(-mean f)/da' through phi (no parameter gradients)
   NetCall back = {0, xsa2, x->net[0].ld_in, params, pb, nullptr, dact, x->cfg.obs_dim, x->A, x->ldd};
-  CRL_TRY(mlp_backward(x, &back, 1, ws, s));
-  CRL_HIP(launch_actor_head_bwd(pout, x->P, x->A, eps, dact, x->ldd, log_alpha,
+  GemmParams dx{};
+  CRL_TRY(mlp_backward(x, &back, 1, ws, s, false, nullptr, nullptr, &dx));
+  CRL_HIP(launch_actor_head_bwd(pout, x->P, x->A, eps, dact, x->ldd, dx, log_alpha,
                                 WF(ws, x->sl[2].dout), W(ws, x->sl[2].dout_t), B, x->bf16, s),
           "policy head backward");
-  CRL_TRY(mlp_backward(x, &pol, 1, ws, s, false, adam));
-  CRL_HIP(launch_actor_loss(logpi, fpol, B, log_alpha, x->cfg.target_entropy, loss_out,
-                            alpha_grad, s), "actor loss");
-  return CRL_OK;
+  const ActorLossArgs loss = {logpi, fpol, B, log_alpha, x->cfg.target_entropy, loss_out,
+                              alpha_grad};
+  return mlp_backward(x, &pol, 1, ws, s, false, adam, &loss);
 }
 
 CRL_API int crl_actor_step(crl_ctx* x, const float* params, const uint16_t* params_bf16,

@@ -75,13 +75,13 @@ struct LnArgs {
   // backward
   const void* dH[2];
   void* dZ[2];
-  float* part[2];       // [ceil(B/128)][3][N] column partials
+  float* part[2];       // [ln_bwd_partials(B)][3][N] column partials; NULL: only dZ
 };
 hipError_t launch_ln_swish_fwd(const LnArgs& a, int count, int B, int N, float eps,
                                bool bf16, hipStream_t s);
 hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf16,
-                               int rows_per_wave, hipStream_t s);
-int ln_bwd_partials(int B, int rows_per_wave);
+                               hipStream_t s);
+int ln_bwd_partials(int B);
 
 // column sums of X [B][N] (FP32) over chunks of 128 rows: part[e][ceil(B/128)][N]
 struct ColSumArgs {
@@ -117,12 +117,25 @@ struct RedJob {
 constexpr int kRedChunk4 = 1024;
 constexpr int kManyCols = 32;  // outputs per workgroup of a many-part reduction job
 struct AdamArgs;
+// loss_out = {L_pi, mean log pi, L_alpha, mean f}; *alpha_grad = dL_alpha/dlog alpha:
+//   L_pi = alpha mean(log pi) - mean(f),  L_alpha = -log alpha (mean(log pi) + H)
+struct ActorLossArgs {
+  const float* logpi;
+  const float* f;
+  int B;
+  const float* log_alpha;
+  float target_entropy;
+  float* loss_out;
+  float* alpha_grad;
+};
 // few-part jobs (total4 float4 outputs) and many-part jobs (nblocks blocks of
 // 16 outputs) in one launch.  With A, each gradient element goes straight
 // into the Adam step of its parameter (g, if not NULL, still receives it).
+// With L, one more block reduces the policy's loss.
 hipError_t launch_grad_reduce(const char* ws, float* g, const RedJob* few, int nfew,
                               int64_t total4, const RedJob* many, int nmany, int64_t nblocks,
-                              double bytes, hipStream_t s, const AdamArgs* A = nullptr);
+                              double bytes, hipStream_t s, const AdamArgs* A = nullptr,
+                              const ActorLossArgs* L = nullptr);
 
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
 // Adam coefficients: 1 - b and log b are formed in double on the host.
@@ -235,23 +248,22 @@ hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int lo
 bool fused_bwd_one_pass(int B, int D);
 
 // actor.hip: the policy step's elementwise/row kernels
-hipError_t launch_actor_head_fwd(const float* out, int ldo, int A, uint64_t seed,
+// Each takes its input either final (top / dx with splits == 1) or as the
+// launch's split-K partials, which it sums in split order (plus the bias) and
+// also writes out.
+hipError_t launch_actor_head_fwd(float* out, const GemmParams& top, int ldo, int A, uint64_t seed,
                                  const int64_t* step, const void* x_sa, void* x_sa2, int ld,
                                  int d_s, float* eps, float* logpi, int B, bool bf16,
                                  hipStream_t s);
 // f_b = energy(phi_b, psi_b) (CRL_ENERGY_*) and d(-mean f)/dphi
-hipError_t launch_actor_energy(const float* phi, const float* psi, int D, int energy, float* f,
-                               void* dphi, int B, bool bf16, hipStream_t s);
+hipError_t launch_actor_energy(float* phi, float* psi, const GemmParams& top, int D, int energy,
+                               float* f, void* dphi, int B, bool bf16, hipStream_t s);
 hipError_t launch_actor_head_bwd(const float* out, int ldo, int A, const float* eps,
-                                 const float* da, int ldd, const float* log_alpha, float* dout,
-                                 void* dout_t, int B, bool bf16, hipStream_t s);
+                                 float* da, int ldd, const GemmParams& dx, const float* log_alpha,
+                                 float* dout, void* dout_t, int B, bool bf16, hipStream_t s);
 // random goals: xg_out[b] = x_g[j], xsg_out[b] = [x_sg[b][0:d_s], x_g[j], 0...]
 // with j the partner drawn for b (j = b when b is not mixed)
 hipError_t launch_goal_mix(const void* x_g, int ld_g, const void* x_sg, int ld_sg, int d_s,
                            int d_g, uint64_t seed, const int64_t* step, uint64_t thr53, int B,
                            void* xg_out, void* xsg_out, bool bf16, hipStream_t s);
-hipError_t launch_actor_loss(const float* logpi, const float* f, int B, const float* log_alpha,
-                             float target_entropy, float* loss_out, float* alpha_grad,
-                             hipStream_t s);
-
 }  // namespace crl

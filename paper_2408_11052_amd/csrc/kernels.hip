@@ -188,19 +188,18 @@ hipError_t launch_ln_swish_fwd(const LnArgs& a, int count, int B, int N, float e
 }
 
 // Backward of h = Swish(g * zhat + b), zhat = (z - mu) * rstd.  Each
-// workgroup owns `rows` rows (a multiple of kLnRows, taken kLnRows at a time,
-// kLnRows / 4 per wavefront, one row at a time):
+// workgroup owns `rows` rows (a multiple of 4 R, taken 4 R at a time, R per
+// wavefront, one row at a time):
 //   dy = dh * Swish'(y), dzhat = g * dy,
 //   dz = rstd * (dzhat - mean(dzhat) - zhat * mean(dzhat * zhat)),
 // and it accumulates the column sums dg = sum dy*zhat, db_ln = sum dy,
 // db_linear = sum dz of its rows; the four wavefronts' sums are added in LDS
-// in a fixed order and written as one partial row per workgroup.
-constexpr int kLnRows = 16;
-
-template <typename T, int CH>
+// in a fixed order and written as one partial row per workgroup (PARTS = 0:
+// no parameter gradients are wanted, only dz).
+template <typename T, int CH, int R, int PARTS>
 __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int N, int rows) {
   extern __shared__ float red[];  // [4 waves][3][N]
-  constexpr int R = kLnRows / 4;  // rows per wavefront
+  constexpr int kRound = 4 * R;   // rows of a round
   const int e = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nch = N >> 3;
@@ -216,10 +215,10 @@ __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int 
     if (ch < nch) { load8(a.g[e] + ch * 8, gv[c]); load8(a.b[e] + ch * 8, bv[c]); }
   }
   const float inv_n = 1.f / (float)N;
-  // rounds of kLnRows rows (R per wavefront) over the workgroup's rows; the
-  // column sums run on across the rounds
+  // rounds of 4 R rows (R per wavefront) over the workgroup's rows; the column
+  // sums run on across the rounds
   const int wg_end = min(B, (blockIdx.x + 1) * rows);
-  for (int base = blockIdx.x * rows; base < wg_end; base += kLnRows) {
+  for (int base = blockIdx.x * rows; base < wg_end; base += kRound) {
     const int r0 = base + wave * R;
     const int nr = max(0, min(R, B - r0));
     // all rows of this wavefront are requested before any is used
@@ -262,8 +261,10 @@ __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int 
             // Swish'(y) = sg (1 + y (1 - sg)) = sg + y sg (1 - sg)
             const float q = __builtin_fmaf(-sg, sg, sg);
             const float dy = dh[i] * __builtin_fmaf(y, q, sg);
-            cg[c][i] += dy * xh;
-            cb[c][i] += dy;
+            if (PARTS) {
+              cg[c][i] += dy * xh;
+              cb[c][i] += dy;
+            }
             const float d = dy * gv[c][i];
             zh[c][i] = xh;
             dzh[c][i] = d;
@@ -284,13 +285,14 @@ __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int 
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             o[i] = __builtin_fmaf(rs[j], dzh[c][i], __builtin_fmaf(e, zh[c][i], k));
-            cz[c][i] += o[i];
+            if (PARTS) cz[c][i] += o[i];
           }
           store8(dZb + (int64_t)row * N + ch * 8, o);
         }
       }
     }
   }
+  if (!PARTS) return;
   float* mine = red + (int64_t)wave * 3 * N;
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -317,29 +319,47 @@ __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int 
   }
 }
 
-// Rows per workgroup: kLnRows up to B = 4096 (one round of at most 512
-// workgroups for two encoders), then more rounds per workgroup instead of
-// more workgroups, so the column partials (3 N floats per workgroup, summed
-// again in the gradient reduction) stop growing with B.
-int ln_bwd_rows(int B) { return kLnRows * std::max(1, (B + 4095) / 4096); }
-int ln_bwd_partials(int B, int) {
+// Rows of a wavefront at a time.  Up to B = 2048 one or two, so that the
+// launch has four times or twice the workgroups and each its chain of rows
+// shortened (one encoder at B = 1000: 63 workgroups and 7.2 us with four rows,
+// 250 and 5.0 us with one); above, four: a workgroup's 256 column partials
+// are then paid for by 16 rows.  The number of partial rows is at most 256
+// either way.
+int ln_bwd_r(int B) { return B <= 1024 ? 1 : B <= 2048 ? 2 : 4; }
+// Rows per workgroup: one round up to B = 4096 (at most 512 workgroups for two
+// encoders), then more rounds per workgroup instead of more workgroups, so the
+// column partials (3 N floats per workgroup, summed again in the gradient
+// reduction) stop growing with B.
+int ln_bwd_rows(int B) { return 4 * ln_bwd_r(B) * std::max(1, (B + 4095) / 4096); }
+int ln_bwd_partials(int B) {
   const int rows = ln_bwd_rows(B);
   return (B + rows - 1) / rows;
 }
 
-hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf16, int,
+template <typename T, int CH, int R>
+static void ln_bwd_run(const LnArgs& a, int count, int B, int N, hipStream_t s) {
+  const dim3 grid(ln_bwd_partials(B), count);
+  const size_t lds = (size_t)4 * 3 * N * sizeof(float);
+  if (a.part[0]) ln_swish_bwd_kernel<T, CH, R, 1><<<grid, 256, lds, s>>>(a, B, N, ln_bwd_rows(B));
+  else ln_swish_bwd_kernel<T, CH, R, 0><<<grid, 256, 0, s>>>(a, B, N, ln_bwd_rows(B));
+}
+template <typename T, int CH>
+static void ln_bwd_rows_run(const LnArgs& a, int count, int B, int N, hipStream_t s) {
+  const int r = ln_bwd_r(B);
+  if (r == 1) ln_bwd_run<T, CH, 1>(a, count, B, N, s);
+  else if (r == 2) ln_bwd_run<T, CH, 2>(a, count, B, N, s);
+  else ln_bwd_run<T, CH, 4>(a, count, B, N, s);
+}
+hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf16,
                                hipStream_t s) {
   const int ch = (N / 8 + 63) / 64;
-  const int rows = ln_bwd_rows(B);
-  const int nparts = ln_bwd_partials(B, 0);
-  dim3 grid(nparts, count), block(256);
-  const size_t lds = (size_t)4 * 3 * N * sizeof(float);
-  const double bytes = (double)count * ((double)B * N * 3.0 * (bf16 ? 2 : 4) + 12.0 * nparts * N);
-#define LNB(T, C) CRL_TIMED("ln_swish_bwd_kernel", 0.0, bytes, s, \
-                            ln_swish_bwd_kernel<T, C><<<grid, block, lds, s>>>(a, B, N, rows))
-  if (bf16) { if (ch <= 1) LNB(bf16_t, 1); else LNB(bf16_t, 2); }
-  else      { if (ch <= 1) LNB(float, 1);  else LNB(float, 2); }
-#undef LNB
+  const double bytes = (double)count * ((double)B * N * 3.0 * (bf16 ? 2 : 4) +
+                                        (a.part[0] ? 12.0 * ln_bwd_partials(B) * N : 0.0));
+  KTimer t = timing_begin("ln_swish_bwd_kernel", 0.0, bytes, s);
+  // hidden widths are at most 1024 (checked at context creation): CH <= 2
+  if (bf16) { if (ch <= 1) ln_bwd_rows_run<bf16_t, 1>(a, count, B, N, s); else ln_bwd_rows_run<bf16_t, 2>(a, count, B, N, s); }
+  else      { if (ch <= 1) ln_bwd_rows_run<float, 1>(a, count, B, N, s);  else ln_bwd_rows_run<float, 2>(a, count, B, N, s); }
+  timing_end(t);
   return hipGetLastError();
 }
 
@@ -679,18 +699,60 @@ __device__ __forceinline__ void reduce_many(const char* __restrict__ ws, float* 
   }
 }
 
+// The policy step's loss (see ActorLossArgs) by one workgroup of 256 threads:
+// 1024 Kahan sums over the samples (four per thread, so that the sums are those
+// of 1024 threads), then an ordered tree.
+__device__ void actor_loss(const ActorLossArgs& L, float* __restrict__ sh) {
+  const int tid = threadIdx.x;
+  for (int v = tid; v < 1024; v += 256) {
+    float s0 = 0.f, c0 = 0.f, s1 = 0.f, c1 = 0.f;
+    for (int i = v; i < L.B; i += 1024) {
+      kahan_add(s0, c0, L.logpi[i]);
+      kahan_add(s1, c1, L.f[i]);
+    }
+    sh[v] = s0 - c0;
+    sh[1024 + v] = s1 - c1;
+  }
+  __syncthreads();
+  for (int w = 512; w >= 1; w >>= 1) {
+    for (int v = tid; v < w; v += 256) {
+      sh[v] += sh[v + w];
+      sh[1024 + v] += sh[1024 + v + w];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    const float la = *L.log_alpha;
+    const float mlp = sh[0] / (float)L.B, mf = sh[1024] / (float)L.B;
+    L.loss_out[0] = expf(la) * mlp - mf;
+    L.loss_out[1] = mlp;
+    L.loss_out[2] = -la * (mlp + L.target_entropy);
+    L.loss_out[3] = mf;
+    *L.alpha_grad = -(mlp + L.target_entropy);
+  }
+}
+
 // Both reductions in one launch: blocks [0, nbf) take the few-part jobs,
-// the rest the many-part jobs.  ADAM: each reduced element goes into the
-// Adam step of its parameter (the jobs then cover the whole vector).
+// the rest the many-part jobs, and one more block the policy's loss where
+// L.loss_out is set (a launch of its own took 4.8 us).  ADAM: each reduced
+// element goes into the Adam step of its parameter (the jobs then cover the
+// whole vector).
 template <bool ADAM>
 __global__ __launch_bounds__(256) void grad_reduce_kernel(const char* __restrict__ ws,
                                                           float* __restrict__ g,
                                                           const RedJob* __restrict__ few,
                                                           int nfew, int64_t total4,
                                                           const RedJob* __restrict__ many,
-                                                          int nmany, int64_t nbf, AdamArgs A) {
+                                                          int nmany, int64_t nbf, AdamArgs A,
+                                                          ActorLossArgs L) {
+  constexpr int kLds = ADAM ? kRedLdsFloats : 2048;
+  __shared__ __attribute__((aligned(16))) float T[kLds];
+  static_assert(kLds >= 2048, "the policy loss takes 2048 floats");
+  if (L.loss_out && blockIdx.x == gridDim.x - 1) {
+    actor_loss(L, T);
+    return;
+  }
   if constexpr (ADAM) {
-    __shared__ __attribute__((aligned(16))) float T[kRedLdsFloats];
     float c1, c2;
     adam_factors(A.c, A.step, c1, c2);
     if (blockIdx.x < nbf) reduce_few_adam(ws, g, few, nfew, blockIdx.x, A, c1, c2, T);
@@ -703,20 +765,22 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const char* __restrict
 
 hipError_t launch_grad_reduce(const char* ws, float* g, const RedJob* few, int nfew,
                               int64_t total4, const RedJob* many, int nmany, int64_t nblocks,
-                              double bytes, hipStream_t s, const AdamArgs* A) {
+                              double bytes, hipStream_t s, const AdamArgs* A,
+                              const ActorLossArgs* L) {
   // with Adam, total4 counts chunks of kRedChunk4 float4s
   const int64_t nbf = nfew > 0 ? (A ? total4 : (total4 + 255) / 256) : 0;
   const int64_t nbm = nmany > 0 ? nblocks : 0;
-  if (nbf + nbm == 0) return hipSuccess;
-  const dim3 grid((unsigned)(nbf + nbm));
+  if (nbf + nbm == 0) return L ? hipErrorInvalidValue : hipSuccess;
+  const dim3 grid((unsigned)(nbf + nbm + (L ? 1 : 0)));
+  const ActorLossArgs la = L ? *L : ActorLossArgs{};
   if (A)
     CRL_TIMED("grad_reduce_adam_kernel", 0.0, bytes, s,
               grad_reduce_kernel<true><<<grid, 256, 0, s>>>(ws, g, few, nfew, total4, many,
-                                                            nmany, nbf, *A));
+                                                            nmany, nbf, *A, la));
   else
     CRL_TIMED("grad_reduce_kernel", 0.0, bytes, s,
               grad_reduce_kernel<false><<<grid, 256, 0, s>>>(ws, g, few, nfew, total4, many,
-                                                             nmany, nbf, AdamArgs{}));
+                                                             nmany, nbf, AdamArgs{}, la));
   return hipGetLastError();
 }
 
