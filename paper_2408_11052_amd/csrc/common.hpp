@@ -124,6 +124,28 @@ __device__ inline void philox4x64_10(uint64_t (&x)[4], uint64_t k0, uint64_t k1)
   }
 }
 
+// ---------------------------------------------------------------------------
+// Global memory straight into LDS
+// ---------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ uint32_t lds_address(void* p) {
+  return (uint32_t)(uintptr_t)(lds_char*)p;
+}
+// 64 lanes x 16 bytes: lane l's 16 bytes at base + off go to LDS address
+// lds + 16 l.  No register is written and the compiler does not count the
+// load: wait_vm below does.  (Through the builtin the compiler, which cannot
+// tell buffers apart, waits for every such load before the next transpose read.)
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               ::"s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+// all but this wave's N latest vector-memory operations done, and its LDS reads
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
+}
+
 // Compensated (Kahan) summation step.
 __device__ inline void kahan_add(float& s, float& comp, float x) {
   float y = x - comp;

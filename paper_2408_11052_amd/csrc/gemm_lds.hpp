@@ -14,15 +14,13 @@
 // Every result is the same chain of MFMAs in K order whatever the tile, so all
 // tiles give the same bits.
 //
-// The loads are issued through inline assembly.  Through the builtin the
-// compiler knows that they write LDS and, since it cannot tell the stages
-// apart, waits for all of them (s_waitcnt vmcnt(0)) before the next transpose
-// read: the prefetch then overlapped nothing.  With the explicit counted waits
-// below one 2 x (4096 x 1024 x 1024) BF16 forward launch went from 25.0 to
-// 21.7 us, one 2 x (1024 x 1024 x 4096, two splits) dW launch from 36.7 to
-// 24.7 us (794 and 695 TFLOP/s; a 64-deep step of a resident pair of
-// workgroups takes 0.93 us, 86% of the 1.25-1.35 PFLOP/s that large library
-// products reach on this card; 7 us of a launch are its fixed cost).
+// The loads are issued with explicit counted waits (load_to_lds): with the
+// compiler's own waits the prefetch overlapped nothing.  One 2 x (4096 x 1024
+// x 1024) BF16 forward launch went from 25.0 to 21.7 us, one 2 x (1024 x 1024 x
+// 4096, two splits) dW launch from 36.7 to 24.7 us (794 and 695 TFLOP/s; a
+// 64-deep step of a resident pair of workgroups takes 0.93 us, 86% of the
+// 1.25-1.35 PFLOP/s that large library products reach on this card; 7 us of a
+// launch are its fixed cost).
 #pragma once
 #include "gemm.hpp"
 
@@ -32,7 +30,6 @@ namespace lds {
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
-typedef __attribute__((address_space(3))) char lds_char;
 
 template <typename T> constexpr int bk() { return 128 / (int)sizeof(T); }   // K per stage
 template <typename T> constexpr int vec() { return 16 / (int)sizeof(T); }   // values per chunk
@@ -74,20 +71,6 @@ template <typename T, int W> __device__ __forceinline__ int mc_swz(int kr) {
   if (W >= 128) return 2 * ((kr & 3) + 4 * ((kr >> 3) & 1));
   if (W == 64) return 2 * (((kr >> 1) & 1) + 2 * ((kr >> 3) & 1));
   return 2 * ((kr >> 3) & 1);
-}
-
-// 64 lanes x 16 bytes: lane l's 16 bytes at base + off go to LDS address
-// lds + 16 l.  No register is written and the compiler does not count the
-// load: wait_vm below does.
-__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               ::"s"(lds), "v"(off), "s"(base)
-               : "memory");
-}
-// all but this wave's N latest vector-memory operations done, and its LDS reads
-template <int N> __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
 }
 
 // One operand's stages.  One wave instruction fills one 1 KB block of the
@@ -284,7 +267,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+  const uint32_t lds0 = lds_address(smem);
   floatx4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)

@@ -270,9 +270,9 @@ __device__ __forceinline__ void tile_product(floatx4 (&acc)[4], const bf16x8 (&x
 
 // Occupancy targets (wavefronts per SIMD) that the register allocation must
 // meet: the forward's LDS holds three workgroups per CU at D = 256, the
-// backward passes need about 256 registers per lane there.
+// backward's two.
 template <int KS> constexpr int fwd_waves() { return KS >= 8 ? 3 : 4; }
-template <int KS> constexpr int bwd_waves() { return KS >= 4 ? 2 : 4; }
+template <int KS, int EN> constexpr int wide_waves() { return KS >= 8 || EN != kEnDot ? 2 : 3; }
 
 template <int KS, int EN>
 __global__ __launch_bounds__(256, fwd_waves<KS>()) void infonce_fwd_kernel(FusedArgs a, int B, int cps) {
@@ -467,13 +467,9 @@ __device__ __forceinline__ int gt_at(int c, int e) {
 // TRANS = 1: rows are psi, streamed operand phi -> partials of dpsi.
 // Per 64-column tile: F (MFMA), G (or H) into the wave's own LDS strip, then
 // dX += G . Y with the Y operand read from the row-major tile by the 16-bit
-// transpose read (no transposed copy of the tile is kept).  For D >= 128 the
-// product is split over D instead of rows: after a workgroup barrier each
-// wave multiplies all four strips (64 rows) by its quarter of the tile's
-// columns, so the tile is read once per workgroup in that product rather
-// than once per wave; for D <= 64 a wave reads its own strip back.  The tile's
-// column values (the other side's LSE, |y|^2) are fetched together with the
-// tile, one tile ahead.
+// transpose read (no transposed copy of the tile is kept).  D <= 64 here: a
+// wave reads its own strip back.  The tile's column values (the other side's
+// LSE, |y|^2) are fetched together with the tile, one tile ahead.
 //
 // Entry (i, j) of G (rows pass; the columns pass exchanges the roles) is
 //   P^r_ij (wf + 2 beta r_i) / B + wb P^c_ij / B - (wf + wb) delta_ij / B,
@@ -484,7 +480,7 @@ __device__ __forceinline__ int gt_at(int c, int e) {
 // column as one 8-byte write; the transpose read gives back the row-major A
 // operand of the product.
 template <int KS, int EN, int TRANS>
-__global__ __launch_bounds__(256, bwd_waves<KS>()) void infonce_bwd_kernel(FusedArgs a, int B, int cps,
+__global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B, int cps,
                                                           float beta, float wf, float wb,
                                                           float log2b) {
   constexpr bool L2 = EN != kEnDot;
@@ -492,9 +488,7 @@ __global__ __launch_bounds__(256, bwd_waves<KS>()) void infonce_bwd_kernel(Fused
   constexpr int LDY = D + 16;
   constexpr int LDG = 16;     // transposed G strip: [64 columns][16 rows]
   constexpr int NB = D / 16;  // 16-wide output blocks of dX
-  // D >= 128: wave w owns columns [w D/4, (w+1) D/4) of dX for all 64 rows
-  constexpr bool DSPLIT = NB >= 8;
-  constexpr int NW = NB / 4;  // 16-wide output blocks per wave when split
+  static_assert(KS <= 2, "wider representations: infonce_bwd_wide_kernel");
   typedef short v4s __attribute__((ext_vector_type(4)));
   typedef short v8s __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) v4s lds_v4s;
@@ -636,79 +630,41 @@ __global__ __launch_bounds__(256, bwd_waves<KS>()) void infonce_bwd_kernel(Fused
       w.y = pack2bf(h[2], h[3]);
       *reinterpret_cast<uint2*>(&Gt[wave][gt_at(jb * 16 + r16, 4 * g)]) = w;
     }
-    if constexpr (DSPLIT) {
-      // every wave reads all four strips: a workgroup barrier
-      __syncthreads();
-      // dX[64 rows][this wave's D/4 columns] += G[64][64] . Y[64][D/4 columns];
-      // the A fragments of the four strips are read once and each used NW times
+    // only this wave reads its strip back: a wave-local LDS wait suffices
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+    // dX[16 rows][D] += G[16][64] . Y[64][D]; lane (g, j) needs G[j][8g + 0..7]
+    // and Y[8g + 0..7][d] of column d = nb*16 + j: transpose reads of 4 rows
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 ga[4];
+    for (int kk = 0; kk < 2; ++kk) {
+      v4s gq[2];
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          v4s gq[2];
+      for (int q = 0; q < 2; ++q) {
+        const int krow = kk * 32 + 8 * g + 4 * q + (r16 >> 2);
+        gq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_v4s*)(&Gt[wave][gt_at(krow, 4 * (r16 & 3))]));
+      }
+      v8s gv8 = {gq[0][0], gq[0][1], gq[0][2], gq[0][3], gq[1][0], gq[1][1], gq[1][2], gq[1][3]};
+      const bf16x8 ga = __builtin_bit_cast(bf16x8, gv8);
+      // up to four output blocks at a time: their B fragments read together
+      constexpr int NU = NB < 4 ? NB : 4;
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int krow = kk * 32 + 8 * g + 4 * q + (r16 >> 2);
-            gq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (lds_v4s*)(&Gt[st][gt_at(krow, 4 * (r16 & 3))]));
-          }
-          v8s gv8 = {gq[0][0], gq[0][1], gq[0][2], gq[0][3], gq[1][0], gq[1][1], gq[1][2], gq[1][3]};
-          ga[st] = __builtin_bit_cast(bf16x8, gv8);
-        }
+      for (int nb0 = 0; nb0 < NB; nb0 += NU) {
+        v4s hq[NU][2];
 #pragma unroll
-        for (int u = 0; u < NW; ++u) {
-          v4s hq[2];
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
             const int jpos = kk * 32 + 8 * q + lds_row(8 * g + (r16 >> 2));
-            const int dcol = (wave * NW + u) * 16 + 4 * (r16 & 3);
-            hq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(Yt + lds_pos<D>(jpos, dcol)));
+            const int dcol = (nb0 + u) * 16 + 4 * (r16 & 3);
+            hq[u][q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(Yt + lds_pos<D>(jpos, dcol)));
           }
-          v8s yv = {hq[0][0], hq[0][1], hq[0][2], hq[0][3], hq[1][0], hq[1][1], hq[1][2], hq[1][3]};
 #pragma unroll
-          for (int st = 0; st < 4; ++st)
-            acc_dx[st * NW + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                ga[st], __builtin_bit_cast(bf16x8, yv), acc_dx[st * NW + u], 0, 0, 0);
-        }
-      }
-    } else {
-      // only this wave reads its strip back: a wave-local LDS wait suffices
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-      __builtin_amdgcn_wave_barrier();
-      // dX[16 rows][D] += G[16][64] . Y[64][D]; lane (g, j) needs G[j][8g + 0..7]
-      // and Y[8g + 0..7][d] of column d = nb*16 + j: transpose reads of 4 rows
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        v4s gq[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int krow = kk * 32 + 8 * g + 4 * q + (r16 >> 2);
-          gq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_v4s*)(&Gt[wave][gt_at(krow, 4 * (r16 & 3))]));
-        }
-        v8s gv8 = {gq[0][0], gq[0][1], gq[0][2], gq[0][3], gq[1][0], gq[1][1], gq[1][2], gq[1][3]};
-        const bf16x8 ga = __builtin_bit_cast(bf16x8, gv8);
-        // up to four output blocks at a time: their B fragments read together
-        constexpr int NU = NB < 4 ? NB : 4;
-#pragma unroll
-        for (int nb0 = 0; nb0 < NB; nb0 += NU) {
-          v4s hq[NU][2];
-#pragma unroll
-          for (int u = 0; u < NU; ++u)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const int jpos = kk * 32 + 8 * q + lds_row(8 * g + (r16 >> 2));
-              const int dcol = (nb0 + u) * 16 + 4 * (r16 & 3);
-              hq[u][q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(Yt + lds_pos<D>(jpos, dcol)));
-            }
-#pragma unroll
-          for (int u = 0; u < NU; ++u) {
-            v8s yv = {hq[u][0][0], hq[u][0][1], hq[u][0][2], hq[u][0][3],
-                      hq[u][1][0], hq[u][1][1], hq[u][1][2], hq[u][1][3]};
-            acc_dx[nb0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                ga, __builtin_bit_cast(bf16x8, yv), acc_dx[nb0 + u], 0, 0, 0);
-          }
+        for (int u = 0; u < NU; ++u) {
+          v8s yv = {hq[u][0][0], hq[u][0][1], hq[u][0][2], hq[u][0][3],
+                    hq[u][1][0], hq[u][1][1], hq[u][1][2], hq[u][1][3]};
+          acc_dx[nb0 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              ga, __builtin_bit_cast(bf16x8, yv), acc_dx[nb0 + u], 0, 0, 0);
         }
       }
     }
@@ -717,25 +673,13 @@ __global__ __launch_bounds__(256, bwd_waves<KS>()) void infonce_bwd_kernel(Fused
   }
   // write this split's partials (the two passes use separate halves)
   float* dst = a.dX_part + ((int64_t)TRANS * gridDim.y + blockIdx.y) * B * D;
-  if constexpr (DSPLIT) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int u = 0; u < NW; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = rb * kFRows + st * 16 + 4 * g + r;
-          if (row < B) dst[(int64_t)row * D + (wave * NW + u) * 16 + r16] = acc_dx[st * NW + u][r];
-        }
-  } else {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = row_base + 4 * g + r;
-        if (row < B) dst[(int64_t)row * D + nb * 16 + r16] = acc_dx[nb][r];
-      }
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int row = row_base + 4 * g + r;
+      if (row < B) dst[(int64_t)row * D + nb * 16 + r16] = acc_dx[nb][r];
+    }
   if (L2) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -746,6 +690,287 @@ __global__ __launch_bounds__(256, bwd_waves<KS>()) void infonce_bwd_kernel(Fused
       if (r16 == 0 && row < B) a.rs_part[((int64_t)TRANS * gridDim.y + blockIdx.y) * B + row] = s;
     }
   }
+}
+
+// The two passes at D >= 128, both in one launch (blockIdx.z; each writes its
+// own half of the partials).  As infonce_bwd_kernel, but the dX product is
+// split over D instead of rows: after a workgroup barrier each wave multiplies
+// all four G strips (64 rows) by its quarter of the tile's columns, so the
+// tile is read once per workgroup in that product rather than once per wave.
+//
+// What binds it is the mix per 64 x 64 tile: 64 MFMAs a wave, about 19 vector
+// instructions an entry and 192 KB of LDS reads a workgroup, with two
+// workgroups on a CU.  Tiles go from global memory straight into LDS, one
+// ahead: staged through registers they held 32 of a lane's 256, which spilled,
+// and left each step of the tile product waiting for its own fragments; now
+// the next step's fragments are read during a step, and the entries of a tile
+// that touches neither an edge nor the diagonal run without branches.
+// B=16384, D=256, L2: 703 -> 635 us for both passes (the vector
+// instructions alone take some 430, the MFMAs 250); B=4096, D=128, L2: 56 -> 46 us; B=1500,
+// D=128: 23 -> 15 us, one launch instead of two.
+//
+// A tile row is 2 D bytes unpadded, its 16-byte chunk c in slot c ^ wide_swz(row):
+// the row operand's 16-byte reads (16 lanes at a time: rows 0-3 and 12-15 of
+// one chunk, 4-11 of the next) and the transpose reads (a half-wave: rows
+// 4q..4q+3 and 8 + 4q.., two chunks) each fall on 16 distinct 16-byte banks.
+__device__ __forceinline__ int wide_swz(int row) { return 2 * (row & 3) + (row & 8); }
+
+// One wave's share of the 64-row tile at row j0 of Y [B][D] into LDS address
+// dst: blocks of 1 KB (NR rows), 16 rows a wave.  Rows past B re-read row B-1;
+// the entries they meet are masked.
+template <int D>
+__device__ __forceinline__ void wide_tile_load(const bf16_t* __restrict__ Y, int j0, int B,
+                                               uint32_t dst, int wave, int lane) {
+  constexpr int RB = 2 * D, NR = 1024 / RB, NI = 16 / NR;  // row bytes, rows per block, blocks
+  constexpr int CPR = RB / 16;                             // chunks per row
+  const char* base = reinterpret_cast<const char*>(Y) + (int64_t)j0 * RB;
+  const int rl = lane / CPR, c = lane % CPR;
+  const int last = B - 1 - j0;  // the tile's last row that exists (>= 0)
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int r = wave * 16 + i * NR;  // the block's first row
+    const int slot = (c ^ wide_swz(i * NR + rl)) * 16;
+    if (last >= kFCols - 1)
+      load_to_lds(base + r * RB, rl * RB + slot, dst + (wave * NI + i) * 1024);
+    else
+      load_to_lds(base, min(r + rl, last) * RB + slot, dst + (wave * NI + i) * 1024);
+  }
+}
+
+template <int KS, int EN, int TRANS>
+__device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int cps, float beta,
+                                                 float wf, float wb, float log2b,
+                                                 bf16_t* __restrict__ Ys,
+                                                 bf16_t* __restrict__ Gt) {
+  constexpr bool L2 = EN != kEnDot;
+  constexpr int D = KS * 32;
+  constexpr int NB = D / 16;  // 16-wide output blocks of dX
+  constexpr int NW = NB / 4;  // ... per wave: columns [w D/4, (w+1) D/4) of all 64 rows
+  constexpr int TILE = kFCols * D;  // elements of a tile
+  constexpr int STRIP = kFCols * 16;
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  typedef short v8s __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) v4s lds_v4s;
+
+  const bf16_t* Xb = TRANS ? a.psi_b : a.phi_b;
+  const bf16_t* Yb = TRANS ? a.phi_b : a.psi_b;
+  const float* nX = TRANS ? a.npsi : a.nphi;
+  const float* nY = TRANS ? a.nphi : a.npsi;
+  // TRANS=0: rows own r_i (and the penalty), columns own c_j; TRANS=1: swapped
+  const float* lseX = TRANS ? a.c : a.r;
+  const float* lseY = TRANS ? a.r : a.c;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int rb = blockIdx.x;
+  const int row_base = rb * kFRows + wave * 16;
+  const int c0 = blockIdx.y * cps, c1 = min(B, c0 + cps);
+  const bool rows_full = row_base + 16 <= B;
+  const float beta2 = 2.f * beta;
+  const float dgv = (wf + wb) / (float)B;  // the diagonal's -delta_ij terms
+  auto main_shift = [&](float lse) { return __builtin_fmaf(lse, kL2E, log2b); };
+  auto other_shift = [&](float lse) {
+    return wb != 0.f ? __builtin_fmaf(lse, kL2E, log2b) : INFINITY;
+  };
+  const uint32_t lds0 = lds_address(Ys);
+  if (c0 < c1) wide_tile_load<D>(Yb, c0, B, lds0, wave, lane);
+
+  bf16x8 xa[KS];
+  {
+    const int row = row_base + r16;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (row < B) xa[ks] = *reinterpret_cast<const bf16x8*>(Xb + (int64_t)row * D + ks * 32 + g * 8);
+      else xa[ks] = bf16x8{};
+    }
+  }
+  float nx[4], sh_a[4], k_a[4], hsum[4];
+  bool rvalid[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = row_base + 4 * g + r;
+    rvalid[r] = row < B;
+    nx[r] = (L2 && rvalid[r]) ? nX[row] : 0.f;
+    const float l = rvalid[r] ? lseX[row] : 0.f;
+    sh_a[r] = TRANS ? other_shift(l) : main_shift(l);
+    k_a[r] = wf + beta2 * l;  // used by the rows pass only
+    hsum[r] = 0.f;
+  }
+  floatx4 acc_dx[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) acc_dx[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // per-lane column values of a tile (columns j0 + jb*16 + r16)
+  struct ColVals { float lse[4], ny[4]; };
+  auto col_load = [&](ColVals& cvv, int j0) {
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+      const int col = min(j0 + jb * 16 + r16, B - 1);  // past the edge: masked
+      cvv.lse[jb] = lseY[col];
+      cvv.ny[jb] = L2 ? nY[col] : 0.f;
+    }
+  };
+  const int jlast = c0 + ((c1 - c0 - 1) / kFCols) * kFCols;
+  ColVals cvals, cpf;
+  if (c0 < c1) col_load(cvals, c0);
+  // byte offsets in a tile: row operand chunk (t ^ (its row's swizzle)), t the
+  // step's low two bits; transpose read of output block u
+  int oa[4], ot[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    oa[t] = r16 * 2 * D + (((4 * t + g) ^ wide_swz(r16)) << 4);
+    const int tr = 8 * g + (r16 >> 2);  // + 4 q + 32 kk: the same swizzle
+    const int ch = (wave * NW + (t < NW ? t : 0)) * 2 + ((r16 & 3) >> 1);
+    ot[t] = tr * 2 * D + ((ch ^ wide_swz(tr)) << 4) + (r16 & 1) * 8;
+  }
+
+  int buf = 0;
+  for (int j0 = c0; j0 < c1; j0 += kFCols, buf ^= 1) {
+    // this tile has arrived (its loads were issued a tile ago), and every wave
+    // is past the previous tile's reads of the other buffer and of the strips
+    asm volatile("" ::: "memory");
+    wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    col_load(cpf, min(j0 + kFCols, jlast));
+    if (j0 + kFCols < c1)
+      wide_tile_load<D>(Yb, j0 + kFCols, B, lds0 + (buf ^ 1) * TILE * 2, wave, lane);
+    const char* __restrict__ Yt = reinterpret_cast<const char*>(Ys + buf * TILE);
+    floatx4 acc[4];
+    {
+      bf16x8 b[2][4];
+      auto frags = [&](int ks) {
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+          b[ks & 1][jb] = *reinterpret_cast<const bf16x8*>(Yt + oa[ks & 3] + (ks >> 2) * 256 +
+                                                           jb * 16 * 2 * D);
+      };
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) acc[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      frags(0);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + 1 < KS) frags(ks + 1);
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+          acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], b[ks & 1][jb], acc[jb], 0, 0, 0);
+      }
+    }
+    float sh_b[4], k_b[4];
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+      sh_b[jb] = TRANS ? main_shift(cvals.lse[jb]) : other_shift(cvals.lse[jb]);
+      k_b[jb] = wf + beta2 * cvals.lse[jb];  // used by the columns pass only
+    }
+    const bool edge = !rows_full || j0 + kFCols > c1;
+    const bool diag = j0 <= row_base && row_base < j0 + kFCols;
+    // one 16-column block at a time: its four rows' G, the diagonal and edge
+    // terms, H, the rows' sums and the strip store
+    auto entries = [&](bool special) {
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) {
+        float h[4], wv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float fv = energy_fw<EN>(acc[jb][r], nx[r], cvals.ny[jb], wv[r]);
+          const float pa = __builtin_amdgcn_exp2f(__builtin_fmaf(fv, kL2E, -sh_a[r]));
+          const float pb = __builtin_amdgcn_exp2f(__builtin_fmaf(fv, kL2E, -sh_b[jb]));
+          h[r] = TRANS ? __builtin_fmaf(pb, k_b[jb], pa) : __builtin_fmaf(pa, k_a[r], pb);
+        }
+        if (special) {
+          const bool cv = j0 + jb * 16 + r16 < c1;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (row_base + 4 * g + r == j0 + jb * 16 + r16) h[r] -= dgv;
+            h[r] = (cv && rvalid[r]) ? h[r] : 0.f;
+          }
+        }
+        // H = G / d (L2; 0 where d = 0) or 2 G (L2 without the root)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (EN != kEnDot) {
+            h[r] *= wv[r];
+            asm("" : "+v"(h[r]));  // the sum takes the rounded H: no contraction
+          }
+          hsum[r] += h[r];
+        }
+        uint2 w;
+        w.x = pack2bf(h[0], h[1]);
+        w.y = pack2bf(h[2], h[3]);
+        *reinterpret_cast<uint2*>(Gt + wave * STRIP + gt_at(jb * 16 + r16, 4 * g)) = w;
+      }
+    };
+    if (edge || diag) entries(true);
+    else entries(false);
+    // every wave reads all four strips: a workgroup barrier (LDS only)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // dX[64 rows][this wave's D/4 columns] += G[64][64] . Y[64][D/4 columns];
+    // the A fragments of the four strips are read once and each used NW times
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      bf16x8 ga[4];
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        v4s gq[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int krow = kk * 32 + 8 * g + 4 * q + (r16 >> 2);
+          gq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_v4s*)(Gt + st * STRIP + gt_at(krow, 4 * (r16 & 3))));
+        }
+        v8s gv8 = {gq[0][0], gq[0][1], gq[0][2], gq[0][3], gq[1][0], gq[1][1], gq[1][2], gq[1][3]};
+        ga[st] = __builtin_bit_cast(bf16x8, gv8);
+      }
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        v4s hq[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          hq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_v4s*)(Yt + ot[u] + (kk * 32 + 4 * q) * 2 * D));
+        v8s yv = {hq[0][0], hq[0][1], hq[0][2], hq[0][3], hq[1][0], hq[1][1], hq[1][2], hq[1][3]};
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+          acc_dx[st * NW + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              ga[st], __builtin_bit_cast(bf16x8, yv), acc_dx[st * NW + u], 0, 0, 0);
+      }
+    }
+    cvals = cpf;
+  }
+  // write this split's partials (the two passes use separate halves)
+  float* dst = a.dX_part + ((int64_t)TRANS * gridDim.y + blockIdx.y) * B * D;
+#pragma unroll
+  for (int st = 0; st < 4; ++st)
+#pragma unroll
+    for (int u = 0; u < NW; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = rb * kFRows + st * 16 + 4 * g + r;
+        if (row < B) dst[(int64_t)row * D + (wave * NW + u) * 16 + r16] = acc_dx[st * NW + u][r];
+      }
+  if (L2) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float s = hsum[r];
+#pragma unroll
+      for (int o = 1; o <= 8; o <<= 1) s += __shfl_xor(s, o, 64);
+      const int row = row_base + 4 * g + r;
+      if (r16 == 0 && row < B) a.rs_part[((int64_t)TRANS * gridDim.y + blockIdx.y) * B + row] = s;
+    }
+  }
+}
+template <int KS, int EN>
+__global__ __launch_bounds__(256, (wide_waves<KS, EN>())) void infonce_bwd_wide_kernel(
+    FusedArgs a, int B, int cps, float beta, float wf, float wb, float log2b) {
+  // two tiles and the four G strips
+  __shared__ __attribute__((aligned(1024))) bf16_t sm[2 * kFCols * KS * 32 + 4 * kFCols * 16];
+  bf16_t* Gt = sm + 2 * kFCols * KS * 32;
+  if (blockIdx.z) infonce_bwd_wide<KS, EN, 1>(a, B, cps, beta, wf, wb, log2b, sm, Gt);
+  else infonce_bwd_wide<KS, EN, 0>(a, B, cps, beta, wf, wb, log2b, sm, Gt);
 }
 
 // Both gradients in one pass (D = 64): a workgroup of 16 wavefronts owns 256
@@ -1164,19 +1389,25 @@ static int bwd_resident_wgs(int D, int en) {
   k = en == kEnL2 ? reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnL2, 0>)     \
     : en == kEnL2sq ? reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnL2sq, 0>) \
                     : reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnDot, 0>)
+#define CRL_WIDE_PTR(KS_)                                                             \
+  k = en == kEnL2 ? reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnL2>)   \
+    : en == kEnL2sq ? reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnL2sq>) \
+                    : reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnDot>)
   switch (D) {
     case 32: CRL_BWD_PTR(1); break;
     case 64: CRL_BWD_PTR(2); break;
-    case 128: CRL_BWD_PTR(4); break;
-    case 256: CRL_BWD_PTR(8); break;
+    case 128: CRL_WIDE_PTR(4); break;
+    case 256: CRL_WIDE_PTR(8); break;
     default: return 0;
   }
+#undef CRL_WIDE_PTR
 #undef CRL_BWD_PTR
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0) != hipSuccess)
     return 0;
+  if (D >= 128) per_cu = std::min(per_cu, D >= 256 || en != kEnDot ? 2 : 3);  // wide_waves
   return per_cu * cus;
 }
 
@@ -1202,6 +1433,10 @@ static int fused_bwd2_splits(int B, int D, int en) {
   const int cps = cols_per_split(B, best);
   return (B + cps - 1) / cps;
 }
+
+#define CRL_NARROW_DISPATCH(KS_, BODY)                     \
+  if (D == 32) { constexpr int KS_ = 1; BODY; }            \
+  else { constexpr int KS_ = 2; BODY; }
 
 #define CRL_EN_DISPATCH(EN_, BODY)                                  \
   switch (en) {                                                      \
@@ -1277,13 +1512,25 @@ hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int lo
   dim3 grid(nrb, S);
   const double bw_flops = 2.0 * B * B * D;  // G . Y per pass; the tile recompute is not counted
   const double bw_bytes = 2.0 * 2.0 * B * D + 4.0 * 2.0 * B + 4.0 * (double)S * B * (D + 1.0);
-  for (int pass = 0; pass < (one ? 0 : 2); ++pass) {
+  if (D >= 128) {  // both passes in one launch
+    KTimer t = timing_begin("infonce_bwd_wide_kernel", 2.0 * bw_flops, 2.0 * bw_bytes, s);
+    const dim3 grid2(nrb, S, 2);
+    if (D == 128) {
+      CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<4, EN><<<grid2, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
+    } else {
+      CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<8, EN><<<grid2, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
+    }
+    timing_end(t);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  for (int pass = 0; pass < (one || D >= 128 ? 0 : 2); ++pass) {
     KTimer t = timing_begin(pass ? "infonce_bwd_kernel<cols>" : "infonce_bwd_kernel<rows>",
                             bw_flops, bw_bytes, s);
     if (pass == 0) {
-      CRL_EN_DISPATCH(EN, CRL_FUSED_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 0><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
+      CRL_EN_DISPATCH(EN, CRL_NARROW_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 0><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
     } else {
-      CRL_EN_DISPATCH(EN, CRL_FUSED_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 1><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
+      CRL_EN_DISPATCH(EN, CRL_NARROW_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 1><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
     }
     timing_end(t);
     hipError_t e = hipGetLastError();
