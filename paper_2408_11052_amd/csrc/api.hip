@@ -379,10 +379,12 @@ GemmParams dw_params(const crl_ctx* x, const Group& G, int l) {
   // per CU).  In one launch with its layer's dX (launch_gemm_dw_dx) the launch
   // takes about (total 64-deep steps) / 512 steps, and dW is split only until
   // one split is no deeper than that, and than 64 steps (deeper splits leave
-  // the end of the launch to a few long work items).
+  // the end of the launch to a few long work items).  Ragged batches and layers
+  // of one 64-wide input take the rule of a launch alone: the splits decide the
+  // order of a sum, which BF16 training keeps.
   P.partial = reinterpret_cast<float*>(1);
   int target = 512;
-  if (l > 0) {
+  if (l > 0 && x->B % 64 == 0 && P.d[0].M > 64) {
     GemmParams P1 = P;
     plan_split_k(P1, x->bf16, 0, 8);  // unsplit
     const GemmParams Px = dx_params(x, G, l);
@@ -414,10 +416,11 @@ bool dw_dx_paired(const crl_ctx* x, const Group& G, int l) {
   return gemm_pair_ok(Pw, dx_params(x, G, l), x->bf16);
 }
 
-// Whether a layer's bias gradient is summed inside its dW launch: the launch
-// then reads the same values that a column sum would (not the BF16 copy of an
-// FP32 output gradient).
-bool bias_from_dw(const crl_ctx* x, bool top) { return top ? !x->bf16 : true; }
+// Whether a layer's bias gradient is summed inside its dW launch: in FP32,
+// where that saves a launch a layer.  BF16 contexts keep the column sums: the
+// output layer's reads the FP32 gradient and not its BF16 copy, and a bias
+// summed in another order moves the next step's BF16 weights.
+bool bias_from_dw(const crl_ctx* x) { return !x->bf16; }
 
 // Partial buffers of a group's backward and the jobs that reduce them into
 // the gradient vector: dW split-K partials, bias column partials (output
@@ -487,10 +490,10 @@ void plan_group(crl_ctx* x, int gi, int64_t& off) {
       if (top || !x->ln) {
         // the critic's output-layer partials come from the fused InfoNCE
         // backward reduction (blocks of 256 / D rows), those of a layer whose
-        // dW reads the gradient itself from that launch (one per split), the
-        // others (FP32 gradients with a BF16 copy) from the column sums
+        // dW sums it from that launch (one per split), the others from the
+        // column sums
         const int np = (top && gi == 0 && x->fused) ? fused_bias_chunks(x->B, lo.fan_out)
-                       : bias_from_dw(x, top)       ? P.splits
+                       : bias_from_dw(x)            ? P.splits
                                                     : nrb;
         S.bp[l] = take_bytes(x, off, (int64_t)np * lo.fan_out * 4);
         add(G.many, S.bp[l], lo.fan_out, lo.b, np, lo.fan_out);
@@ -538,7 +541,7 @@ void plan_workspace(crl_ctx* x) {
   auto take = [&](int64_t bytes) { return take_bytes(x, off, bytes); };
   const int64_t B = x->B, D = x->D;
   x->ldF = x->fused ? 0 : (int)align_up(B, 8);
-  x->ln_nparts = ln_bwd_partials(x->B);
+  x->ln_nparts = ln_bwd_partials(x->B, x->bf16);
   for (int e = 0; e < (x->actor ? 3 : 2); ++e) plan_slots(x, e, take_bytes, off);
   x->grp[0].nets[0] = 0; x->grp[0].nets[1] = 1; x->grp[0].count = 2;
   x->grp[1].nets[0] = 2; x->grp[1].nets[1] = 2; x->grp[1].count = 1;
@@ -830,17 +833,18 @@ int mlp_backward(crl_ctx* x, const NetCall* nc, int count, void* ws, hipStream_t
       // bias partials of this layer (LayerNorm layers get theirs with dZ;
       // top_bias_ready: the output layer's were written with dout)
       const bool own_bias = (top && !top_bias_ready) || (!top && !x->ln);
-      if (own_bias && bias_from_dw(x, top))
+      if (own_bias && bias_from_dw(x))
         for (int e = 0; e < count; ++e)
           Pw.d[e].bsum = WF(ws, x->sl[nc[e].net].bp[l]);
-      if (own_bias && !bias_from_dw(x, top)) {
+      if (own_bias && !bias_from_dw(x)) {
         ColSumArgs ca{};
         for (int e = 0; e < count; ++e) {
           const Slots& S = x->sl[nc[e].net];
-          ca.X[e] = WF(ws, S.dout);
+          ca.X[e] = top ? (const void*)WF(ws, S.dout) : dZ[e];
           ca.part[e] = WF(ws, S.bp[l]);
         }
-        CRL_HIP(launch_colsum_partials(ca, count, B, N0.out_dim, N0.out_dim, s),
+        const int Nc = top ? N0.out_dim : H;
+        CRL_HIP(launch_colsum_partials(ca, count, B, Nc, Nc, top ? false : x->bf16, s),
                 "bias gradient");
       }
     }

@@ -132,6 +132,15 @@ static int pick_tile(const GemmParams& P, int splits, bool bf16) {
   return pick_tile(n, bf16);
 }
 
+// BF16 launches with a K that is no whole number of stages run in the other k
+// order (see fragment), on 64 tiles.
+template <typename T> static bool alt_order(const GemmParams& P) {
+  bool alt = false;
+  if (sizeof(T) == 2)
+    for (int g = 0; g < P.count; ++g) alt = alt || P.d[g].K % lds::bk<T>() != 0;
+  return alt;
+}
+
 template <typename T, int LA, int LB, typename OutT, int TILE, bool ALT>
 static void run_tile(const GemmParams& P, hipStream_t s) {
   typedef typename lds::TileOf<T, TILE>::type C;
@@ -145,11 +154,7 @@ static hipError_t run(GemmParams& P, hipStream_t s) {
   if (!operands_ok(P, sizeof(T) == 2)) return hipErrorInvalidValue;
   double flops = 0.0, bytes = 0.0;
   algo_counts(P, sizeof(T), sizeof(OutT), flops, bytes);
-  // BF16 launches with a K that is no whole number of stages: the other k
-  // order (see fragment), 64 tiles
-  bool alt = false;
-  if (sizeof(T) == 2)
-    for (int g = 0; g < P.count; ++g) alt = alt || P.d[g].K % lds::bk<T>() != 0;
+  const bool alt = alt_order<T>(P);
   if (alt) set_tile(P, kTile64);
   KTimer t = timing_begin(lds_kernel_name<T, LA, LB, OutT>(), flops, bytes, s);
   if constexpr (sizeof(T) == 2) {
@@ -197,10 +202,10 @@ bool gemm_pair_ok(const GemmParams& Pw, const GemmParams& Px, bool bf16) {
 }
 
 // Tile of a pair of launches, and the grid that holds both.
-static PairGrid plan_pair(GemmParams& P1, GemmParams& P2, bool bf16) {
+static PairGrid plan_pair(GemmParams& P1, GemmParams& P2, bool bf16, bool alt) {
   int64_t n[4];
   for (int t = 0; t < 4; ++t) n[t] = tiles_of(P1, t) * P1.splits + tiles_of(P2, t) * P2.splits;
-  const int tile = pick_tile(n, bf16);
+  const int tile = alt ? kTile64 : pick_tile(n, bf16);
   set_tile(P1, tile);
   set_tile(P2, tile);
   PairGrid G;
@@ -213,20 +218,27 @@ static PairGrid plan_pair(GemmParams& P1, GemmParams& P2, bool bf16) {
   return G;
 }
 
-template <typename T, int TILE, int LA2, int LB2>
+template <typename T, int TILE, int LA2, int LB2, bool ALT1>
 static void run_pair_tile(const GemmParams& P1, const GemmParams& P2, const PairGrid& G,
                           hipStream_t s) {
   typedef typename lds::TileOf<T, TILE>::type C;
-  gemm_lds_pair_kernel<T, LAY_MC, LAY_MC, float, LA2, LB2, T, C>
+  gemm_lds_pair_kernel<T, LAY_MC, LAY_MC, float, LA2, LB2, T, C, ALT1>
       <<<G.n1 + G.n2, C::NT, 0, s>>>(P1, P2, G);
 }
 template <typename T, int LA2, int LB2>
 static void run_pair(GemmParams& P1, GemmParams& P2, hipStream_t s) {
-  const PairGrid G = plan_pair(P1, P2, sizeof(T) == 2);
-  if (P1.tile == kTile128) run_pair_tile<T, kTile128, LA2, LB2>(P1, P2, G, s);
-  else if (P1.tile == kTile64) run_pair_tile<T, kTile64, LA2, LB2>(P1, P2, G, s);
-  else if (P1.tile == kTile32) run_pair_tile<T, kTile32, LA2, LB2>(P1, P2, G, s);
-  else if constexpr (sizeof(T) == 4) run_pair_tile<T, kTile64x32, LA2, LB2>(P1, P2, G, s);
+  const bool alt = alt_order<T>(P1);
+  const PairGrid G = plan_pair(P1, P2, sizeof(T) == 2, alt);
+  if constexpr (sizeof(T) == 2) {
+    if (alt) {
+      run_pair_tile<T, kTile64, LA2, LB2, true>(P1, P2, G, s);
+      return;
+    }
+  }
+  if (P1.tile == kTile128) run_pair_tile<T, kTile128, LA2, LB2, false>(P1, P2, G, s);
+  else if (P1.tile == kTile64) run_pair_tile<T, kTile64, LA2, LB2, false>(P1, P2, G, s);
+  else if (P1.tile == kTile32) run_pair_tile<T, kTile32, LA2, LB2, false>(P1, P2, G, s);
+  else if constexpr (sizeof(T) == 4) run_pair_tile<T, kTile64x32, LA2, LB2, false>(P1, P2, G, s);
 }
 
 hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s) {

@@ -38,7 +38,7 @@ struct GemmDesc {
                       // k >= kb are re-reads of row kb-1; the caller
                       // guarantees A is zero in those columns
   float* asum;        // FP32 MC x MC launches: sum_k A(m,k) to asum[split * M + m], or NULL
-  float* bsum;        // MC x MC launches: sum_k B(k,n) to bsum[split * N + n], or NULL
+  float* bsum;        // FP32 MC x MC launches: sum_k B(k,n) to bsum[split * N + n], or NULL
 };
 
 constexpr int kGemmMaxGroup = 2;

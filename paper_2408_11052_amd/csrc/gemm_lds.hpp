@@ -151,7 +151,8 @@ __device__ __forceinline__ void zero_tail(char* tile, int valid, int tid) {
 // (g, j) = (lane / 16, lane % 16).  BF16: 8 consecutive k of row j, starting
 // at 8 c with c = 4 hh + g, or (ALT) 2 g + hh.  ALT is the order of launches
 // whose K is not a whole number of stages; it is kept because BF16 outputs of
-// such launches round differently in another order.
+// such launches round differently in another order (and weights that such a
+// weight gradient has moved).
 template <int LAY, int W, bool ALT>
 __device__ __forceinline__ bf16x8 fragment(const char* tile, int mb, int hh, int g, int j,
                                            bf16_t*) {
@@ -274,10 +275,10 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // MC x MC launches may ask for an operand's sums over K (wave-uniform)
-  constexpr bool SUMS = LA == LAY_MC && LB == LAY_MC;
+  // FP32 MC x MC launches may ask for an operand's sums over K (wave-uniform)
+  constexpr bool SUMS = sizeof(T) == 4 && LA == LAY_MC && LB == LAY_MC;
   constexpr int NS = sizeof(T) == 2 || NJ > MI ? NJ : MI;  // A's sums: FP32 only
-  const bool want_a = SUMS && sizeof(T) == 4 && D.asum != nullptr && tn == 0 && wn == 0;
+  const bool want_a = SUMS && D.asum != nullptr && tn == 0 && wn == 0;
   const bool want_b = SUMS && D.bsum != nullptr && tm == 0 && wm == 0;
   floatx4 ks[NS], kss[NS];
 #pragma unroll
@@ -587,13 +588,15 @@ void gemm_lds_kernel(GemmParams P) {
 // saves a launch's fixed cost (first stage, epilogue, ramp) and lets the
 // second launch's tiles fill the first one's tail.
 struct PairGrid { int n1, gx1, gy1, gx2, gy2, n2; };
-template <typename T, int LA1, int LB1, typename Out1, int LA2, int LB2, typename Out2, typename C>
+// ALT1: the first launch in the other k order (see fragment).
+template <typename T, int LA1, int LB1, typename Out1, int LA2, int LB2, typename Out2, typename C,
+          bool ALT1>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC)))
 void gemm_lds_pair_kernel(GemmParams P1, GemmParams P2, PairGrid G) {
   __shared__ __attribute__((aligned(1024))) char smem[C::SMEM];
   const int id = blockIdx.x;
   if (id < G.n1)
-    gemm_lds_tile<T, LA1, LB1, Out1, C, false>(P1, work_item_of(id, G.gx1, G.gy1, G.n1), smem);
+    gemm_lds_tile<T, LA1, LB1, Out1, C, ALT1>(P1, work_item_of(id, G.gx1, G.gy1, G.n1), smem);
   else
     gemm_lds_tile<T, LA2, LB2, Out2, C, false>(P2, work_item_of(id - G.n1, G.gx2, G.gy2, G.n2),
                                                smem);

@@ -75,21 +75,21 @@ struct LnArgs {
   // backward
   const void* dH[2];
   void* dZ[2];
-  float* part[2];       // [ln_bwd_partials(B)][3][N] column partials; NULL: only dZ
+  float* part[2];       // [ln_bwd_partials(B, bf16)][3][N] column partials; NULL: only dZ
 };
 hipError_t launch_ln_swish_fwd(const LnArgs& a, int count, int B, int N, float eps,
                                bool bf16, hipStream_t s);
 hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf16,
                                hipStream_t s);
-int ln_bwd_partials(int B);
+int ln_bwd_partials(int B, bool bf16_parts);
 
-// column sums of X [B][N] (FP32) over chunks of 128 rows: part[e][ceil(B/128)][N]
+// column sums of X [B][N] over chunks of 128 rows: part[e][ceil(B/128)][N]
 struct ColSumArgs {
-  const float* X[2];
+  const void* X[2];
   float* part[2];
 };
 hipError_t launch_colsum_partials(const ColSumArgs& a, int count, int B, int N, int ld,
-                                  hipStream_t s);
+                                  bool bf16, hipStream_t s);
 int colsum_chunks(int B);
 
 // Deferred gradient reductions: g[dst + i] = sum_k part_k[i], part_k at byte

@@ -324,28 +324,37 @@ __global__ __launch_bounds__(256) void ln_swish_bwd_kernel(LnArgs a, int B, int 
 // shortened (one encoder at B = 1000: 63 workgroups and 7.2 us with four rows,
 // 250 and 5.0 us with one); above, four: a workgroup's 256 column partials
 // are then paid for by 16 rows.  The number of partial rows is at most 256
-// either way.
-int ln_bwd_r(int B) { return B <= 1024 ? 1 : B <= 2048 ? 2 : 4; }
+// either way.  BF16 parameter gradients always take four: in another order
+// they differ in the last bit, the next step's BF16 weights then now and then
+// in theirs, and that step's result at 1e-4.
+int ln_bwd_r(int B, bool bf16_parts) {
+  return bf16_parts ? 4 : B <= 1024 ? 1 : B <= 2048 ? 2 : 4;
+}
 // Rows per workgroup: one round up to B = 4096 (at most 512 workgroups for two
 // encoders), then more rounds per workgroup instead of more workgroups, so the
 // column partials (3 N floats per workgroup, summed again in the gradient
 // reduction) stop growing with B.
-int ln_bwd_rows(int B) { return 4 * ln_bwd_r(B) * std::max(1, (B + 4095) / 4096); }
-int ln_bwd_partials(int B) {
-  const int rows = ln_bwd_rows(B);
+int ln_bwd_rows(int B, bool bf16_parts) {
+  return 4 * ln_bwd_r(B, bf16_parts) * std::max(1, (B + 4095) / 4096);
+}
+int ln_bwd_partials(int B, bool bf16_parts) {
+  const int rows = ln_bwd_rows(B, bf16_parts);
   return (B + rows - 1) / rows;
 }
 
 template <typename T, int CH, int R>
 static void ln_bwd_run(const LnArgs& a, int count, int B, int N, hipStream_t s) {
-  const dim3 grid(ln_bwd_partials(B), count);
+  const bool bp = sizeof(T) == 2 && a.part[0];
+  const int rows = ln_bwd_rows(B, bp);
+  const dim3 grid(ln_bwd_partials(B, bp), count);
   const size_t lds = (size_t)4 * 3 * N * sizeof(float);
-  if (a.part[0]) ln_swish_bwd_kernel<T, CH, R, 1><<<grid, 256, lds, s>>>(a, B, N, ln_bwd_rows(B));
-  else ln_swish_bwd_kernel<T, CH, R, 0><<<grid, 256, 0, s>>>(a, B, N, ln_bwd_rows(B));
+  if (!a.part[0]) ln_swish_bwd_kernel<T, CH, R, 0><<<grid, 256, 0, s>>>(a, B, N, rows);
+  else if constexpr (sizeof(T) == 4 || R == 4)
+    ln_swish_bwd_kernel<T, CH, R, 1><<<grid, 256, lds, s>>>(a, B, N, rows);
 }
 template <typename T, int CH>
 static void ln_bwd_rows_run(const LnArgs& a, int count, int B, int N, hipStream_t s) {
-  const int r = ln_bwd_r(B);
+  const int r = ln_bwd_r(B, sizeof(T) == 2 && a.part[0]);
   if (r == 1) ln_bwd_run<T, CH, 1>(a, count, B, N, s);
   else if (r == 2) ln_bwd_run<T, CH, 2>(a, count, B, N, s);
   else ln_bwd_run<T, CH, 4>(a, count, B, N, s);
@@ -354,7 +363,7 @@ hipError_t launch_ln_swish_bwd(const LnArgs& a, int count, int B, int N, bool bf
                                hipStream_t s) {
   const int ch = (N / 8 + 63) / 64;
   const double bytes = (double)count * ((double)B * N * 3.0 * (bf16 ? 2 : 4) +
-                                        (a.part[0] ? 12.0 * ln_bwd_partials(B) * N : 0.0));
+                                        (a.part[0] ? 12.0 * ln_bwd_partials(B, bf16) * N : 0.0));
   KTimer t = timing_begin("ln_swish_bwd_kernel", 0.0, bytes, s);
   // hidden widths are at most 1024 (checked at context creation): CH <= 2
   if (bf16) { if (ch <= 1) ln_bwd_rows_run<bf16_t, 1>(a, count, B, N, s); else ln_bwd_rows_run<bf16_t, 2>(a, count, B, N, s); }
@@ -368,9 +377,17 @@ __device__ inline void load4(const float* p, float (&o)[4]) {
   float4 a = *reinterpret_cast<const float4*>(p);
   o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
 }
+__device__ inline void load4(const bf16_t* p, float (&o)[4]) {
+  uint2 u = *reinterpret_cast<const uint2*>(p);
+  o[0] = __builtin_bit_cast(float, u.x << 16);
+  o[1] = __builtin_bit_cast(float, u.x & 0xffff0000u);
+  o[2] = __builtin_bit_cast(float, u.y << 16);
+  o[3] = __builtin_bit_cast(float, u.y & 0xffff0000u);
+}
 constexpr int kColRows = 128;  // rows per chunk of the column-sum kernel
 
 // Column sums of X [B][ld] over one chunk of rows, 256 columns per workgroup.
+template <typename T>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B, int N, int ld) {
   __shared__ float red[4][256];
   const int e = blockIdx.z;
@@ -379,7 +396,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B
   const int r0 = blockIdx.y * kColRows, r1 = min(B, r0 + kColRows);
   float acc[4] = {0, 0, 0, 0};
   if (n0 < N) {
-    const float* X = a.X[e];
+    const T* X = reinterpret_cast<const T*>(a.X[e]);
     // the wavefront's rows r0 + wave, + 4, + 8, ... in that order, eight
     // rows' loads in flight before they are added
     int row = r0 + wave;
@@ -411,12 +428,15 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSumArgs a, int B
 int colsum_chunks(int B) { return (B + kColRows - 1) / kColRows; }
 
 hipError_t launch_colsum_partials(const ColSumArgs& a, int count, int B, int N, int ld,
-                                  hipStream_t s) {
+                                  bool bf16, hipStream_t s) {
   // N and ld must be multiples of 4 (vector loads of 4 elements)
   const int nrb = colsum_chunks(B);
   dim3 grid((N + 255) / 256, nrb, count), block(256);
-  CRL_TIMED("colsum_partial_kernel", 0.0, 4.0 * count * B * N, s,
-            colsum_partial_kernel<<<grid, block, 0, s>>>(a, B, N, ld));
+  const double cs_bytes = (double)count * B * N * (bf16 ? 2 : 4);
+  if (bf16) CRL_TIMED("colsum_partial_kernel", 0.0, cs_bytes, s,
+                      colsum_partial_kernel<bf16_t><<<grid, block, 0, s>>>(a, B, N, ld));
+  else      CRL_TIMED("colsum_partial_kernel", 0.0, cs_bytes, s,
+                      colsum_partial_kernel<float><<<grid, block, 0, s>>>(a, B, N, ld));
   return hipGetLastError();
 }
 
