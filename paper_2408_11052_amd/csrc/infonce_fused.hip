@@ -698,16 +698,24 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 // all four G strips (64 rows) by its quarter of the tile's columns, so the
 // tile is read once per workgroup in that product rather than once per wave.
 //
-// What binds it is the mix per 64 x 64 tile: 64 MFMAs a wave, about 19 vector
-// instructions an entry and 192 KB of LDS reads a workgroup, with two
-// workgroups on a CU.  Tiles go from global memory straight into LDS, one
-// ahead: staged through registers they held 32 of a lane's 256, which spilled,
-// and left each step of the tile product waiting for its own fragments; now
-// the next step's fragments are read during a step, and the entries of a tile
-// that touches neither an edge nor the diagonal run without branches.
-// B=16384, D=256, L2: 703 -> 635 us for both passes (the vector
-// instructions alone take some 430, the MFMAs 250); B=4096, D=128, L2: 56 -> 46 us; B=1500,
-// D=128: 23 -> 15 us, one launch instead of two.
+// What binds it is the mix per 64 x 64 tile: 64 MFMAs a wave, 17 vector
+// instructions an entry (of 13 that an L2 entry itself takes) and 192 KB of LDS
+// reads a workgroup, with two workgroups on a CU.  Vector instructions and
+// MFMAs of a SIMD's two waves overlap only in part (a wave of FMAs beside one
+// that keeps the matrix core busy runs at half its rate), and their times
+// added, 390 and 250 us at B=16384, D=256, are about the time measured.  Four
+// waves on a SIMD (workgroups of eight, half the columns each) or one tile's
+// product, another's entries and a third's dX interleaved in one wave took as
+// long or longer.
+// Tiles go from global memory straight into LDS, one ahead: staged through
+// registers they held 32 of a lane's 256, which spilled, and left each step
+// waiting for its own fragments.  Fragments are read a step ahead of the tile
+// product and two ahead of the dX product, the first of them before the
+// barrier; the tile and column loads, and the entries of a tile that touches
+// neither an edge nor the diagonal, run without branches.
+// B=16384, D=256, L2: 703 -> 625 us for both passes; B=8192, D=256, dot: 150;
+// B=8192, D=128, dot: 115 -> 90; B=1500, D=128: 23 -> 15, one launch instead of
+// two.
 //
 // A tile row is 2 D bytes unpadded, its 16-byte chunk c in slot c ^ wide_swz(row):
 // the row operand's 16-byte reads (16 lanes at a time: rows 0-3 and 12-15 of
@@ -726,14 +734,19 @@ __device__ __forceinline__ void wide_tile_load(const bf16_t* __restrict__ Y, int
   const char* base = reinterpret_cast<const char*>(Y) + (int64_t)j0 * RB;
   const int rl = lane / CPR, c = lane % CPR;
   const int last = B - 1 - j0;  // the tile's last row that exists (>= 0)
+  if (last >= kFCols - 1) {
+    base += wave * 16 * RB;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int r = wave * 16 + i * NR;  // the block's first row
-    const int slot = (c ^ wide_swz(i * NR + rl)) * 16;
-    if (last >= kFCols - 1)
-      load_to_lds(base + r * RB, rl * RB + slot, dst + (wave * NI + i) * 1024);
-    else
-      load_to_lds(base, min(r + rl, last) * RB + slot, dst + (wave * NI + i) * 1024);
+    for (int i = 0; i < NI; ++i)
+      load_to_lds(base + i * 1024, rl * RB + (c ^ wide_swz(i * NR + rl)) * 16,
+                  dst + (wave * NI + i) * 1024);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = i * NR + rl;
+      load_to_lds(base, min(wave * 16 + r, last) * RB + (c ^ wide_swz(r)) * 16,
+                  dst + (wave * NI + i) * 1024);
+    }
   }
 }
 
@@ -804,6 +817,16 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
   // per-lane column values of a tile (columns j0 + jb*16 + r16)
   struct ColVals { float lse[4], ny[4]; };
   auto col_load = [&](ColVals& cvv, int j0) {
+    if (j0 + kFCols <= B) {
+      const float* __restrict__ lp = lseY + j0;
+      const float* __restrict__ np = nY + j0;
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) {
+        cvv.lse[jb] = lp[jb * 16 + r16];
+        cvv.ny[jb] = L2 ? np[jb * 16 + r16] : 0.f;
+      }
+      return;
+    }
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb) {
       const int col = min(j0 + jb * 16 + r16, B - 1);  // past the edge: masked
@@ -811,7 +834,6 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
       cvv.ny[jb] = L2 ? nY[col] : 0.f;
     }
   };
-  const int jlast = c0 + ((c1 - c0 - 1) / kFCols) * kFCols;
   ColVals cvals, cpf;
   if (c0 < c1) col_load(cvals, c0);
   // byte offsets in a tile: row operand chunk (t ^ (its row's swizzle)), t the
@@ -833,12 +855,10 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
     wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    col_load(cpf, min(j0 + kFCols, jlast));
-    if (j0 + kFCols < c1)
-      wide_tile_load<D>(Yb, j0 + kFCols, B, lds0 + (buf ^ 1) * TILE * 2, wave, lane);
     const char* __restrict__ Yt = reinterpret_cast<const char*>(Ys + buf * TILE);
     floatx4 acc[4];
     {
+      // fragments a step ahead of their products (two ahead spills)
       bf16x8 b[2][4];
       auto frags = [&](int ks) {
 #pragma unroll
@@ -849,12 +869,18 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
 #pragma unroll
       for (int jb = 0; jb < 4; ++jb) acc[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
       frags(0);
+      if (j0 + kFCols < c1) {
+        col_load(cpf, j0 + kFCols);
+        wide_tile_load<D>(Yb, j0 + kFCols, B, lds0 + (buf ^ 1) * TILE * 2, wave, lane);
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         if (ks + 1 < KS) frags(ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int jb = 0; jb < 4; ++jb)
           acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], b[ks & 1][jb], acc[jb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     float sh_b[4], k_b[4];
@@ -903,16 +929,21 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
     };
     if (edge || diag) entries(true);
     else entries(false);
-    // every wave reads all four strips: a workgroup barrier (LDS only)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
     // dX[64 rows][this wave's D/4 columns] += G[64][64] . Y[64][D/4 columns];
-    // the A fragments of the four strips are read once and each used NW times
+    // the A fragments of the four strips are read once and each used NW times,
+    // the B fragments two steps ahead
+    bf16x8 y[3], ga[2][4];
+    auto yread = [&](int i) {
+      const int kk = i / NW, u = i % NW;
+      v4s hq[2];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      bf16x8 ga[4];
+      for (int q = 0; q < 2; ++q)
+        hq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_v4s*)(Yt + ot[u] + (kk * 32 + 4 * q) * 2 * D));
+      v8s yv = {hq[0][0], hq[0][1], hq[0][2], hq[0][3], hq[1][0], hq[1][1], hq[1][2], hq[1][3]};
+      y[i % 3] = __builtin_bit_cast(bf16x8, yv);
+    };
+    auto gread = [&](int kk) {
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
         v4s gq[2];
@@ -923,21 +954,27 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
               (lds_v4s*)(Gt + st * STRIP + gt_at(krow, 4 * (r16 & 3))));
         }
         v8s gv8 = {gq[0][0], gq[0][1], gq[0][2], gq[0][3], gq[1][0], gq[1][1], gq[1][2], gq[1][3]};
-        ga[st] = __builtin_bit_cast(bf16x8, gv8);
+        ga[kk][st] = __builtin_bit_cast(bf16x8, gv8);
       }
+    };
+    yread(0);
+    yread(1);
+    // every wave reads all four strips: a workgroup barrier (LDS only)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    gread(0);
 #pragma unroll
-      for (int u = 0; u < NW; ++u) {
-        v4s hq[2];
+    for (int i = 0; i < 2 * NW; ++i) {
+      if (i + 2 < 2 * NW) yread(i + 2);
+      if (i == (NW > 2 ? NW - 2 : 0)) gread(1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-          hq[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_v4s*)(Yt + ot[u] + (kk * 32 + 4 * q) * 2 * D));
-        v8s yv = {hq[0][0], hq[0][1], hq[0][2], hq[0][3], hq[1][0], hq[1][1], hq[1][2], hq[1][3]};
-#pragma unroll
-        for (int st = 0; st < 4; ++st)
-          acc_dx[st * NW + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              ga[st], __builtin_bit_cast(bf16x8, yv), acc_dx[st * NW + u], 0, 0, 0);
-      }
+      for (int st = 0; st < 4; ++st)
+        acc_dx[st * NW + i % NW] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            ga[i / NW][st], y[i % 3], acc_dx[st * NW + i % NW], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
     cvals = cpf;
   }
