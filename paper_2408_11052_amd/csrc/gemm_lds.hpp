@@ -231,12 +231,6 @@ __device__ __forceinline__ void mma_half(floatx4 (&acc)[C::MI][C::NJ], const flo
 }
 // acc + (sum over K of one fragment's rows), through a product with ones; rhs:
 // the fragment is the column operand
-__device__ __forceinline__ floatx4 mma_ones(bf16x8 x, floatx4 acc, bool rhs) {
-  const __bf16 o = (__bf16)1.f;
-  const bf16x8 one = {o, o, o, o, o, o, o, o};
-  return rhs ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x, acc, 0, 0, 0)
-             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, one, acc, 0, 0, 0);
-}
 __device__ __forceinline__ floatx4 mma_ones(floatx4 x, floatx4 acc, bool rhs) {
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -251,6 +245,17 @@ __device__ __forceinline__ float square_sum(floatx4 x, float s) {
 }
 __device__ __forceinline__ float square_sum(bf16x8, float s) { return s; }  // not used
 }  // namespace lds
+
+// Wait states between MFMAs and the first vector instruction that reads their
+// results, where a branch may lie between.  (The compiler inserts them, but
+// counts back along one path into a block: behind a skipped branch it left 5
+// or 6 of the 10 that a 16x16x4 FP32 MFMA needs, and 3 gave wrong sums.)
+template <typename A> __device__ __forceinline__ void settle(A& acc) {
+  floatx4* v = reinterpret_cast<floatx4*>(&acc);
+  asm volatile("s_nop 15" : "+v"(v[0]));
+#pragma unroll
+  for (int i = 1; i < (int)(sizeof(A) / sizeof(floatx4)); ++i) asm volatile("" : "+v"(v[i]));
+}
 
 // One workgroup's work item wi of launch P; smem holds C::SMEM bytes.
 template <typename T, int LA, int LB, typename OutT, typename C, bool ALT>
@@ -277,7 +282,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
 
   // FP32 MC x MC launches may ask for an operand's sums over K (wave-uniform)
   constexpr bool SUMS = sizeof(T) == 4 && LA == LAY_MC && LB == LAY_MC;
-  constexpr int NS = sizeof(T) == 2 || NJ > MI ? NJ : MI;  // A's sums: FP32 only
+  constexpr int NS = NJ > MI ? NJ : MI;
   const bool want_a = SUMS && D.asum != nullptr && tn == 0 && wn == 0;
   const bool want_b = SUMS && D.bsum != nullptr && tm == 0 && wm == 0;
   floatx4 ks[NS], kss[NS];
@@ -336,10 +341,9 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     // the first tile row (B) or column (A) of the launch
     auto sum_k = [&](const typename Frag<T>::type (&a)[MI], const typename Frag<T>::type (&b)[NJ]) {
       if constexpr (SUMS) {
-        if constexpr (sizeof(T) == 4)
-          if (want_a)
+        if (want_a)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) ks[i] = mma_ones(a[i], ks[i], false);
+          for (int i = 0; i < MI; ++i) ks[i] = mma_ones(a[i], ks[i], false);
         if (want_b)
 #pragma unroll
           for (int j = 0; j < NJ; ++j) ks[j] = mma_ones(b[j], ks[j], true);
@@ -357,6 +361,8 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
       }
     };
     auto flush = [&]() {
+      settle(acc);
+      if constexpr (SUMS) settle(ks);
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -441,16 +447,15 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
   }
   if constexpr (SUMS) {
     // every column (A) or row (B) of a ones product holds the sum
-    if constexpr (sizeof(T) == 4)
-      if (want_a && (lane & 15) == 0) {
+    if (want_a && (lane & 15) == 0) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = m0 + (wm * MI + i) * 16 + (lane >> 4) * 4 + r;
-            if (row < D.M) D.asum[(int64_t)wi.split * D.M + row] = ks[i][r];
-          }
-      }
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + (wm * MI + i) * 16 + (lane >> 4) * 4 + r;
+          if (row < D.M) D.asum[(int64_t)wi.split * D.M + row] = ks[i][r];
+        }
+    }
     if (want_b && lane < 16) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
