@@ -911,6 +911,11 @@ hipError_t launch_lse_merge(const LseMergeArgs& a, int count, int B, hipStream_t
 // mean of term[] (Forward-Backward, DPO, IPO, SPPO).
 // With nparts > 0 each thread first merges its columns' (max, sum) partials in
 // part order into c: one launch (4.5 us) less where the columns are few.
+// Latency is all it costs: four rows' loads go out together, and the last six
+// levels of the tree run inside a wavefront (B=16384 9.8 -> 8.4 us, B=4096 4.6
+// -> 4.2).  Joined to lse_merge_kernel (its last workgroup takes the loss) it
+// cost as much as the two launches from B=1500 on: 8.9 us at B=4096, 23 at
+// B=16384, mostly the workgroups' counting.
 __global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ r,
                                                     float* __restrict__ c,
                                                     const float* __restrict__ diag,
@@ -921,56 +926,80 @@ __global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ r,
                                                     const float* __restrict__ col_m,
                                                     const float* __restrict__ col_s, int nparts) {
   __shared__ float sh[7][1024];
+  constexpr int NR = 4;  // rows in flight per thread
+  const int tid = threadIdx.x;
   float acc[6] = {0, 0, 0, 0, 0, 0}, cmp[6] = {0, 0, 0, 0, 0, 0};
   float bad = 0.f;
   const bool pairwise = loss >= CRL_LOSS_FB;
-  for (int i = threadIdx.x; i < B; i += 1024) {
-    const float ri = r[i], di = diag[i];
-    float ci;
-    if (nparts > 0) {
-      float m = -INFINITY, sum = 0.f;
-#pragma unroll 4
-      for (int p = 0; p < nparts; ++p)
-        lse_merge(m, sum, col_m[(int64_t)p * B + i], col_s[(int64_t)p * B + i]);
-      ci = m + __logf(sum);
-      c[i] = ci;
-    } else {
-      ci = c[i];
+  for (int i0 = tid; i0 < B; i0 += NR * 1024) {
+    float rv[NR], cv[NR], dv[NR], tv[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const int i = min(i0 + k * 1024, B - 1);
+      rv[k] = r[i];
+      dv[k] = diag[i];
+      cv[k] = nparts > 0 ? 0.f : c[i];
+      tv[k] = pairwise ? term[i] : 0.f;
     }
-    float o = 0.f;
-    if (loss == CRL_LOSS_FLATNCE_FWD) { const float x = ri - di; o = __expf(x - x); }
-    else if (loss == CRL_LOSS_FLATNCE_BWD) { const float x = ci - di; o = __expf(x - x); }
-    else if (pairwise) o = term[i];
-    float t[6] = {ri - di, ci - di, ri * ri, ri, ci, o};
 #pragma unroll
-    for (int k = 0; k < 6; ++k) kahan_add(acc[k], cmp[k], t[k]);
-    if (!isfinite(ri) || !isfinite(ci) || !isfinite(di) || !isfinite(o)) bad += 1.f;
+    for (int k = 0; k < NR; ++k) {
+      const int i = i0 + k * 1024;
+      if (i >= B) break;
+      const float ri = rv[k], di = dv[k];
+      float ci = cv[k];
+      if (nparts > 0) {
+        float m = -INFINITY, sum = 0.f;
+#pragma unroll 4
+        for (int p = 0; p < nparts; ++p)
+          lse_merge(m, sum, col_m[(int64_t)p * B + i], col_s[(int64_t)p * B + i]);
+        ci = m + __logf(sum);
+        c[i] = ci;
+      }
+      float o = tv[k];
+      if (loss == CRL_LOSS_FLATNCE_FWD) { const float x = ri - di; o = __expf(x - x); }
+      else if (loss == CRL_LOSS_FLATNCE_BWD) { const float x = ci - di; o = __expf(x - x); }
+      const float t[6] = {ri - di, ci - di, ri * ri, ri, ci, o};
+#pragma unroll
+      for (int q = 0; q < 6; ++q) kahan_add(acc[q], cmp[q], t[q]);
+      if (!isfinite(ri) || !isfinite(ci) || !isfinite(di) || !isfinite(o)) bad += 1.f;
+    }
   }
+  float v[7];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) sh[k][threadIdx.x] = acc[k] - cmp[k];
-  sh[6][threadIdx.x] = bad;
+  for (int q = 0; q < 6; ++q) v[q] = acc[q] - cmp[q];
+  v[6] = bad;
+#pragma unroll
+  for (int q = 0; q < 7; ++q) sh[q][tid] = v[q];
   __syncthreads();
-  for (int w = 512; w >= 1; w >>= 1) {
-    if ((int)threadIdx.x < w)
+  for (int w = 512; w >= 64; w >>= 1) {
+    if (tid < w)
 #pragma unroll
-      for (int k = 0; k < 7; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + w];
+      for (int q = 0; q < 7; ++q) {
+        v[q] += sh[q][tid + w];
+        sh[q][tid] = v[q];
+      }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (tid >= 64) return;
+#pragma unroll
+  for (int w = 32; w >= 1; w >>= 1)
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] += __shfl_down(v[q], w, 64);
+  if (tid == 0) {
     const float inv = 1.f / (float)B;
-    const float lf = sh[0][0] * inv, lb = sh[1][0] * inv, lp = beta * sh[2][0] * inv;
+    const float lf = v[0] * inv, lb = v[1] * inv, lp = beta * v[2] * inv;
     float obj;
     if (loss == CRL_LOSS_FWD) obj = lf;
     else if (loss == CRL_LOSS_SYM) obj = lf + lb;
     else if (loss == CRL_LOSS_BWD) obj = lb;
-    else obj = sh[5][0] * inv;
+    else obj = v[5] * inv;
     loss_out[0] = obj + lp;
     loss_out[1] = lf;
     loss_out[2] = lb;
     loss_out[3] = lp;
-    loss_out[4] = sh[3][0] * inv;
-    loss_out[5] = sh[4][0] * inv;
-    loss_out[6] = sh[6][0];
+    loss_out[4] = v[3] * inv;
+    loss_out[5] = v[4] * inv;
+    loss_out[6] = v[6];
     loss_out[7] = obj;
     if (advance) *advance += 1;
   }
