@@ -54,26 +54,38 @@ __device__ inline int geom_count(const uint64_t* __restrict__ thr, const GeomPro
 // One sample's encoder inputs from its rows (one wavefront, lane-strided):
 // x_sa = [s, a, 0...], x_g = [g, 0...], x_sg = [s, g, 0...] (x_sg optional).
 // With s_row == nullptr every column is 0 (no sample could be drawn).
+// The copy is bound by latency: the loads of 128 columns go out together, and
+// the state's are shared by x_sa and x_sg.
 template <typename T>
 __device__ inline void write_inputs(const float* s_row, const float* a_row, const float* g_row,
                                     int d_s, int d_a, int d_g, int64_t b, int lane,
                                     T* __restrict__ x_sa, int ld_sa, T* __restrict__ x_g, int ld_g,
                                     T* __restrict__ x_sg, int ld_sg) {
+  constexpr int UN = 2;
   const bool ok = s_row != nullptr;
-  for (int c = lane; c < ld_sa; c += 64) {
-    float v = 0.f;
-    if (ok) v = c < d_s ? s_row[c] : (c < d_s + d_a ? a_row[c - d_s] : 0.f);
-    x_sa[b * ld_sa + c] = Store<T>::from_f(v);
-  }
-  for (int c = lane; c < ld_g; c += 64)
-    x_g[b * ld_g + c] = Store<T>::from_f(ok && c < d_g ? g_row[c] : 0.f);
-  if (x_sg) {
-    for (int c = lane; c < ld_sg; c += 64) {
-      float v = 0.f;
-      if (ok) v = c < d_s ? s_row[c] : (c < d_s + d_g ? g_row[c - d_s] : 0.f);
-      x_sg[b * ld_sg + c] = Store<T>::from_f(v);
+  const int n_sa = ok ? d_s + d_a : 0;
+  const int n_sg = ok && x_sg ? d_s + d_g : 0;
+  const int n_g = ok ? d_g : 0;
+  if (!x_sg) ld_sg = 0;
+  const float g0 = lane < n_g ? g_row[lane] : 0.f;
+  for (int c0 = lane; c0 < max(ld_sa, ld_sg); c0 += 64 * UN) {
+    float sa[UN], sg[UN];
+#pragma unroll
+    for (int i = 0; i < UN; ++i) {
+      const int c = c0 + 64 * i;
+      sa[i] = c < n_sa ? *(c < d_s ? s_row + c : a_row + (c - d_s)) : 0.f;
+      sg[i] = c >= d_s && c < n_sg ? g_row[c - d_s] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < UN; ++i) {
+      const int c = c0 + 64 * i;
+      if (c < ld_sa) x_sa[b * ld_sa + c] = Store<T>::from_f(sa[i]);
+      if (c < ld_sg) x_sg[b * ld_sg + c] = Store<T>::from_f(c < d_s ? sa[i] : sg[i]);
     }
   }
+  if (lane < ld_g) x_g[b * ld_g + lane] = Store<T>::from_f(g0);
+  for (int c = lane + 64; c < ld_g; c += 64)
+    x_g[b * ld_g + c] = Store<T>::from_f(c < n_g ? g_row[c] : 0.f);
 }
 
 }  // namespace crl
