@@ -5,8 +5,8 @@
 
 namespace crl {
 
-// One wavefront per sample: draw (e, t, k), then copy the rows.
-template <typename T>
+// S samples per wavefront: draw (e, t, k), then copy the rows.
+template <typename T, int S>
 __global__ __launch_bounds__(256) void relabel_kernel(
     const float* __restrict__ obs, const float* __restrict__ act, int E, int T_,
     int d_s, int d_a, int d_g, int goal_lo, uint64_t seed, const int64_t* __restrict__ step,
@@ -14,25 +14,38 @@ __global__ __launch_bounds__(256) void relabel_kernel(
     T* __restrict__ x_sa, int ld_sa, T* __restrict__ x_g, int ld_g,
     T* __restrict__ x_sg, int ld_sg) {
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= B) return;
+  const int b0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * S;
+  if (b0 >= B) return;
+  const int n = min(S, B - b0);
   const GeomProbe probe = geom_prefetch(thr, T_ - 2, lane);
-  uint64_t x[4] = {(uint64_t)b, (uint64_t)(*step), 0ull, 0ull};
+  uint64_t x[4] = {(uint64_t)(b0 + min(lane, S - 1)), (uint64_t)(*step), 0ull, 0ull};
   philox4x64_10(x, seed, 0ull);
-  const int e = (int)__umul64hi(x[0], (uint64_t)E);
-  const int t = (int)__umul64hi(x[1], (uint64_t)(T_ - 1));
-  const int km1 = geom_count(thr, probe, x[2], lane);  // k - 1
-  const int tg = min(t + 1 + km1, T_ - 1);
-  if (lane == 0) {
-    idx[3 * b + 0] = e;
-    idx[3 * b + 1] = t;
-    idx[3 * b + 2] = tg;
+  const int el = (int)__umul64hi(x[0], (uint64_t)E);
+  const int tl = (int)__umul64hi(x[1], (uint64_t)(T_ - 1));
+  uint64_t w2[S];
+  int km1[S];  // k - 1
+#pragma unroll
+  for (int s = 0; s < S; ++s) w2[s] = lane_value(x[2], s);
+  geom_counts<S>(thr, probe, w2, lane, km1);
+  const float *s_row[S], *a_row[S], *g_row[S];
+  int gl = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int t = lane_value(tl, s);
+    const int tg = min(t + 1 + km1[s], T_ - 1);
+    const int64_t ep = (int64_t)lane_value(el, s) * T_;
+    s_row[s] = obs + (ep + t) * d_s;
+    a_row[s] = act + (ep + t) * d_a;
+    g_row[s] = obs + (ep + tg) * d_s + goal_lo;
+    gl = lane == s ? tg : gl;
   }
-  const float* s_row = obs + ((int64_t)e * T_ + t) * d_s;
-  const float* a_row = act + ((int64_t)e * T_ + t) * d_a;
-  const float* g_row = obs + ((int64_t)e * T_ + tg) * d_s + goal_lo;
-  write_inputs<T>(s_row, a_row, g_row, d_s, d_a, d_g, b, lane, x_sa, ld_sa, x_g, ld_g, x_sg,
-                  ld_sg);
+  if (lane < n) {
+    idx[3 * (b0 + lane) + 0] = el;
+    idx[3 * (b0 + lane) + 1] = tl;
+    idx[3 * (b0 + lane) + 2] = gl;
+  }
+  write_inputs<T, S>(s_row, a_row, g_row, d_s, d_a, d_g, b0, n, lane, x_sa, ld_sa, x_g,
+                     ld_g, x_sg, ld_sg);
 }
 
 hipError_t launch_relabel(const float* obs, const float* act, int E, int T, int d_s,
@@ -40,20 +53,26 @@ hipError_t launch_relabel(const float* obs, const float* act, int E, int T, int 
                           const int64_t* step, const uint64_t* thr, int B,
                           int32_t* idx, void* x_sa, int ld_sa, void* x_g, int ld_g,
                           void* x_sg, int ld_sg, bool bf16, hipStream_t s) {
-  dim3 grid((B + 3) / 4), block(256);
+  const int per = relabel_samples(B);
+  dim3 grid((B + 4 * per - 1) / (4 * per)), block(256);
   const double es = bf16 ? 2.0 : 4.0;
   const double bytes = (double)B * (4.0 * (d_s + d_a + d_g + (x_sg ? d_s + d_g : 0)) +
                                     es * (ld_sa + ld_g + (x_sg ? ld_sg : 0)) + 12.0);
-  if (bf16)
-    CRL_TIMED("relabel_kernel", 0.0, bytes, s,
-      relabel_kernel<bf16_t><<<grid, block, 0, s>>>(obs, act, E, T, d_s, d_a, d_g, goal_lo,
-        seed, step, thr, B, idx, (bf16_t*)x_sa, ld_sa, (bf16_t*)x_g, ld_g,
-        (bf16_t*)x_sg, ld_sg));
-  else
-    CRL_TIMED("relabel_kernel", 0.0, bytes, s,
-      relabel_kernel<float><<<grid, block, 0, s>>>(obs, act, E, T, d_s, d_a, d_g, goal_lo,
-        seed, step, thr, B, idx, (float*)x_sa, ld_sa, (float*)x_g, ld_g,
-        (float*)x_sg, ld_sg));
+#define CRL_RELABEL(T_, S_)                                                              \
+  CRL_TIMED("relabel_kernel", 0.0, bytes, s,                                             \
+            relabel_kernel<T_, S_><<<grid, block, 0, s>>>(                               \
+                obs, act, E, T, d_s, d_a, d_g, goal_lo, seed, step, thr, B, idx, (T_*)x_sa, \
+                ld_sa, (T_*)x_g, ld_g, (T_*)x_sg, ld_sg))
+  if (bf16) {
+    if (per == 1) CRL_RELABEL(bf16_t, 1);
+    else if (per == 2) CRL_RELABEL(bf16_t, 2);
+    else CRL_RELABEL(bf16_t, 4);
+  } else {
+    if (per == 1) CRL_RELABEL(float, 1);
+    else if (per == 2) CRL_RELABEL(float, 2);
+    else CRL_RELABEL(float, 4);
+  }
+#undef CRL_RELABEL
   return hipGetLastError();
 }
 

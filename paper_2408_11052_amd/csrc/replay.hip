@@ -30,6 +30,12 @@ __device__ __forceinline__ void scatter_rows(V* __restrict__ buf, const V* __res
   }
 }
 
+// n mod C, in 32 bits where they hold n (the 64-bit remainder takes longer than
+// the rest of a row's arithmetic)
+__device__ __forceinline__ int ring_first(int64_t n, int C) {
+  return n >> 31 ? (int)(n % C) : (int)((uint32_t)n % (uint32_t)C);
+}
+
 // kInsRows consecutive (step u, env e) rows of the chunk per wavefront: a row's
 // obs and act words go to ring row (count + u) mod C of env e, its trajectory
 // id beside them.  The chunk is read in order (rows of one step are
@@ -49,10 +55,7 @@ __global__ __launch_bounds__(256) void replay_insert_kernel(
   const int nr = min(kInsRows, U * E - r0);
   if (nr <= 0) return;
   const int id = lane < nr ? ntraj[r0 + lane] : 0;
-  const int64_t cnt = *count;
-  // 32 bits where they hold the count: the 64-bit remainder takes longer than
-  // the rest of a row's arithmetic
-  const int first = cnt >> 31 ? (int)(cnt % C) : (int)((uint32_t)cnt % (uint32_t)C);
+  const int first = ring_first(*count, C);
   int64_t dst[kInsRows];
   int u = r0 / E, e = r0 - u * E;
 #pragma unroll
@@ -80,13 +83,14 @@ __global__ __launch_bounds__(256) void replay_insert_kernel(
   }
 }
 
-// One wavefront per sample.  size = min(count, C) steps are stored, logical
+// S samples per wavefront.  size = min(count, C) steps are stored, logical
 // index i (0 = oldest) at ring row (count - size + i) mod C.  Draw e, i and
 // the offset k, then clip i + k to the last step of i's trajectory: the
 // lanes compare 64 ids at a time against i's, and the first differing one
 // ends the run.  k averages 1 / (1 - gamma), so this is one or two probes of
-// 256 contiguous bytes for most samples.
-template <typename T>
+// 256 contiguous bytes for most samples; the first of each goes out with its
+// own id.
+template <typename T, int S>
 __global__ __launch_bounds__(256) void ring_relabel_kernel(
     const float* __restrict__ obs, const float* __restrict__ act,
     const int32_t* __restrict__ traj, int E, int C, const int64_t* __restrict__ count,
@@ -95,52 +99,73 @@ __global__ __launch_bounds__(256) void ring_relabel_kernel(
     T* __restrict__ x_sa, int ld_sa, T* __restrict__ x_g, int ld_g,
     T* __restrict__ x_sg, int ld_sg) {
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= B) return;
+  const int b0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * S;
+  if (b0 >= B) return;
+  const int n = min(S, B - b0);
   const int64_t cnt = *count;
   const int size = (int)(cnt < (int64_t)C ? cnt : (int64_t)C);
   if (size < 2) {  // nothing to draw: (-1, -1, -1) and zero rows
-    if (lane == 0) {
-      idx[3 * b + 0] = -1;
-      idx[3 * b + 1] = -1;
-      idx[3 * b + 2] = -1;
-    }
-    write_inputs<T>(nullptr, nullptr, nullptr, d_s, d_a, d_g, b, lane, x_sa, ld_sa, x_g, ld_g,
-                    x_sg, ld_sg);
+    if (lane < 3 * n) idx[3 * b0 + lane] = -1;
+    const int64_t b = b0;
+    for (int c = lane; c < n * ld_sa; c += 64) x_sa[b * ld_sa + c] = T(0);
+    for (int c = lane; c < n * ld_g; c += 64) x_g[b * ld_g + c] = T(0);
+    if (x_sg)
+      for (int c = lane; c < n * ld_sg; c += 64) x_sg[b * ld_sg + c] = T(0);
     return;
   }
   const GeomProbe probe = geom_prefetch(thr, n_thr, lane);
-  const int base = (int)((cnt - size) % C);  // ring row of logical index 0
-  uint64_t x[4] = {(uint64_t)b, (uint64_t)(*step), 0ull, 0ull};
+  const int base = ring_first(cnt - size, C);  // ring row of logical index 0
+  uint64_t x[4] = {(uint64_t)(b0 + min(lane, S - 1)), (uint64_t)(*step), 0ull, 0ull};
   philox4x64_10(x, seed, 0ull);
-  const int e = (int)__umul64hi(x[0], (uint64_t)E);
-  const int i = (int)__umul64hi(x[1], (uint64_t)(size - 1));
-  const int km1 = geom_count(thr, probe, x[2], lane);  // k - 1
-  const int32_t* __restrict__ tr = traj + (int64_t)e * C;
+  const int el = (int)__umul64hi(x[0], (uint64_t)E);
+  const int il = (int)__umul64hi(x[1], (uint64_t)(size - 1));
   auto ring_row = [&](int j) { int q = base + j; return q >= C ? q - C : q; };
-  const int32_t tid = tr[ring_row(i)];
-  const int lim = min(i + 1 + km1, size - 1);
-  int tg = lim;
-  for (int j0 = i + 1; j0 <= lim; j0 += 64) {
-    const int j = j0 + lane;
-    const bool other = j <= lim && tr[ring_row(j)] != tid;
-    const uint64_t m = __ballot(other);
-    if (m) {
-      tg = j0 + (int)__builtin_ctzll(m) - 1;
-      break;
+  uint64_t w2[S];
+  int km1[S];  // k - 1
+#pragma unroll
+  for (int s = 0; s < S; ++s) w2[s] = lane_value(x[2], s);
+  geom_counts<S>(thr, probe, w2, lane, km1);
+  const float *s_row[S], *a_row[S], *g_row[S];
+  int32_t tid[S], ids[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int i = lane_value(il, s), lim = min(i + 1 + km1[s], size - 1);
+    const int32_t* __restrict__ tr = traj + (int64_t)lane_value(el, s) * C;
+    tid[s] = tr[ring_row(i)];
+    ids[s] = tr[ring_row(min(i + 1 + lane, lim))];
+  }
+  int rl = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int e = lane_value(el, s), i = lane_value(il, s);
+    const int32_t* __restrict__ tr = traj + (int64_t)e * C;
+    const int lim = min(i + 1 + km1[s], size - 1);
+    int tg = lim;
+    int32_t id = ids[s];
+    for (int j0 = i + 1;;) {
+      const uint64_t m = __ballot(j0 + lane <= lim && id != tid[s]);
+      if (m) {
+        tg = j0 + (int)__builtin_ctzll(m) - 1;
+        break;
+      }
+      j0 += 64;
+      if (j0 > lim) break;
+      id = tr[ring_row(min(j0 + lane, lim))];
     }
+    const int ri = ring_row(i), rg = ring_row(tg);
+    rl = lane == 2 * s ? ri : lane == 2 * s + 1 ? rg : rl;
+    s_row[s] = obs + ((int64_t)e * C + ri) * d_s;
+    a_row[s] = act + ((int64_t)e * C + ri) * d_a;
+    g_row[s] = obs + ((int64_t)e * C + rg) * d_s + goal_lo;
   }
-  const int ri = ring_row(i), rg = ring_row(tg);
-  if (lane == 0) {
-    idx[3 * b + 0] = e;
-    idx[3 * b + 1] = ri;
-    idx[3 * b + 2] = rg;
+  const int ri = __shfl(rl, 2 * (lane & (S - 1)), 64), rg = __shfl(rl, 2 * (lane & (S - 1)) + 1, 64);
+  if (lane < n) {
+    idx[3 * (b0 + lane) + 0] = el;
+    idx[3 * (b0 + lane) + 1] = ri;
+    idx[3 * (b0 + lane) + 2] = rg;
   }
-  const float* s_row = obs + ((int64_t)e * C + ri) * d_s;
-  const float* a_row = act + ((int64_t)e * C + ri) * d_a;
-  const float* g_row = obs + ((int64_t)e * C + rg) * d_s + goal_lo;
-  write_inputs<T>(s_row, a_row, g_row, d_s, d_a, d_g, b, lane, x_sa, ld_sa, x_g, ld_g, x_sg,
-                  ld_sg);
+  write_inputs<T, S>(s_row, a_row, g_row, d_s, d_a, d_g, b0, n, lane, x_sa, ld_sa, x_g,
+                     ld_g, x_sg, ld_sg);
 }
 
 hipError_t launch_replay_insert(float* obs, float* act, int32_t* traj, int E, int C, int d_s,
@@ -170,20 +195,26 @@ hipError_t launch_ring_relabel(const float* obs, const float* act, const int32_t
                                const uint64_t* thr, int n_thr, int B, int32_t* idx, void* x_sa,
                                int ld_sa, void* x_g, int ld_g, void* x_sg, int ld_sg, bool bf16,
                                hipStream_t s) {
-  dim3 grid((B + 3) / 4), block(256);
+  const int per = relabel_samples(B);
+  dim3 grid((B + 4 * per - 1) / (4 * per)), block(256);
   const double es = bf16 ? 2.0 : 4.0;
   const double bytes = (double)B * (4.0 * (d_s + d_a + d_g + (x_sg ? d_s + d_g : 0)) +
                                     es * (ld_sa + ld_g + (x_sg ? ld_sg : 0)) + 12.0);
-  if (bf16)
-    CRL_TIMED("ring_relabel_kernel", 0.0, bytes, s,
-      ring_relabel_kernel<bf16_t><<<grid, block, 0, s>>>(obs, act, traj, E, C, count, d_s, d_a,
-        d_g, goal_lo, seed, step, thr, n_thr, B, idx, (bf16_t*)x_sa, ld_sa, (bf16_t*)x_g, ld_g,
-        (bf16_t*)x_sg, ld_sg));
-  else
-    CRL_TIMED("ring_relabel_kernel", 0.0, bytes, s,
-      ring_relabel_kernel<float><<<grid, block, 0, s>>>(obs, act, traj, E, C, count, d_s, d_a,
-        d_g, goal_lo, seed, step, thr, n_thr, B, idx, (float*)x_sa, ld_sa, (float*)x_g, ld_g,
-        (float*)x_sg, ld_sg));
+#define CRL_RING_RELABEL(T_, S_)                                                          \
+  CRL_TIMED("ring_relabel_kernel", 0.0, bytes, s,                                         \
+            ring_relabel_kernel<T_, S_><<<grid, block, 0, s>>>(                           \
+                obs, act, traj, E, C, count, d_s, d_a, d_g, goal_lo, seed, step, thr, n_thr, B, \
+                idx, (T_*)x_sa, ld_sa, (T_*)x_g, ld_g, (T_*)x_sg, ld_sg))
+  if (bf16) {
+    if (per == 1) CRL_RING_RELABEL(bf16_t, 1);
+    else if (per == 2) CRL_RING_RELABEL(bf16_t, 2);
+    else CRL_RING_RELABEL(bf16_t, 4);
+  } else {
+    if (per == 1) CRL_RING_RELABEL(float, 1);
+    else if (per == 2) CRL_RING_RELABEL(float, 2);
+    else CRL_RING_RELABEL(float, 4);
+  }
+#undef CRL_RING_RELABEL
   return hipGetLastError();
 }
 
