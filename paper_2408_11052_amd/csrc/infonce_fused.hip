@@ -244,10 +244,6 @@ __device__ __forceinline__ float exp_diff(float x, float m) {
   return __builtin_amdgcn_exp2f((x - m) * kL2E);
 }
 
-// Per workgroup: 64 rows (wave w: rows 16w + 4g + r of lane (r16, g), r < 4)
-// against the 64-column tiles of one column split.  Tiles inside the batch
-// on every side skip the masking, and only the tile that holds a wave's
-// diagonal entries looks for them (both are wave-uniform branches).
 // The 16 x 64 tile F = X[16 rows] . Y[64 columns]^T of one wave: four
 // 16-column accumulators, the K loop outside, so that the four products of
 // a K step are independent and their B fragments can be read together.
@@ -268,19 +264,100 @@ __device__ __forceinline__ void tile_product(floatx4 (&acc)[4], const bf16x8 (&x
   }
 }
 
+// Tiles of wide representations (D >= 128), loaded straight into LDS.
+// A tile row is 2 D bytes unpadded, its 16-byte chunk c in slot c ^ wide_swz(row):
+// the row operand's 16-byte reads (16 lanes at a time: rows 0-3 and 12-15 of
+// one chunk, 4-11 of the next) and the transpose reads (a half-wave: rows
+// 4q..4q+3 and 8 + 4q.., two chunks) each fall on 16 distinct 16-byte banks.
+__device__ __forceinline__ int wide_swz(int row) { return 2 * (row & 3) + (row & 8); }
+
+// One wave's share of the 64-row tile at row j0 of Y [B][D] into LDS address
+// dst: blocks of 1 KB (NR rows), 16 rows a wave.  Rows past B re-read row B-1;
+// the entries they meet are masked.
+template <int D>
+__device__ __forceinline__ void wide_tile_load(const bf16_t* __restrict__ Y, int j0, int B,
+                                               uint32_t dst, int wave, int lane) {
+  constexpr int RB = 2 * D, NR = 1024 / RB, NI = 16 / NR;  // row bytes, rows per block, blocks
+  constexpr int CPR = RB / 16;                             // chunks per row
+  const char* base = reinterpret_cast<const char*>(Y) + (int64_t)j0 * RB;
+  const int rl = lane / CPR, c = lane % CPR;
+  const int last = B - 1 - j0;  // the tile's last row that exists (>= 0)
+  dst = __builtin_amdgcn_readfirstlane(dst + wave * NI * 1024);
+  if (last >= kFCols - 1) {
+    base += wave * 16 * RB;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      load_to_lds(base + i * 1024, rl * RB + (c ^ wide_swz(i * NR + rl)) * 16,
+                  dst + i * 1024);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = i * NR + rl;
+      load_to_lds(base, min(wave * 16 + r, last) * RB + (c ^ wide_swz(r)) * 16,
+                  dst + i * 1024);
+    }
+  }
+}
+
+// byte offset in a tile of row r16 (of any 16) and step ks's chunk of lane group
+// g, less 256 (ks / 4)
+template <int D> __device__ __forceinline__ int wide_at(int r16, int ks, int g) {
+  return r16 * 2 * D + (((4 * (ks & 3) + g) ^ wide_swz(r16)) << 4);
+}
+
+// tile_product from such a tile, fragments a step ahead of their products
+template <int KS, typename F>
+__device__ __forceinline__ void wide_product(floatx4 (&acc)[4], const bf16x8 (&xa)[KS],
+                                             const char* __restrict__ Yt, const int (&oa)[4],
+                                             F&& between) {
+  bf16x8 b[2][4];
+  auto frags = [&](int ks) {
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb)
+      b[ks & 1][jb] = *reinterpret_cast<const bf16x8*>(Yt + oa[ks & 3] + (ks >> 2) * 256 +
+                                                       jb * 16 * 2 * KS * 32);
+  };
+#pragma unroll
+  for (int jb = 0; jb < 4; ++jb) acc[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  frags(0);
+  between();
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (ks + 1 < KS) frags(ks + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb)
+      acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], b[ks & 1][jb], acc[jb], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Occupancy targets (wavefronts per SIMD) that the register allocation must
 // meet: the forward's LDS holds three workgroups per CU at D = 256, the
 // backward's two.
 template <int KS> constexpr int fwd_waves() { return KS >= 8 ? 3 : 4; }
 template <int KS, int EN> constexpr int wide_waves() { return KS >= 8 || EN != kEnDot ? 2 : 3; }
 
+// Per workgroup: 64 rows (wave w: rows 16w + 4g + r of lane (r16, g), r < 4)
+// against the 64-column tiles of one column split.  Tiles inside the batch
+// on every side skip the masking, and only the tile that holds a wave's
+// diagonal entries looks for them (one wave-uniform branch).
+// What binds it is the entries: some 17 vector instructions each, three of them
+// exponentials or roots.  At D >= 128 the tile goes from global memory straight
+// into the one LDS tile while the entries of the tile before are formed, and
+// the tile product reads its fragments a step ahead: staged through registers,
+// with a branch for each masked sum, B=16384, D=256, L2 took 305 us, now 278;
+// B=8192, D=128, dot 62, now 57.  At D <= 64 the tile is a few registers; there
+// the branch-free entries alone gave 201 -> 187 us (B=16384, D=64, L2 without
+// the root, prep and merge included).
 template <int KS, int EN>
 __global__ __launch_bounds__(256, fwd_waves<KS>()) void infonce_fwd_kernel(FusedArgs a, int B, int cps) {
   constexpr bool L2 = EN != kEnDot;
   constexpr int D = KS * 32;
   constexpr int LDY = D + 16;
   constexpr int LDC = kFCols + 16;  // column-partial rows
-  __shared__ __attribute__((aligned(16))) bf16_t Ys[kFCols * LDY];
+  constexpr bool WIDE = KS >= 4;
+  __shared__ __attribute__((aligned(1024))) bf16_t Ys[kFCols * (WIDE ? D : LDY)];
   // column (max, sum) of each (wave, 4-row group) for the current tile
   __shared__ float cm_s[16][LDC], cs_s[16][LDC];
 
@@ -337,6 +414,58 @@ __global__ __launch_bounds__(256, fwd_waves<KS>()) void infonce_fwd_kernel(Fused
       a.col_s[(int64_t)rb * B + col] = cs;
     }
   };
+  // The entries of a tile, once F is in acc: the row states, the wave's share of
+  // the column partials.  special: the tile touches an edge or the diagonal.
+  auto entries = [&](const floatx4 (&acc)[4], const float (&nyv)[4], int j0, bool special) {
+    float f[4][4];
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float d;
+        f[jb][r] = energy_f<EN>(acc[jb][r], nx[r], nyv[jb], d);
+      }
+    if (special && j0 <= row_base && row_base < j0 + kFCols) {  // this wave's diagonal entries
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = row_base + 4 * g + r;
+          if (row == j0 + jb * 16 + r16 && row < c1 && rvalid[r]) a.diag[row] = f[jb][r];
+        }
+    }
+    if (special) {  // entries outside the batch or the split become -inf
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) {
+        const bool cv = j0 + jb * 16 + r16 < c1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[jb][r] = (cv && rvalid[r]) ? f[jb][r] : -INFINITY;
+      }
+    }
+    // rows: online (max, sum)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float nm = max_nan(rm[r], max_nan(max_nan(f[0][r], f[1][r]), max_nan(f[2][r], f[3][r])));
+      float sr = rsum[r] * exp_diff(rm[r], nm);
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) sr += exp_diff(f[jb][r], nm);
+      if (special) sr = nm == -INFINITY ? 0.f : sr;  // nothing of this row seen yet
+      rsum[r] = sr;
+      rm[r] = nm;
+    }
+    // columns: (max, sum) over this lane's 4 rows, one entry per (wave, row
+    // group); the merge runs after the next barrier
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+      const float cm = max_nan(max_nan(f[jb][0], f[jb][1]), max_nan(f[jb][2], f[jb][3]));
+      float cs = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) cs += exp_diff(f[jb][r], cm);
+      if (special) cs = cm == -INFINITY ? 0.f : cs;
+      cm_s[wave * 4 + g][jb * 16 + r16] = cm;
+      cs_s[wave * 4 + g][jb * 16 + r16] = cs;
+    }
+  };
   // the prefetch is unconditional (clamped to the last tile) so the wait
   // before each LDS store covers exactly the previous fetch
   const int jlast = c0 + ((c1 - c0 - 1) / kFCols) * kFCols;
@@ -353,68 +482,53 @@ __global__ __launch_bounds__(256, fwd_waves<KS>()) void infonce_fwd_kernel(Fused
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb) nypf[jb] = j0 + jb * 16 + r16 < c1 ? base[jb * 16 + r16] : 0.f;
   };
-  if (c0 < c1) { tile_load<D>(pf, a.psi_b, c0, B, tid); ny_load(c0); }
+  const uint32_t lds0 = lds_address(Ys);
+  int oa[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) oa[t] = wide_at<D>(r16, t, g);
+  if (c0 < c1) {
+    if constexpr (WIDE) wide_tile_load<D>(a.psi_b, c0, B, lds0, wave, lane);
+    else tile_load<D>(pf, a.psi_b, c0, B, tid);
+    ny_load(c0);
+  }
   for (int j0 = c0; j0 < c1; j0 += kFCols) {
-    __syncthreads();
-    if (j0 > c0) flush_cols(j0 - kFCols);
-    tile_store_rows<D, LDY>(Ys, pf, tid);
-    float nyv[4];
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb) nyv[jb] = nypf[jb];
-    tile_load<D>(pf, a.psi_b, min(j0 + kFCols, jlast), B, tid);
-    ny_load(min(j0 + kFCols, jlast));
-    __syncthreads();
     floatx4 acc[4];
-    tile_product<KS>(acc, xa, Ys, r16, g);
-    float f[4][4];
+    float nyv[4];
+    if constexpr (WIDE) {
+      // the tile has arrived, and so have the previous tile's column partials
+      asm volatile("" ::: "memory");
+      wait_vm<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float d;
-        f[jb][r] = energy_f<EN>(acc[jb][r], nx[r], nyv[jb], d);
+      for (int jb = 0; jb < 4; ++jb) nyv[jb] = nypf[jb];
+      wide_product<KS>(acc, xa, reinterpret_cast<const char*>(Ys), oa, []() {});
+      if (j0 > c0) flush_cols(j0 - kFCols);
+      // every wave has read both: the next tile loads while this one's entries
+      // are formed
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (j0 + kFCols < c1) {
+        ny_load(j0 + kFCols);
+        wide_tile_load<D>(a.psi_b, j0 + kFCols, B, lds0, wave, lane);
       }
-    if (j0 <= row_base && row_base < j0 + kFCols) {  // this wave's diagonal entries
+    } else {
+      __syncthreads();
+      if (j0 > c0) flush_cols(j0 - kFCols);
+      tile_store_rows<D, LDY>(Ys, pf, tid);
 #pragma unroll
-      for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = row_base + 4 * g + r;
-          if (row == j0 + jb * 16 + r16 && row < c1 && rvalid[r]) a.diag[row] = f[jb][r];
-        }
+      for (int jb = 0; jb < 4; ++jb) nyv[jb] = nypf[jb];
+      tile_load<D>(pf, a.psi_b, min(j0 + kFCols, jlast), B, tid);
+      ny_load(min(j0 + kFCols, jlast));
+      __syncthreads();
+      tile_product<KS>(acc, xa, Ys, r16, g);
     }
-    const bool edge = !rows_full || j0 + kFCols > c1;
-    if (edge) {  // entries outside the batch or the split become -inf
-#pragma unroll
-      for (int jb = 0; jb < 4; ++jb) {
-        const bool cv = j0 + jb * 16 + r16 < c1;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) f[jb][r] = (cv && rvalid[r]) ? f[jb][r] : -INFINITY;
-      }
-    }
-    // rows: online (max, sum)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float nm = max_nan(rm[r], max_nan(max_nan(f[0][r], f[1][r]), max_nan(f[2][r], f[3][r])));
-      float sr = rsum[r] * exp_diff(rm[r], nm);
-#pragma unroll
-      for (int jb = 0; jb < 4; ++jb) sr += exp_diff(f[jb][r], nm);
-      if (edge) sr = nm == -INFINITY ? 0.f : sr;  // nothing of this row seen yet
-      rsum[r] = sr;
-      rm[r] = nm;
-    }
-    // columns: (max, sum) over this lane's 4 rows, one entry per (wave, row
-    // group); the merge runs after the next barrier
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb) {
-      const float cm = max_nan(max_nan(f[jb][0], f[jb][1]), max_nan(f[jb][2], f[jb][3]));
-      float cs = 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) cs += exp_diff(f[jb][r], cm);
-      if (edge) cs = cm == -INFINITY ? 0.f : cs;
-      cm_s[wave * 4 + g][jb * 16 + r16] = cm;
-      cs_s[wave * 4 + g][jb * 16 + r16] = cs;
-    }
+    if (!rows_full || j0 + kFCols > c1 || (j0 <= row_base && row_base < j0 + kFCols))
+      entries(acc, nyv, j0, true);
+    else
+      entries(acc, nyv, j0, false);
   }
   if (c0 < c1) {
     __syncthreads();
@@ -717,39 +831,6 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 // B=8192, D=128, dot: 115 -> 90; B=1500, D=128: 23 -> 15, one launch instead of
 // two.
 //
-// A tile row is 2 D bytes unpadded, its 16-byte chunk c in slot c ^ wide_swz(row):
-// the row operand's 16-byte reads (16 lanes at a time: rows 0-3 and 12-15 of
-// one chunk, 4-11 of the next) and the transpose reads (a half-wave: rows
-// 4q..4q+3 and 8 + 4q.., two chunks) each fall on 16 distinct 16-byte banks.
-__device__ __forceinline__ int wide_swz(int row) { return 2 * (row & 3) + (row & 8); }
-
-// One wave's share of the 64-row tile at row j0 of Y [B][D] into LDS address
-// dst: blocks of 1 KB (NR rows), 16 rows a wave.  Rows past B re-read row B-1;
-// the entries they meet are masked.
-template <int D>
-__device__ __forceinline__ void wide_tile_load(const bf16_t* __restrict__ Y, int j0, int B,
-                                               uint32_t dst, int wave, int lane) {
-  constexpr int RB = 2 * D, NR = 1024 / RB, NI = 16 / NR;  // row bytes, rows per block, blocks
-  constexpr int CPR = RB / 16;                             // chunks per row
-  const char* base = reinterpret_cast<const char*>(Y) + (int64_t)j0 * RB;
-  const int rl = lane / CPR, c = lane % CPR;
-  const int last = B - 1 - j0;  // the tile's last row that exists (>= 0)
-  if (last >= kFCols - 1) {
-    base += wave * 16 * RB;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      load_to_lds(base + i * 1024, rl * RB + (c ^ wide_swz(i * NR + rl)) * 16,
-                  dst + (wave * NI + i) * 1024);
-  } else {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = i * NR + rl;
-      load_to_lds(base, min(wave * 16 + r, last) * RB + (c ^ wide_swz(r)) * 16,
-                  dst + (wave * NI + i) * 1024);
-    }
-  }
-}
-
 template <int KS, int EN, int TRANS>
 __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int cps, float beta,
                                                  float wf, float wb, float log2b,
@@ -841,7 +922,7 @@ __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int 
   int oa[4], ot[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    oa[t] = r16 * 2 * D + (((4 * t + g) ^ wide_swz(r16)) << 4);
+    oa[t] = wide_at<D>(r16, t, g);
     const int tr = 8 * g + (r16 >> 2);  // + 4 q + 32 kk: the same swizzle
     const int ch = (wave * NW + (t < NW ? t : 0)) * 2 + ((r16 & 3) >> 1);
     ot[t] = tr * 2 * D + ((ch ^ wide_swz(tr)) << 4) + (r16 & 1) * 8;
@@ -1397,7 +1478,7 @@ static int fwd_resident_wgs(int D, int en) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0) != hipSuccess)
     return 0;
-  return per_cu * cus;
+  return std::min(per_cu, D >= 256 ? fwd_waves<8>() : fwd_waves<4>()) * cus;
 }
 
 // Column splits of the forward: fused_splits(B), or fewer where the kernel's
