@@ -570,8 +570,8 @@ void plan_workspace(crl_ctx* x) {
       x->upsi = take(B * D * 4);
     }
   } else {
-    // the one-pass backward (D = 64) indexes its partials by 256-row blocks
-    const int S = fused_bwd_one_pass(x->B, x->D)
+    // at D = 64 the backward indexes its partials by 256-row blocks
+    const int S = fused_bwd_blocks(x->B, x->D)
                       ? std::max(fused_splits(x->B), fused_bwd_splits(x->B))
                       : fused_splits(x->B);
     const int nrb = (x->B + 63) / 64;

@@ -24,6 +24,7 @@
 #include <cmath>
 
 #include "internal.hpp"
+#include <type_traits>
 
 namespace crl {
 
@@ -577,6 +578,9 @@ __device__ __forceinline__ int gt_at(int c, int e) {
   return (c & ~15) * 16 + t * 128 + (((c & 7) + 4 * t) & 7) * 16 + (e ^ (8 * t));
 }
 
+// The two passes at D <= 64, both in one launch (blockIdx.z; each writes its
+// own half of the partials): D=32, reduction included, B=65 13.3 -> 8.7 us,
+// B=9000 82.9 -> 72.3, D=64 B=8192 87.2 -> 75.7 against a launch each.
 // TRANS = 0: rows are phi, streamed operand psi -> partials of dphi.
 // TRANS = 1: rows are psi, streamed operand phi -> partials of dpsi.
 // Per 64-column tile: F (MFMA), G (or H) into the wave's own LDS strip, then
@@ -593,22 +597,39 @@ __device__ __forceinline__ int gt_at(int c, int e) {
 // transposed, [column][row], so that each lane stores its four rows of a
 // column as one 8-byte write; the transpose read gives back the row-major A
 // operand of the product.
-template <int KS, int EN, int TRANS>
-__global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B, int cps,
-                                                          float beta, float wf, float wb,
-                                                          float log2b) {
+template <int KS> constexpr int narrow_ldy() { return KS * 32 + 16; }
+constexpr int kStripLd = 16;  // transposed G strip: [64 columns][16 rows]
+// Sum over the 16 lanes of a row of 16, each quad's in lane order, then the
+// quads' pairwise: the order in which the one-pass kernel sums 16 rows of a
+// column (four rows of a lane, then the lane groups).
+__device__ __forceinline__ float sum16(float h) {
+  auto lane = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 decltype(ctrl)::value, 15, 15, true));
+  };
+  using std::integral_constant;
+  const float h0 = lane(h, integral_constant<int, 0x00>{}), h1 = lane(h, integral_constant<int, 0x55>{});
+  const float h2 = lane(h, integral_constant<int, 0xAA>{}), h3 = lane(h, integral_constant<int, 0xFF>{});
+  float s = ((h0 + h1) + h2) + h3;
+  s += lane(s, integral_constant<int, 0x141>{});  // the other quad of 8 lanes
+  s += lane(s, integral_constant<int, 0x140>{});  // the other half of 16
+  return s;
+}
+
+// BLK: partials of 256 columns with the one-pass kernel's sums, to the bit.
+template <int KS, int EN, int TRANS, bool BLK>
+__device__ __forceinline__ void infonce_bwd_narrow(const FusedArgs& a, int B, int cps, float beta,
+                                                   float wf, float wb, float log2b,
+                                                   bf16_t (&Ys)[2][kFCols * narrow_ldy<KS>()],
+                                                   bf16_t (&Gt)[4][kFCols * kStripLd]) {
   constexpr bool L2 = EN != kEnDot;
   constexpr int D = KS * 32;
-  constexpr int LDY = D + 16;
-  constexpr int LDG = 16;     // transposed G strip: [64 columns][16 rows]
+  constexpr int LDY = narrow_ldy<KS>();
   constexpr int NB = D / 16;  // 16-wide output blocks of dX
   static_assert(KS <= 2, "wider representations: infonce_bwd_wide_kernel");
   typedef short v4s __attribute__((ext_vector_type(4)));
   typedef short v8s __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) v4s lds_v4s;
-  // two tile buffers: the next tile is stored while this one is in use
-  __shared__ __attribute__((aligned(16))) bf16_t Ys[2][kFCols * LDY];
-  __shared__ __attribute__((aligned(16))) bf16_t Gt[4][kFCols * LDG];
 
   const bf16_t* Xb = TRANS ? a.psi_b : a.phi_b;
   const bf16_t* Yb = TRANS ? a.phi_b : a.psi_b;
@@ -737,7 +758,8 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (EN != kEnDot) h[r] *= wv[r];
-        hsum[r] += h[r];
+        if (BLK) asm("" : "+v"(h[r]));  // the sums take the rounded H: no contraction
+        hsum[r] += BLK && TRANS ? sum16(h[r]) : h[r];
       }
       uint2 w;
       w.x = pack2bf(h[0], h[1]);
@@ -798,12 +820,24 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float s = hsum[r];
+      if (!(BLK && TRANS))
 #pragma unroll
-      for (int o = 1; o <= 8; o <<= 1) s += __shfl_xor(s, o, 64);
+        for (int o = 1; o <= 8; o <<= 1) s += __shfl_xor(s, o, 64);
       const int row = row_base + 4 * g + r;
       if (r16 == 0 && row < B) a.rs_part[((int64_t)TRANS * gridDim.y + blockIdx.y) * B + row] = s;
     }
   }
+}
+
+template <int KS, int EN, bool BLK>
+__global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B, int cps,
+                                                          float beta, float wf, float wb,
+                                                          float log2b) {
+  // two tile buffers: the next tile is stored while this one is in use
+  __shared__ __attribute__((aligned(16))) bf16_t Ys[2][kFCols * narrow_ldy<KS>()];
+  __shared__ __attribute__((aligned(16))) bf16_t Gt[4][kFCols * kStripLd];
+  if (blockIdx.z) infonce_bwd_narrow<KS, EN, 1, BLK>(a, B, cps, beta, wf, wb, log2b, Ys, Gt);
+  else infonce_bwd_narrow<KS, EN, 0, BLK>(a, B, cps, beta, wf, wb, log2b, Ys, Gt);
 }
 
 // The two passes at D >= 128, both in one launch (blockIdx.z; each writes its
@@ -1516,33 +1550,16 @@ static int fused_fwd_splits(int B, int D, int en) {
   return (B + cps - 1) / cps;
 }
 
-// Resident workgroups of the rows pass of the two-pass backward (the columns
-// pass has the same resources).
+// Workgroups of one of the two backward passes that the device holds at once,
+// for the split rule: the waves on a SIMD (one of each workgroup on its CU) that
+// each kernel's registers leave, which is part of the rule (the splits decide
+// the order of the partial sums) and so stated here.
 static int bwd_resident_wgs(int D, int en) {
-  const void* k = nullptr;
-#define CRL_BWD_PTR(KS_)                                                              \
-  k = en == kEnL2 ? reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnL2, 0>)     \
-    : en == kEnL2sq ? reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnL2sq, 0>) \
-                    : reinterpret_cast<const void*>(&infonce_bwd_kernel<KS_, kEnDot, 0>)
-#define CRL_WIDE_PTR(KS_)                                                             \
-  k = en == kEnL2 ? reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnL2>)   \
-    : en == kEnL2sq ? reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnL2sq>) \
-                    : reinterpret_cast<const void*>(&infonce_bwd_wide_kernel<KS_, kEnDot>)
-  switch (D) {
-    case 32: CRL_BWD_PTR(1); break;
-    case 64: CRL_BWD_PTR(2); break;
-    case 128: CRL_WIDE_PTR(4); break;
-    case 256: CRL_WIDE_PTR(8); break;
-    default: return 0;
-  }
-#undef CRL_WIDE_PTR
-#undef CRL_BWD_PTR
-  int dev = 0, cus = 0, per_cu = 0;
+  const int per_cu = D >= 256 ? 2 : D >= 128 ? (en == kEnDot ? 3 : 2) : D >= 64 ? 4 : (en == kEnDot ? 6 : 4);
+  int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, 0) != hipSuccess)
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  if (D >= 128) per_cu = std::min(per_cu, D >= 256 || en != kEnDot ? 2 : 3);  // wide_waves
   return per_cu * cus;
 }
 
@@ -1568,10 +1585,6 @@ static int fused_bwd2_splits(int B, int D, int en) {
   const int cps = cols_per_split(B, best);
   return (B + cps - 1) / cps;
 }
-
-#define CRL_NARROW_DISPATCH(KS_, BODY)                     \
-  if (D == 32) { constexpr int KS_ = 1; BODY; }            \
-  else { constexpr int KS_ = 2; BODY; }
 
 #define CRL_EN_DISPATCH(EN_, BODY)                                  \
   switch (en) {                                                      \
@@ -1612,12 +1625,24 @@ hipError_t launch_fused_fwd(const FusedArgs& a, int B, int D, int energy, const 
   return launch_lse_merge(m, 2, B, s);
 }
 
-// The one-pass backward (D = 64) writes ceil(B / 256) partials per row of
-// dphi and of dpsi, B x 64 floats each; above kBothMaxSplits partials the
-// row and column passes run instead, whose partial count is bounded by
-// fused_splits (at most 16).
+// At D = 64 the partials of dphi and of dpsi are those of 256-row blocks,
+// ceil(B / 256) of B x 64 floats each; above kBothMaxSplits of them the passes
+// choose their splits, at most 16 (fused_splits).
 constexpr int kBothMaxSplits = 16;
-bool fused_bwd_one_pass(int B, int D) { return D == 64 && fused_bwd_splits(B) <= kBothMaxSplits; }
+bool fused_bwd_blocks(int B, int D) { return D == 64 && fused_bwd_splits(B) <= kBothMaxSplits; }
+
+// Such partials come from the one-pass kernel, a 256 x 256 block per workgroup
+// of a whole CU, or, equal to the bit, from the two passes with 256 columns a
+// workgroup: twice the entries, but 16 times the workgroups, each with a
+// quarter of the waves.  The passes are faster while the device holds all of
+// their workgroups at once (B up to 2816 on 256 CUs).  Reduction included, one
+// pass against two: dot B=333 16.7, 9.8 us; B=1000 18.5, 11.7; B=2048 20.9, 15.3;
+// B=2816 23.9, 23.5; B=4096 33.9, 34.4.  L2 B=333 23.0, 13.8; B=2048 29.1, 21.2;
+// B=3072 35.8, 36.6.
+static bool blocks_by_passes(int B, int en) {
+  const int64_t nrb = (B + kFRows - 1) / kFRows;
+  return 2 * nrb * fused_bwd_splits(B) <= bwd_resident_wgs(64, en);
+}
 
 hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int loss, float beta,
                             bool out_bf16, hipStream_t s) {
@@ -1626,10 +1651,10 @@ hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int lo
   const float wb = (loss == CRL_LOSS_SYM || loss == CRL_LOSS_BWD || loss == CRL_LOSS_FLATNCE_BWD) ? 1.f : 0.f;
   const int64_t n = (int64_t)B * D;
   const float l2b = (float)std::log2((double)B);
-  const bool one = fused_bwd_one_pass(B, D);
-  int S = one ? 0 : fused_bwd2_splits(B, D, en);
+  const bool blocks = fused_bwd_blocks(B, D);
+  const bool one = blocks && !blocks_by_passes(B, en);
+  const int S = blocks ? fused_bwd_splits(B) : fused_bwd2_splits(B, D, en);
   if (one) {  // one pass for both gradients
-    S = fused_bwd_splits(B);
     const dim3 grid(S, S);
     const double flops = 4.0 * B * B * D;  // G . psi and G^T . phi; the tile recompute is not counted
     const double bytes = 2.0 * 2.0 * B * D + 4.0 * 2.0 * B + 2.0 * 4.0 * (double)S * B * (D + 1.0);
@@ -1642,30 +1667,25 @@ hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int lo
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int cps = cols_per_split(B, S);
+  const int cps = blocks ? kBRows : cols_per_split(B, S);
   const int nrb = (B + kFRows - 1) / kFRows;
-  dim3 grid(nrb, S);
   const double bw_flops = 2.0 * B * B * D;  // G . Y per pass; the tile recompute is not counted
   const double bw_bytes = 2.0 * 2.0 * B * D + 4.0 * 2.0 * B + 4.0 * (double)S * B * (D + 1.0);
-  if (D >= 128) {  // both passes in one launch
-    KTimer t = timing_begin("infonce_bwd_wide_kernel", 2.0 * bw_flops, 2.0 * bw_bytes, s);
-    const dim3 grid2(nrb, S, 2);
-    if (D == 128) {
-      CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<4, EN><<<grid2, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
-    } else {
-      CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<8, EN><<<grid2, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
-    }
-    timing_end(t);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  for (int pass = 0; pass < (one || D >= 128 ? 0 : 2); ++pass) {
-    KTimer t = timing_begin(pass ? "infonce_bwd_kernel<cols>" : "infonce_bwd_kernel<rows>",
-                            bw_flops, bw_bytes, s);
-    if (pass == 0) {
-      CRL_EN_DISPATCH(EN, CRL_NARROW_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 0><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
-    } else {
-      CRL_EN_DISPATCH(EN, CRL_NARROW_DISPATCH(KS, (infonce_bwd_kernel<KS, EN, 1><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))))
+  if (!one) {  // both passes in one launch
+    const dim3 grid(nrb, S, 2);
+    KTimer t = timing_begin(D >= 128 ? "infonce_bwd_wide_kernel" : "infonce_bwd_kernel",
+                            2.0 * bw_flops, 2.0 * bw_bytes, s);
+    switch (D) {
+      case 32: CRL_EN_DISPATCH(EN, (infonce_bwd_kernel<1, EN, false><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))) break;
+      case 64:
+        if (blocks) {
+          CRL_EN_DISPATCH(EN, (infonce_bwd_kernel<2, EN, EN != kEnDot><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
+        } else {
+          CRL_EN_DISPATCH(EN, (infonce_bwd_kernel<2, EN, false><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
+        }
+        break;
+      case 128: CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<4, EN><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b))) break;
+      default: CRL_EN_DISPATCH(EN, (infonce_bwd_wide_kernel<8, EN><<<grid, 256, 0, s>>>(a, B, cps, beta, wf, wb, l2b)))
     }
     timing_end(t);
     hipError_t e = hipGetLastError();

@@ -245,7 +245,7 @@ hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int lo
                             bool out_bf16, hipStream_t s);
 // whether the backward takes the one-pass kernel (D = 64, at most 16 row
 // blocks of 256), whose partials are indexed by 256-row blocks
-bool fused_bwd_one_pass(int B, int D);
+bool fused_bwd_blocks(int B, int D);
 
 // actor.hip: the policy step's elementwise/row kernels
 // Each takes its input either final (top / dx with splits == 1) or as the
