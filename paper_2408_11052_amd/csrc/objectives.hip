@@ -147,16 +147,18 @@ __global__ __launch_bounds__(256) void l1_backward_kernel(const float* __restric
     __syncthreads();
 #pragma unroll 4
     for (int y = 0; y < kL1Y; ++y) {  // rows past the split hold C = 0
-      const uint32_t c = __builtin_bit_cast(uint32_t, Cs[y][xl]);
+      const float cf = Cs[y][xl];
+      const uint32_t c = __builtin_bit_cast(uint32_t, cf);
+      const float none = cf * 0.f;  // c sign(d) where d is 0 or NaN: NaN for a NaN or infinite c
       float yv[8];
       *reinterpret_cast<float4*>(yv) = *reinterpret_cast<const float4*>(&Ys[y][fq]);
       *reinterpret_cast<float4*>(yv + 4) = *reinterpret_cast<const float4*>(&Ys[y][fq + 4]);
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
-        // -c sign(d): c with the opposite of d's sign; nothing where d is 0 (or NaN)
+        // -c sign(d): c with the opposite of d's sign
         const float d = xv[m] - yv[m];
         const uint32_t t = c ^ (~__builtin_bit_cast(uint32_t, d) & 0x80000000u);
-        acc[m] += __builtin_islessgreater(d, 0.f) ? __builtin_bit_cast(float, t) : 0.f;
+        acc[m] += __builtin_islessgreater(d, 0.f) ? __builtin_bit_cast(float, t) : none;
       }
     }
   }
