@@ -229,15 +229,7 @@ __device__ __forceinline__ void mma_half(floatx4 (&acc)[C::MI][C::NJ], const flo
       for (int j = 0; j < C::NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
 }
-// acc + (sum over K of one fragment's rows), through a product with ones; rhs:
-// the fragment is the column operand
-__device__ __forceinline__ floatx4 mma_ones(floatx4 x, floatx4 acc, bool rhs) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    acc = rhs ? __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, x[q], acc, 0, 0, 0)
-              : __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], 1.f, acc, 0, 0, 0);
-  return acc;
-}
+__device__ __forceinline__ float sum4(floatx4 x) { return (x[0] + x[1]) + (x[2] + x[3]); }
 __device__ __forceinline__ float square_sum(floatx4 x) {
   return __builtin_fmaf(x[1], x[1], x[0] * x[0]) + __builtin_fmaf(x[3], x[3], x[2] * x[2]);
 }
@@ -277,14 +269,19 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // FP32 MC x MC launches may ask for an operand's sums over K (wave-uniform)
+  // FP32 MC x MC launches may ask for an operand's sums over K (wave-uniform):
+  // each lane's quarter of K, four values at a time added in 64 bits.  (Products
+  // with ones, four MFMAs a fragment, were chains of 128 rounded sums: at
+  // B = 1024, D = 64 the L2 energy's dpsi was 4.0e-7 off what its own matrix
+  // gives, against 3.2e-7 with a column-sum kernel and 2.8e-7 now.)
   constexpr bool SUMS = sizeof(T) == 4 && LA == LAY_MC && LB == LAY_MC;
-  constexpr int NS = NJ > MI ? NJ : MI;
   const bool want_a = SUMS && D.asum != nullptr && tn == 0 && wn == 0;
   const bool want_b = SUMS && D.bsum != nullptr && tm == 0 && wm == 0;
-  floatx4 ks[NS], kss[NS];
+  double ka[MI], kb[NJ];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) ks[i] = kss[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < MI; ++i) ka[i] = 0.0;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) kb[j] = 0.0;
   // distance energies (FP32 KC x KC): the rows' squared norms, four squares at
   // a time added in 64 bits: a lane has a quarter of K, and a running FP32 sum
   // that long errs by more than a tree over 64 lanes (RMS in 2^-24 at K = 64
@@ -337,16 +334,16 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     // FP32: the running sums are added into `sum` every 128 of K, so that a
     // long K rounds like the short chains of a split one
     floatx4 sum[MI][NJ];
-    // the operands' own sums over K: one more MFMA per fragment with ones, in
-    // the first tile row (B) or column (A) of the launch
+    // the operands' own sums over K, in the first tile row (B) or column (A) of
+    // the launch
     auto sum_k = [&](const typename Frag<T>::type (&a)[MI], const typename Frag<T>::type (&b)[NJ]) {
       if constexpr (SUMS) {
         if (want_a)
 #pragma unroll
-          for (int i = 0; i < MI; ++i) ks[i] = mma_ones(a[i], ks[i], false);
+          for (int i = 0; i < MI; ++i) ka[i] += (double)sum4(a[i]);
         if (want_b)
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) ks[j] = mma_ones(b[j], ks[j], true);
+          for (int j = 0; j < NJ; ++j) kb[j] += (double)sum4(b[j]);
       }
     };
     // squared norms of the operands' rows, from the fragments as they pass
@@ -362,19 +359,12 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     };
     auto flush = [&]() {
       settle(acc);
-      if constexpr (SUMS) settle(ks);
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
           sum[i][j] += acc[i][j];
           acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-      if constexpr (SUMS)
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          kss[i] += ks[i];
-          ks[i] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
     };
     if constexpr (sizeof(T) == 4) {
@@ -441,26 +431,26 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = sum[i][j];
-#pragma unroll
-      for (int i = 0; i < NS; ++i) ks[i] = kss[i];
     }
   }
   if constexpr (SUMS) {
-    // every column (A) or row (B) of a ones product holds the sum
-    if (want_a && (lane & 15) == 0) {
+    // the four quarters of K; then lane (g, j) has row / column j's sum
+    if (want_a) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = m0 + (wm * MI + i) * 16 + (lane >> 4) * 4 + r;
-          if (row < D.M) D.asum[(int64_t)wi.split * D.M + row] = ks[i][r];
-        }
+      for (int i = 0; i < MI; ++i) {
+        ka[i] += __shfl_xor(ka[i], 16, 64);
+        ka[i] += __shfl_xor(ka[i], 32, 64);
+        const int row = m0 + (wm * MI + i) * 16 + lane;
+        if (lane < 16 && row < D.M) D.asum[(int64_t)wi.split * D.M + row] = (float)ka[i];
+      }
     }
-    if (want_b && lane < 16) {
+    if (want_b) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
+        kb[j] += __shfl_xor(kb[j], 16, 64);
+        kb[j] += __shfl_xor(kb[j], 32, 64);
         const int col = n0 + (wn * NJ + j) * 16 + lane;
-        if (col < D.N) D.bsum[(int64_t)wi.split * D.N + col] = ks[j][0];
+        if (lane < 16 && col < D.N) D.bsum[(int64_t)wi.split * D.N + col] = (float)kb[j];
       }
     }
   }

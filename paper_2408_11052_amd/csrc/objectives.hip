@@ -418,8 +418,11 @@ __global__ __launch_bounds__(256) void obj_finish_kernel(ObjFinish a, int splits
   float* out = a.out[side] + o;
   bf16_t* outb = a.outb[side];
   float rs = 0.f, dot = 0.f, inv = 1.f;
-  if (fix == kFixDist)
-    for (int k = 0; k < a.nrs[side]; ++k) rs += a.rs[side][(int64_t)k * B + row];
+  if (fix == kFixDist) {
+    double t = 0.0;  // a rounding a split would add up to more than the splits' own
+    for (int k = 0; k < a.nrs[side]; ++k) t += (double)a.rs[side][(int64_t)k * B + row];
+    rs = (float)t;
+  }
   if (fix == kFixCos) {
     for (int d = lane; d < D; d += 64) {
       float v = 0.f;
