@@ -153,5 +153,15 @@ __device__ inline void kahan_add(float& s, float& comp, float x) {
   comp = (t - s) - y;
   s = t;
 }
+// lse_merge into a compensated sum s - comp
+__device__ inline void lse_merge_kahan(float& m, float& s, float& comp, float m2, float s2) {
+  const float mn = s2 == 0.f ? m : (s == 0.f ? m2 : fmaxf(m, m2));
+  const float k = s == 0.f ? 0.f : __expf(m - mn);
+  const float b = s2 == 0.f ? 0.f : s2 * __expf(m2 - mn);
+  s *= k;
+  comp *= k;
+  kahan_add(s, comp, b);
+  m = mn;
+}
 
 }  // namespace crl

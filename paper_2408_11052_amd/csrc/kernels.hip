@@ -957,7 +957,9 @@ hipError_t launch_lse_merge(const LseMergeArgs& a, int count, int B, hipStream_t
 // their sum, FlatNCE (exp(x - x) per row, x = r - diag or c - diag), or the
 // mean of term[] (Forward-Backward, DPO, IPO, SPPO).
 // With nparts > 0 each thread first merges its columns' (max, sum) partials in
-// part order into c: one launch (4.5 us) less where the columns are few.
+// part order into c: one launch (4.5 us) less where the columns are few.  The
+// order is serial, so the sum is compensated (without, c was up to 1.1 times
+// as far off as lse_merge_kernel's tree leaves it).
 // Latency is all it costs: four rows' loads go out together, and the last six
 // levels of the tree run inside a wavefront (B=16384 9.8 -> 8.4 us, B=4096 4.6
 // -> 4.2).  Joined to lse_merge_kernel (its last workgroup takes the loss) it
@@ -995,11 +997,11 @@ __global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ r,
       const float ri = rv[k], di = dv[k];
       float ci = cv[k];
       if (nparts > 0) {
-        float m = -INFINITY, sum = 0.f;
+        float m = -INFINITY, sum = 0.f, low = 0.f;
 #pragma unroll 4
         for (int p = 0; p < nparts; ++p)
-          lse_merge(m, sum, col_m[(int64_t)p * B + i], col_s[(int64_t)p * B + i]);
-        ci = m + __logf(sum);
+          lse_merge_kahan(m, sum, low, col_m[(int64_t)p * B + i], col_s[(int64_t)p * B + i]);
+        ci = m + __logf(sum - low);
         c[i] = ci;
       }
       float o = tv[k];

@@ -235,7 +235,8 @@ __device__ __forceinline__ void row_obj(const float* __restrict__ row, int i, in
   }
 }
 // Column chunk: the (max, sum) of 256 columns over rows [i0, i1), eight rows'
-// loads in flight before their maximum and then their sum are taken.
+// loads in flight before their maximum and then their sum are taken, the sum
+// pairwise (an eighth of the roundings that grow with it).
 __device__ __forceinline__ void col_lse(const float* __restrict__ F, int ld, int B, int j, int i0,
                                         int i1, float& m, float& s) {
   m = -INFINITY;
@@ -249,8 +250,8 @@ __device__ __forceinline__ void col_lse(const float* __restrict__ F, int ld, int
     for (int k = 0; k < 8; ++k) mn = fmaxf(mn, f[k]);
     s = m == -INFINITY ? 0.f : s * __expf(m - mn);
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (i + k < i1) s += __expf(f[k] - mn);
+    for (int k = 0; k < 8; ++k) f[k] = i + k < i1 ? __expf(f[k] - mn) : 0.f;
+    s += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
     m = mn;
   }
 }
