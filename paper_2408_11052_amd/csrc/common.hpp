@@ -135,11 +135,16 @@ __device__ __forceinline__ uint32_t lds_address(void* p) {
 // lds + 16 l.  No register is written and the compiler does not count the
 // load: wait_vm below does.  (Through the builtin the compiler, which cannot
 // tell buffers apart, waits for every such load before the next transpose read.)
+// M0 holds the address; the compiler is told so, for what it keeps there itself
+// (its warning that M0 is not preserved across the block is the intention).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                ::"s"(lds), "v"(off), "s"(base)
-               : "memory");
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // all but this wave's N latest vector-memory operations done, and its LDS reads
 template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
