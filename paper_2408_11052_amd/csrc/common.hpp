@@ -131,12 +131,22 @@ typedef __attribute__((address_space(3))) char lds_char;
 __device__ __forceinline__ uint32_t lds_address(void* p) {
   return (uint32_t)(uintptr_t)(lds_char*)p;
 }
+// Before a group of load_to_lds: with the two instructions that each puts before
+// its load, the five wait states between a vector instruction that writes an
+// SGPR (a base read from a lane, or reloaded from one) and a load that reads it.
+// The compiler counts none into such a block.  (In each load instead, four a
+// stage: 1% of the small GEMMs' time.)
+__device__ __forceinline__ void bases_ready(const char*& a) { asm volatile("s_nop 2" : "+s"(a)); }
+__device__ __forceinline__ void bases_ready(const char*& a, const char*& b) {
+  asm volatile("s_nop 2" : "+s"(a), "+s"(b));
+}
 // 64 lanes x 16 bytes: lane l's 16 bytes at base + off go to LDS address
 // lds + 16 l.  No register is written and the compiler does not count the
 // load: wait_vm below does.  (Through the builtin the compiler, which cannot
 // tell buffers apart, waits for every such load before the next transpose read.)
 // M0 holds the address; the compiler is told so, for what it keeps there itself
 // (its warning that M0 is not preserved across the block is the intention).
+// The caller has passed base through bases_ready just ahead.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds) {

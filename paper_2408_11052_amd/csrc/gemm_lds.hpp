@@ -305,6 +305,7 @@ __device__ __forceinline__ void gemm_lds_tile(const GemmParams& P, const WorkIte
     int head = 0, tail = 0;  // ring slots: the next to fill, the one in use
     auto issue = [&](int t) {
       const uint32_t st = lds0 + head * C::STAGE;
+      bases_ready(oa.base, ob.base);
       oa.issue(kbeg + t * BK, st, wave, lane);
       ob.issue(kbeg + t * BK, st + C::BM * 128, wave, lane);
       head = head + 1 == C::ST ? 0 : head + 1;

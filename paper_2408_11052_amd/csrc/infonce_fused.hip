@@ -286,11 +286,13 @@ __device__ __forceinline__ void wide_tile_load(const bf16_t* __restrict__ Y, int
   dst = __builtin_amdgcn_readfirstlane(dst + wave * NI * 1024);
   if (last >= kFCols - 1) {
     base += wave * 16 * RB;
+    bases_ready(base);
 #pragma unroll
     for (int i = 0; i < NI; ++i)
       load_to_lds(base + i * 1024, rl * RB + (c ^ wide_swz(i * NR + rl)) * 16,
                   dst + i * 1024);
   } else {
+    bases_ready(base);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int r = i * NR + rl;

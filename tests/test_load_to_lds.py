@@ -24,6 +24,18 @@ extern "C" __global__ void own_loads_around(const char* a, char* o) {
   __syncthreads();
   o[threadIdx.x] = sm[threadIdx.x ^ 5];
 }
+// a base that vector instructions write just ahead of the load
+extern "C" __global__ void base_from_lanes(const uint32_t* p, char* o) {
+  __shared__ __attribute__((aligned(1024))) char sm[4096];
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)p[threadIdx.x]);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)p[threadIdx.x + 64]);
+  const char* base = (const char*)(((uint64_t)hi << 32) | lo);
+  bases_ready(base);
+  load_to_lds(base, threadIdx.x * 16, lds_address(sm));
+  wait_vm<0>();
+  __syncthreads();
+  o[threadIdx.x] = sm[threadIdx.x ^ 5];
+}
 '''
 
 
@@ -49,3 +61,55 @@ def test_the_compiler_sets_m0_again_after_ours(asm):
     assert len(loads) == 3
     between = ins[loads[1] + 1:loads[2]]
     assert any(re.match(r"s_\w+ m0,", l) for l in between), "\n".join(ins)
+
+
+def _short_waits(ins):
+    """Loads into LDS whose SGPR base a vector instruction writes fewer than five
+    wait states ahead (looked back along the listing, past labels too)."""
+    loads = bad = 0
+    for i, l in enumerate(ins):
+        m = re.match(r"global_load_lds_dwordx4 v\S+ s\[(\d+):(\d+)\]", l)
+        if not m:
+            continue
+        loads += 1
+        regs = {f"s{k}" for k in range(int(m[1]), int(m[2]) + 1)}
+        states, k = 0, i - 1
+        while k >= 0 and states < 5:
+            op, _, args = ins[k].partition(" ")
+            if op.startswith("v_read") and args.split(",")[0].strip() in regs:
+                bad += 1
+                break
+            states += int(args, 0) + 1 if op == "s_nop" else 1
+            k -= 1
+    return loads, bad
+
+
+def test_wait_states_between_a_lane_read_and_the_load(asm):
+    # a vector instruction's SGPR result may be read by a vector-memory
+    # instruction five wait states later
+    ins = asm["base_from_lanes"]
+    assert sum(l.startswith("v_readfirstlane") for l in ins) >= 2
+    assert _short_waits(ins) == (1, 0), "\n".join(ins)
+
+
+def test_wait_states_in_the_built_library(tmp_path):
+    tools = [os.path.join(os.path.dirname(os.path.realpath(B.HIPCC)), "..", "llvm", "bin", t)
+             for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump")]
+    if not all(os.path.exists(t) for t in tools) or not os.path.exists(B.OUT):
+        pytest.skip("no LLVM tools or no built library")
+    fat = tmp_path / "fat"
+    subprocess.run([tools[0], "--dump-section", f".hip_fatbin={fat}", B.OUT, str(tmp_path / "rest")], check=True)
+    # one bundle a source file, each on a boundary of 4 KB
+    data, magic, loads = fat.read_bytes(), b"__CLANG_OFFLOAD_BUNDLE__", 0
+    starts = [m.start() for m in re.finditer(magic, data)]
+    for a, b in zip(starts, starts[1:] + [len(data)]):
+        (tmp_path / "bundle").write_bytes(data[a:b])
+        subprocess.run([tools[1], "--unbundle", "--type=o", f"--targets=hipv4-amdgcn-amd-amdhsa--{B.ARCH}",
+                        f"--input={tmp_path / 'bundle'}", f"--output={tmp_path / 'obj'}"], check=True)
+        text = subprocess.run([tools[2], "-d", "--no-show-raw-insn", str(tmp_path / "obj")], check=True,
+                              capture_output=True, text=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\w+)>:$(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.S | re.M):
+            n, bad = _short_waits([l.split("//")[0].strip() for l in body.splitlines() if l.strip()])
+            loads += n
+            assert bad == 0, name
+    assert loads > 100
