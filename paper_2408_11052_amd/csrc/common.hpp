@@ -155,9 +155,12 @@ __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
-// all but this wave's N latest vector-memory operations done, and its LDS reads
+// all but this wave's N latest vector-memory operations done, and its LDS reads;
+// those that stand before it, for neither this wait nor a barrier keeps the
+// compiler from moving an LDS read behind them
 template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
 }
 

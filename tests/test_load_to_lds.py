@@ -36,6 +36,19 @@ extern "C" __global__ void base_from_lanes(const uint32_t* p, char* o) {
   __syncthreads();
   o[threadIdx.x] = sm[threadIdx.x ^ 5];
 }
+// an LDS read before a counted wait and a barrier, its value used behind them:
+// other waves may refill the tile once the barrier is passed
+extern "C" __global__ void read_before_barrier(const char* a, float* o, int n) {
+  __shared__ __attribute__((aligned(1024))) float sm[1024];
+  load_to_lds(a, threadIdx.x * 16, lds_address(sm));
+  wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  const float x = sm[threadIdx.x ^ 33];
+  wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  if (n > 3) o[threadIdx.x] = x;
+}
 '''
 
 
@@ -113,3 +126,12 @@ def test_wait_states_in_the_built_library(tmp_path):
             loads += n
             assert bad == 0, name
     assert loads > 100
+
+
+def test_lds_reads_stay_before_the_counted_wait(asm):
+    ins = asm["read_before_barrier"]
+    read = next(i for i, l in enumerate(ins) if l.startswith("ds_read"))
+    barriers = [i for i, l in enumerate(ins) if l == "s_barrier"]
+    assert len(barriers) == 2 and barriers[0] < read < barriers[1], "\n".join(ins)
+    # and the read has arrived by then
+    assert any(l.startswith("s_waitcnt") and "lgkmcnt(0)" in l for l in ins[read:barriers[1]])
