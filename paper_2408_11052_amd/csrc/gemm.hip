@@ -37,21 +37,6 @@ static const char* lds_kernel_name() {
   return names[sizeof(T) == 2][LA][LB][sizeof(OutT) == 2];
 }
 
-// What the kernel assumes of its operands (every caller provides it).
-static bool operands_ok(const GemmParams& P, bool bf16) {
-  const int v = bf16 ? 8 : 4;
-  for (int g = 0; g < P.count; ++g) {
-    const GemmDesc& d = P.d[g];
-    if (d.M < 1 || d.N < 1 || d.K < 1 || d.lda % v || d.ldb % v || d.ldc % 8) return false;
-    if ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B) |
-         reinterpret_cast<uintptr_t>(d.C)) & 15u)
-      return false;
-    if (d.N % 8 && (d.epi == EPI_MASK_POS || (P.splits > 1 && P.defer_reduce && P.frag)))
-      return false;
-  }
-  return true;
-}
-
 int frag_bn(const GemmParams& P) {
   int nmax = 0;
   for (int g = 0; g < P.count; ++g) nmax = P.d[g].N > nmax ? P.d[g].N : nmax;
@@ -151,7 +136,7 @@ static void run_tile(const GemmParams& P, hipStream_t s) {
 template <typename T, int LA, int LB, typename OutT>
 static hipError_t run(GemmParams& P, hipStream_t s) {
   if (max_tiles(P) == 0) return hipSuccess;
-  if (!operands_ok(P, sizeof(T) == 2)) return hipErrorInvalidValue;
+  if (!gemm_operands_ok(P, sizeof(T) == 2, LA, LB)) return hipErrorInvalidValue;
   double flops = 0.0, bytes = 0.0;
   algo_counts(P, sizeof(T), sizeof(OutT), flops, bytes);
   const bool alt = alt_order<T>(P);
@@ -242,7 +227,8 @@ static void run_pair(GemmParams& P1, GemmParams& P2, hipStream_t s) {
 }
 
 hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStream_t s) {
-  if (!gemm_pair_ok(Pw, Px, bf16) || !operands_ok(Pw, bf16) || !operands_ok(Px, bf16))
+  if (!gemm_pair_ok(Pw, Px, bf16) || !gemm_operands_ok(Pw, bf16, LAY_MC, LAY_MC) ||
+      !gemm_operands_ok(Px, bf16, LAY_KC, LAY_KC))
     return hipErrorInvalidValue;
   double flops = 0.0, bytes = 0.0;
   const double es = bf16 ? 2.0 : 4.0;
@@ -257,7 +243,8 @@ hipError_t launch_gemm_dw_dx(GemmParams& Pw, GemmParams& Px, bool bf16, hipStrea
 }
 
 hipError_t launch_gemm_obj(GemmParams& Pc, GemmParams& Pr, hipStream_t s) {
-  if (!operands_ok(Pc, false) || !operands_ok(Pr, false)) return hipErrorInvalidValue;
+  if (!gemm_operands_ok(Pc, false, LAY_MC, LAY_MC) || !gemm_operands_ok(Pr, false, LAY_KC, LAY_MC))
+    return hipErrorInvalidValue;
   if ((Pc.splits > 1 && !Pc.defer_reduce) || (Pr.splits > 1 && !Pr.defer_reduce))
     return hipErrorInvalidValue;
   double flops = 0.0, bytes = 0.0;

@@ -59,6 +59,35 @@ struct GemmParams {
                        // order of 128 x frag blocks (see frag_partial_floats)
 };
 
+// K values of a stage: 128 bytes of every tile row
+constexpr int gemm_bk(bool bf16) { return bf16 ? 64 : 32; }
+
+// What the kernel assumes of a launch (every caller provides it); nothing of it
+// is checked on the device.
+inline bool gemm_operands_ok(const GemmParams& P, bool bf16, int la, int lb) {
+  const int v = bf16 ? 8 : 4, BK = gemm_bk(bf16);
+  if (P.count < 1 || P.count > kGemmMaxGroup || P.splits < 1 || P.k_chunk < BK || P.k_chunk % BK)
+    return false;
+  if (P.splits > 1 && !P.partial) return false;
+  const bool sums = !bf16 && la == LAY_MC && lb == LAY_MC;
+  const bool dist = !bf16 && la == LAY_KC && lb == LAY_KC && P.splits == 1;
+  for (int g = 0; g < P.count; ++g) {
+    const GemmDesc& d = P.d[g];
+    if (d.M < 1 || d.N < 1 || d.K < 1 || d.lda % v || d.ldb % v || d.ldc % 8) return false;
+    if ((reinterpret_cast<uintptr_t>(d.A) | reinterpret_cast<uintptr_t>(d.B) |
+         reinterpret_cast<uintptr_t>(d.C)) & 15u)
+      return false;
+    if ((int64_t)P.splits * P.k_chunk < d.K) return false;
+    // every stage of B has a row to read: loads past the last are clamped to it
+    if (d.kb < 0 || (d.kb > 0 && d.kb <= (d.K - 1) / BK * BK)) return false;
+    if (d.N % 8 && (d.epi == EPI_MASK_POS || (P.splits > 1 && P.defer_reduce && P.frag)))
+      return false;
+    if ((d.asum || d.bsum) && !sums) return false;
+    if ((d.epi == EPI_L2 || d.epi == EPI_L2SQ) && !dist) return false;
+  }
+  return true;
+}
+
 // Work item (tile, split, problem) of a workgroup.  Workgroups are dealt to
 // the 8 XCDs round-robin by linear id; the linear id is remapped so that each
 // XCD gets one contiguous eighth of the (problem, split, tile) order -- a run

@@ -31,7 +31,7 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
 
-template <typename T> constexpr int bk() { return 128 / (int)sizeof(T); }   // K per stage
+template <typename T> constexpr int bk() { return gemm_bk(sizeof(T) == 2); }  // K per stage
 template <typename T> constexpr int vec() { return 16 / (int)sizeof(T); }   // values per chunk
 
 // BM x BN tile, WM x WN waves, ST stages, OCC waves per SIMD to compile for
