@@ -20,8 +20,10 @@ from ._lib import (ACT, ENERGY, LOGITS, LOSS, PREC, WS, check, crl_config,
 # The arguments' declared types (c_void_p) take plain integers and None, and the
 # current stream's handle is asked for without building a torch.cuda.Stream:
 # of the 8.4 us that issuing the smallest call (crl_sample_relabel) took, the
-# Stream object was 2.8 and the c_void_p objects 0.9.
+# Stream object was 2.8 and the c_void_p objects 0.9.  Both getters are torch's
+# private ones: without either, the Stream object it is.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _ptr(t) -> int | None:
@@ -31,9 +33,9 @@ def _ptr(t) -> int | None:
 def _stream(stream=None) -> int:
     if stream is not None:
         return stream.cuda_stream
-    if _raw_stream is None or not torch.cuda.is_initialized():
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
 
 
 def make_config(w, max_episode_len: int | None = None) -> crl_config:
