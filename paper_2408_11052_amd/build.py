@@ -20,6 +20,9 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "libcrl.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
+# the tests' way to the routes that a dispatch rule chooses between: the same
+# objects with tests/routes.hip, in a library of its own
+ROUTES = os.path.join(ROOT, "tests", "libroutes.so")
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
@@ -45,17 +48,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _link(out: str, objs) -> None:
+    tmp = out + ".tmp"
+    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-Wl,-z,defs", "-o", tmp, *objs]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed for {out}:\n{r.stderr}")
+    os.replace(tmp, out)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
     with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(_compile, srcs))
-    tmp = OUT + ".tmp"
-    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stderr}")
-    os.replace(tmp, OUT)
+    _link(OUT, objs)
+    routes = os.path.join(ROOT, "tests", "routes.hip")
+    if os.path.exists(routes):
+        used = ("gemm.hip.o", "infonce_fused.hip.o", "kernels.hip.o", "timing.hip.o")
+        _link(ROUTES, [_compile(routes), *(o for o in objs if os.path.basename(o) in used)])
     if verbose:
         print(f"built {OUT}")
     return OUT

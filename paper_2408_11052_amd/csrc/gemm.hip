@@ -77,7 +77,7 @@ static int64_t tiles_of(const GemmParams& P, int tile) {
 }
 int64_t gemm_tiles128(const GemmDesc& d) { return tiles_of(d, kTile128); }
 
-static void set_tile(GemmParams& P, int tile) {
+void set_tile(GemmParams& P, int tile) {
   static const int cols[4] = {32, 32, 64, 128};
   P.tile = tile;
   for (int g = 0; g < P.count; ++g) {

@@ -1647,14 +1647,14 @@ static bool blocks_by_passes(int B, int en) {
 }
 
 hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int loss, float beta,
-                            bool out_bf16, hipStream_t s) {
+                            bool out_bf16, hipStream_t s, BlockRoute route) {
   const int en = fused_energy(energy);
   const float wf = (loss == CRL_LOSS_FWD || loss == CRL_LOSS_SYM || loss == CRL_LOSS_FLATNCE_FWD) ? 1.f : 0.f;
   const float wb = (loss == CRL_LOSS_SYM || loss == CRL_LOSS_BWD || loss == CRL_LOSS_FLATNCE_BWD) ? 1.f : 0.f;
   const int64_t n = (int64_t)B * D;
   const float l2b = (float)std::log2((double)B);
   const bool blocks = fused_bwd_blocks(B, D);
-  const bool one = blocks && !blocks_by_passes(B, en);
+  const bool one = blocks && (route == kRouteAuto ? !blocks_by_passes(B, en) : route == kRouteOnePass);
   const int S = blocks ? fused_bwd_splits(B) : fused_bwd2_splits(B, D, en);
   if (one) {  // one pass for both gradients
     const dim3 grid(S, S);

@@ -40,6 +40,7 @@ hipError_t launch_gemm_obj(GemmParams& Pc, GemmParams& Pr, hipStream_t s);
 // P.k_chunk, P.tile, P.tiles): the largest power of two that keeps the launch
 // within target_wgs workgroups and every split at least min_steps K steps deep.
 void plan_split_k(GemmParams& P, bool bf16, int target_wgs, int min_steps = 4);
+void set_tile(GemmParams& P, int tile);    // tile (kTile*) and tile counts of a planned launch
 int64_t gemm_tiles128(const GemmDesc& d);  // 128 x 128 tiles of one problem
 // Block width (128, or 64 when no problem is wider) of the fragment order that
 // a launch's deferred split-K partials take.
@@ -240,9 +241,12 @@ int fused_bias_chunks(int B, int D);  // row blocks of the backward reduction
 // energy: CRL_ENERGY_DOT, _L2, _COS (unit rows, dot product) or _L2SQ
 hipError_t launch_fused_fwd(const FusedArgs& a, int B, int D, int energy, const GemmParams* top,
                             hipStream_t s);
+// Where the backward's partials are those of 256-row blocks, the kernel that
+// makes them: by the batch size, or (in tests of their equality) as said.
+enum BlockRoute { kRouteAuto, kRouteOnePass, kRouteTwoPasses };
 // loss: CRL_LOSS_FWD, _SYM, _BWD, _FLATNCE_FWD or _FLATNCE_BWD
 hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int loss, float beta,
-                            bool out_bf16, hipStream_t s);
+                            bool out_bf16, hipStream_t s, BlockRoute route = kRouteAuto);
 // whether the backward takes the one-pass kernel (D = 64, at most 16 row
 // blocks of 256), whose partials are indexed by 256-row blocks
 bool fused_bwd_blocks(int B, int D);
