@@ -308,11 +308,11 @@ template <int D> __device__ __forceinline__ int wide_at(int r16, int ks, int g) 
   return r16 * 2 * D + (((4 * (ks & 3) + g) ^ wide_swz(r16)) << 4);
 }
 
-// tile_product from such a tile, fragments a step ahead of their products
-template <int KS, typename F>
+// tile_product from such a tile, fragments a step ahead of their products (the
+// forward's; the backward has the loop in its own body, where it spills nothing)
+template <int KS>
 __device__ __forceinline__ void wide_product(floatx4 (&acc)[4], const bf16x8 (&xa)[KS],
-                                             const char* __restrict__ Yt, const int (&oa)[4],
-                                             F&& between) {
+                                             const char* __restrict__ Yt, const int (&oa)[4]) {
   bf16x8 b[2][4];
   auto frags = [&](int ks) {
 #pragma unroll
@@ -323,7 +323,6 @@ __device__ __forceinline__ void wide_product(floatx4 (&acc)[4], const bf16x8 (&x
 #pragma unroll
   for (int jb = 0; jb < 4; ++jb) acc[jb] = floatx4{0.f, 0.f, 0.f, 0.f};
   frags(0);
-  between();
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     if (ks + 1 < KS) frags(ks + 1);
@@ -345,8 +344,8 @@ template <int KS, int EN> constexpr int wide_waves() { return KS >= 8 || EN != k
 // against the 64-column tiles of one column split.  Tiles inside the batch
 // on every side skip the masking, and only the tile that holds a wave's
 // diagonal entries looks for them (one wave-uniform branch).
-// What binds it is the entries: some 17 vector instructions each, three of them
-// exponentials or roots.  At D >= 128 the tile goes from global memory straight
+// What binds it is the entries: some 20 vector instructions each beside the two
+// MFMAs (D = 256, L2), 3.5 of them exponentials or roots.  At D >= 128 the tile goes from global memory straight
 // into the one LDS tile while the entries of the tile before are formed, and
 // the tile product reads its fragments a step ahead: staged through registers,
 // with a branch for each masked sum, B=16384, D=256, L2 took 305 us, now 278;
@@ -505,7 +504,7 @@ __global__ __launch_bounds__(256, fwd_waves<KS>()) void infonce_fwd_kernel(Fused
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int jb = 0; jb < 4; ++jb) nyv[jb] = nypf[jb];
-      wide_product<KS>(acc, xa, reinterpret_cast<const char*>(Ys), oa, []() {});
+      wide_product<KS>(acc, xa, reinterpret_cast<const char*>(Ys), oa);
       if (j0 > c0) flush_cols(j0 - kFCols);
       // every wave has read both: the next tile loads while this one's entries
       // are formed
@@ -848,7 +847,7 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 // all four G strips (64 rows) by its quarter of the tile's columns, so the
 // tile is read once per workgroup in that product rather than once per wave.
 //
-// What binds it is the mix per 64 x 64 tile: 64 MFMAs a wave, 17 vector
+// What binds it is the mix per 64 x 64 tile: 64 MFMAs a wave, some 18 vector
 // instructions an entry (of 13 that an L2 entry itself takes) and 192 KB of LDS
 // reads a workgroup, with two workgroups on a CU.  Vector instructions and
 // MFMAs of a SIMD's two waves overlap only in part (a wave of FMAs beside one
@@ -866,7 +865,6 @@ __global__ __launch_bounds__(256, 4) void infonce_bwd_kernel(FusedArgs a, int B,
 // B=16384, D=256, L2: 703 -> 625 us for both passes; B=8192, D=256, dot: 150;
 // B=8192, D=128, dot: 115 -> 90; B=1500, D=128: 23 -> 15, one launch instead of
 // two.
-//
 template <int KS, int EN, int TRANS>
 __device__ __forceinline__ void infonce_bwd_wide(const FusedArgs& a, int B, int cps, float beta,
                                                  float wf, float wb, float log2b,
@@ -1569,8 +1567,11 @@ static int bwd_resident_wgs(int D, int en) {
 // partial of dX that bwd_reduce_kernel reads back, so take the fewest splits
 // (at most fused_splits(B)) whose busiest workgroup slot carries no more
 // 64-column tiles than with fused_splits(B): rounds of resident workgroups
-// times tiles per workgroup (B=16384, D=256: 2 splits in one round of 512
-// workgroups against 4 in two rounds, half the partials).
+// times tiles per workgroup (B=16384, D=256: 2 splits and not 4, half the
+// partials).  The rounds are those of one pass, as when each had a launch of its
+// own; the one grid of both has twice the workgroups (there 1024, two rounds of
+// 512), and a count over it would come to fewer splits still.  It stays because
+// the splits decide the order of the partial sums, which BF16 training keeps.
 static int fused_bwd2_splits(int B, int D, int en) {
   const int S = fused_splits(B);
   const int nrb = (B + kFRows - 1) / kFRows;
@@ -1635,7 +1636,7 @@ bool fused_bwd_blocks(int B, int D) { return D == 64 && fused_bwd_splits(B) <= k
 
 // Such partials come from the one-pass kernel, a 256 x 256 block per workgroup
 // of a whole CU, or, equal to the bit, from the two passes with 256 columns a
-// workgroup: twice the entries, but 16 times the workgroups, each with a
+// workgroup: twice the entries, but 8 times the workgroups, each with a
 // quarter of the waves.  The passes are faster while the device holds all of
 // their workgroups at once (B up to 2816 on 256 CUs).  Reduction included, one
 // pass against two: dot B=333 16.7, 9.8 us; B=1000 18.5, 11.7; B=2048 20.9, 15.3;

@@ -96,7 +96,7 @@ int colsum_chunks(int B);
 // Deferred gradient reductions: g[dst + i] = sum_k part_k[i], part_k at byte
 // offset src + 4 k stride in the workspace, i < n, in the order k = 0, 1, ...
 // (with four interleaved running sums, combined in a fixed order).  `first`
-// is the job's first float4 (few-part jobs) or first 16-output block
+// is the job's first float4 (few-part jobs) or first block of kManyCols outputs
 // (many-part jobs) in the launch's index space.
 // Sum of nparts partial blocks (src + k * stride floats, k = 0..nparts-1, in
 // that order) into g + dst.  bn == 0: n contiguous floats.  bn > 0: split-K
@@ -130,7 +130,7 @@ struct ActorLossArgs {
   float* alpha_grad;
 };
 // few-part jobs (total4 float4 outputs) and many-part jobs (nblocks blocks of
-// 16 outputs) in one launch.  With A, each gradient element goes straight
+// kManyCols outputs) in one launch.  With A, each gradient element goes straight
 // into the Adam step of its parameter (g, if not NULL, still receives it).
 // With L, one more block reduces the policy's loss.
 hipError_t launch_grad_reduce(const char* ws, float* g, const RedJob* few, int nfew,
