@@ -109,7 +109,7 @@ hipError_t launch_l1_energy(const float* phi, const float* psi, float* F, int B,
 // l has row l, wave w features 8w..8w+7, so the block of C is read from LDS
 // without conflicts and Y as broadcasts, and the splits fill the chip.  One
 // thread per row and eight strided features with all of y in one workgroup
-// (54 workgroups a side) took 1755 us at B = 1701, D = 40; this takes 46.
+// (54 workgroups a side) took 1755 us at B = 1701, D = 40; this takes 74.
 constexpr int kL1X = 64, kL1F = 32, kL1Y = 32;
 __global__ __launch_bounds__(256) void l1_backward_kernel(const float* __restrict__ phi,
                                                           const float* __restrict__ psi,
@@ -281,11 +281,15 @@ __global__ __launch_bounds__(256) void row_col_kernel(const float* __restrict__ 
   col_m[(int64_t)chunk * B + j] = m;
   col_s[(int64_t)chunk * B + j] = s;
 }
-// Row chunks of the column log-sum-exps (at most 64, the workspace's slots).
-// Up to B = 2048 the loss kernel itself merges them (its one workgroup takes
-// two columns a thread), so there they are fewer; above, lse_merge_kernel does.
+// Row chunks of the column log-sum-exps (at most 64, the workspace's slots):
+// enough blocks beside the rows' and few parts to merge (loss layer, 64 chunks
+// against these: B = 512 29.6, 28.8 us; B = 1024 39.1, 38.5; B = 2048 the same).
 int col_chunks(int B) { return std::min(B, B <= 1024 ? 16 : B <= 2048 ? 32 : 64); }
-bool col_merge_in_loss(int B) { return B <= 2048; }
+// Up to B = 256 the loss kernel itself merges them, a launch less; its one
+// workgroup reads all of them, so above lse_merge_kernel does.  Loss layer, D =
+// 64, merged in the loss kernel against apart: B = 256 24.3 us both, 384 28.1,
+// 25.8; 1024 41.6, 38.5; 1536 74.8, 57.6; 2048 94.7, 74.7.
+bool col_merge_in_loss(int B) { return B <= 256; }
 hipError_t launch_row_col(const float* F, int B, int ld, int loss, float* r, float* diag,
                           float* term, float* aux, float* col_m, float* col_s, hipStream_t s) {
   const int nrow = (B + 3) / 4, ncol = (B + 255) / 256, chunks = col_chunks(B);

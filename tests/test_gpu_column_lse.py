@@ -2,7 +2,8 @@
 same FP32 matrix taken in 64 bits.  Rows and columns hold the same number of
 exponentials and end in the same logarithm, so for a matrix with like rows and
 columns the columns' error is the rows'; 1.05 covers the sample of a thousand
-or two of each.
+or more of each.  Up to B = 256 the loss kernel merges the columns' chunks, above a
+kernel of its own.
 """
 import numpy as np
 import pytest
@@ -13,7 +14,8 @@ from tests.test_gpu_infonce_hooks import MAT, _ctx
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,D,energy,scale", [(1024, 64, "l2sq", 0.3), (2048, 64, "l2sq", 0.3),
+@pytest.mark.parametrize("B,D,energy,scale", [(256, 64, "l2sq", 0.3), (257, 64, "l2sq", 0.3),
+                                              (1024, 64, "l2sq", 0.3), (2048, 64, "l2sq", 0.3),
                                               (2048, 64, "dot", 0.5), (2049, 64, "dot", 0.5)])
 def test_columns_err_like_rows(B, D, energy, scale):
     w, crit = _ctx(MAT, B, D, energy, "symmetric_infonce")
