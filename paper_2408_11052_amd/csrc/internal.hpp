@@ -247,8 +247,8 @@ enum BlockRoute { kRouteAuto, kRouteOnePass, kRouteTwoPasses };
 // loss: CRL_LOSS_FWD, _SYM, _BWD, _FLATNCE_FWD or _FLATNCE_BWD
 hipError_t launch_fused_bwd(const FusedArgs& a, int B, int D, int energy, int loss, float beta,
                             bool out_bf16, hipStream_t s, BlockRoute route = kRouteAuto);
-// whether the backward takes the one-pass kernel (D = 64, at most 16 row
-// blocks of 256), whose partials are indexed by 256-row blocks
+// whether the backward's partials are those of 256-row blocks (D = 64, at most
+// 16 of them), from the one-pass kernel or from the two passes
 bool fused_bwd_blocks(int B, int D);
 
 // actor.hip: the policy step's elementwise/row kernels
